@@ -17,8 +17,12 @@
 //  * The loop is software-pipelined by hand: per stage four groups of MFMAs, each covering the LDS
 //    latency of the next operand fragments; one workgroup barrier per stage, placed before the last
 //    group; the wait in front of it is a counted vmcnt (the youngest block stays in flight).
-//  * v_mfma_f32_32x32x16_f16 is issued "transposed" (W rows feed the instruction's row operand, X
-//    rows its column operand) so a lane owns 4 consecutive output columns per accumulator quad.
+//  * v_mfma_f32_16x16x32_f16, not 32x32x16: at the board's power limit throughput is set by energy per
+//    flop, and the 16 x 16 form moves fewer accumulator bytes through the register file per flop.  A
+//    register-only loop on N(0, 1) x N(0, 0.02) operands runs at 1625 TFLOP/s with the 32 x 32 form and
+//    at 1835 with this one; this kernel went from 1225 to 1400 (M = 24576, N = 14336, K = 7168).
+//  * The MFMA is issued "transposed" (W rows feed the instruction's row operand, X rows its column
+//    operand) so a lane owns 4 consecutive output columns of one row per accumulator tile.
 //  * Epilogue: bias + conversion in registers, C tile staged through LDS, global stores of whole
 //    512-byte row pieces.  Stores straight from registers (8-byte pieces, or 16-byte pieces after a
 //    v_permlane32_swap) cost 10-15 % of the kernel: 32 rows x 32 bytes per instruction is a poor write.
@@ -31,7 +35,7 @@
 //  * Rotary models (HD = head width 64 or 128): the cache holds K after the rotary embedding, so the
 //    recomputed K columns are rotated in the epilogue with the position of their row
 //    (pos0 + row / batch), in float32 and in registers: a wave tile is 128 columns wide, so a
-//    column and its partner at distance HD/2 sit in the same lane, two or one accumulator tiles
+//    column and its partner at distance HD/2 sit in the same lane, four or two accumulator tiles
 //    apart.  cos/sin come from a float2 table [position][HD/2] (L1/L2 hits: a tile spans few positions).
 #include "kvpr_internal.h"
 #include <mutex>
@@ -42,7 +46,7 @@ namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef const __attribute__((address_space(1))) void* gbl_ptr_t;
 
@@ -69,11 +73,12 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bias_f16(
     int xcd_split_n, RopeArgs rope) {
     constexpr int NW = WM * WN;
     constexpr int WTM = BM / WM, WTN = BN / WN;
-    constexpr int TM = WTM / 32, TN = WTN / 32;
+    constexpr int TM = WTM / 16, TN = WTN / 16, TMH = TM / 2, TNH = TN / 2;
     constexpr int LA = BM / 8 / NW, LW = BN / 8 / NW;     // DMA instructions per wave per block (8 rows x 128 B each)
     static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "tile/waves mismatch");
     constexpr int BLK_BYTES = (BM > BN ? BM : BN) * ROW_BYTES;
-    constexpr int NMFMA = TM * TN, NFRAG = TM + TN;
+    constexpr int NMFMA = TM * TNH;                       // per group: all A rows of the wave tile x half of its W rows, K = 32
+    static_assert(TM % 2 == 0 && TN % 2 == 0, "wave tile must split in halves");
 
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
 
@@ -142,45 +147,47 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bias_f16(
     };
     auto inc = [](int s, int d) { s += d; return s >= NBLK ? s - NBLK : s; };
 
-    // fragment addresses: row r of a block, k-step kk (16 halfs = two 16-byte chunks, lane half picks one).  The
-    // swizzle term (r/2)%8 depends only on lane%32 because every wave / tile offset is a multiple of 32 rows.
-    const int frow = lane & 31, fhalf = lane >> 5;
-    int koff[4];
+    // fragment addresses: row r = lane%16 of a 16-row tile, k-step kk (32 halfs = four 16-byte chunks, lane/16 picks one).
+    // The swizzle term (r/2)%8 depends only on lane%16 because every wave / tile offset is a multiple of 16 rows.
+    const int frow = lane & 15, fchunk = lane >> 4;
+    int koff[2];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) koff[kk] = frow * ROW_BYTES + (((kk * 2 + fhalf) ^ ((frow >> 1) & 7)) << 4);
+    for (int kk = 0; kk < 2; ++kk) koff[kk] = frow * ROW_BYTES + (((kk * 4 + fchunk) ^ ((frow >> 1) & 7)) << 4);
 
-    floatx16 acc[TN][TM];
+    floatx4 acc[TN][TM];
 #pragma unroll
     for (int i = 0; i < TN; ++i)
 #pragma unroll
-        for (int j = 0; j < TM; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int j = 0; j < TM; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    half8 af0[TM], wf0[TN], af1[TM], wf1[TN];
-    auto load_frags = [&](int sa, int sw, int kk, half8* af, half8* wf) {
-        const unsigned char* pa = lds + sa * BLK_BYTES + wm * WTM * ROW_BYTES + koff[kk];
-        const unsigned char* pw = lds + sw * BLK_BYTES + wn * WTN * ROW_BYTES + koff[kk];
+    // operand fragments: A of k-step 0 / 1, and the lower / upper half of the wave tile's W rows
+    half8 a0[TM], a1[TM], wlo[TNH], whi[TNH];
+    auto load_a = [&](int sa, int kk, half8* a, int t0, int t1) {
+        const unsigned char* p = lds + sa * BLK_BYTES + wm * WTM * ROW_BYTES + koff[kk];
 #pragma unroll
-        for (int t = 0; t < TM; ++t) af[t] = *reinterpret_cast<const half8*>(pa + t * 32 * ROW_BYTES);
-#pragma unroll
-        for (int t = 0; t < TN; ++t) wf[t] = *reinterpret_cast<const half8*>(pw + t * 32 * ROW_BYTES);
+        for (int t = t0; t < t1; ++t) a[t] = *reinterpret_cast<const half8*>(p + t * 16 * ROW_BYTES);
     };
-    auto mfma_group = [&](const half8* af, const half8* wf) {
+    auto load_w = [&](int sw, int kk, half8* w, int upper) {
+        const unsigned char* p = lds + sw * BLK_BYTES + (wn * WTN + upper * (WTN / 2)) * ROW_BYTES + koff[kk];
 #pragma unroll
-        for (int i = 0; i < TN; ++i)
+        for (int t = 0; t < TNH; ++t) w[t] = *reinterpret_cast<const half8*>(p + t * 16 * ROW_BYTES);
+    };
+    auto mfma_group = [&](const half8* a, const half8* w, int upper) {
+#pragma unroll
+        for (int i = 0; i < TNH; ++i)
 #pragma unroll
             for (int j = 0; j < TM; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf[i], af[j], acc[i][j], 0, 0, 0);
+                acc[upper * TNH + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[i], a[j], acc[upper * TNH + i][j], 0, 0, 0);
     };
-    auto interleave = [&](auto id) {
-        constexpr int ID = decltype(id)::value;
+    // one LDS read behind each of the group's first MFMAs
+    auto interleave = [&](auto id, auto reads) {
+        constexpr int ID = decltype(id)::value, READS = decltype(reads)::value, PAIRS = READS < NMFMA ? READS : NMFMA;
 #pragma unroll
-        for (int x = 0; x < NFRAG; ++x) {
+        for (int x = 0; x < PAIRS; ++x) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, ID);
             __builtin_amdgcn_sched_group_barrier(0x100, 1, ID);
         }
-        __builtin_amdgcn_sched_group_barrier(0x008, NMFMA - NFRAG, ID);
+        if constexpr (NMFMA > PAIRS) __builtin_amdgcn_sched_group_barrier(0x008, NMFMA - PAIRS, ID);
         __builtin_amdgcn_sched_barrier(0);
     };
     // Ring protocol.  Block 2*kt holds the A rows of stage kt, block 2*kt+1 its W rows; block j lives in slot j % 5.
@@ -197,31 +204,36 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bias_f16(
         wait_counts<0, 0>();
     }
     __builtin_amdgcn_s_barrier();
-    load_frags(0, 1, 0, af0, wf0);
+    load_a(0, 0, a0, 0, TM);
+    load_w(1, 0, wlo, 0);
 
-    // consumes the stage whose A rows sit in slot sa (W rows in sa + 1); on return (af0, wf0) hold k-step 0 of the next
+    // consumes the stage whose A rows sit in slot sa (W rows in sa + 1); on return a0 and wlo hold k-step 0 of the next.
+    // Four groups of MFMAs; each covers the LDS latency of what the next ones need.
     auto stage = [&](int kt, int sa, auto more) {
         constexpr bool MORE = decltype(more)::value;   // stage kt + 2 exists
         const int sw = inc(sa, 1), sa2 = inc(sa, 2), sw2 = inc(sa, 3), sfree = inc(sa, 4);
         if (MORE) issue_a(kt + 2, sfree);
-        load_frags(sa, sw, 1, af1, wf1);
-        mfma_group(af0, wf0);
-        interleave(std::integral_constant<int, 0>{});
-        load_frags(sa, sw, 2, af0, wf0);
-        mfma_group(af1, wf1);
-        interleave(std::integral_constant<int, 1>{});
-        load_frags(sa, sw, 3, af1, wf1);
-        mfma_group(af0, wf0);
-        interleave(std::integral_constant<int, 2>{});
+        load_w(sw, 0, whi, 1);
+        load_a(sa, 1, a1, 0, TMH);
+        mfma_group(a0, wlo, 0);
+        interleave(std::integral_constant<int, 0>{}, std::integral_constant<int, TNH + TMH>{});
+        load_a(sa, 1, a1, TMH, TM);
+        load_w(sw, 1, wlo, 0);
+        mfma_group(a0, whi, 1);
+        interleave(std::integral_constant<int, 1>{}, std::integral_constant<int, TM - TMH + TNH>{});
+        load_w(sw, 1, whi, 1);
+        mfma_group(a1, wlo, 0);
+        interleave(std::integral_constant<int, 2>{}, std::integral_constant<int, TNH>{});
         // this wave's reads of the stage are complete and its share of the next stage has landed
         if (MORE) wait_counts<LA, 1>();
         else wait_counts<0, 1>();
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         if (MORE) issue_w(kt + 2, sa);
-        load_frags(sa2, sw2, 0, af0, wf0);
-        mfma_group(af1, wf1);
-        interleave(std::integral_constant<int, 3>{});
+        load_a(sa2, 0, a0, 0, TM);
+        load_w(sw2, 0, wlo, 0);
+        mfma_group(a1, whi, 1);
+        interleave(std::integral_constant<int, 3>{}, std::integral_constant<int, TM + TNH>{});
     };
     int kt = 0, sa = 0;
     for (; kt + 2 < KT; ++kt) {
@@ -235,60 +247,55 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bias_f16(
     }
     {   // last stage: nothing follows
         const int sw = inc(sa, 1);
-        load_frags(sa, sw, 1, af1, wf1);
-        mfma_group(af0, wf0);
-        load_frags(sa, sw, 2, af0, wf0);
-        mfma_group(af1, wf1);
-        load_frags(sa, sw, 3, af1, wf1);
-        mfma_group(af0, wf0);
-        mfma_group(af1, wf1);
+        load_w(sw, 0, whi, 1);
+        load_a(sa, 1, a1, 0, TM);
+        mfma_group(a0, wlo, 0);
+        mfma_group(a0, whi, 1);
+        load_w(sw, 1, wlo, 0);
+        load_w(sw, 1, whi, 1);
+        mfma_group(a1, wlo, 0);
+        mfma_group(a1, whi, 1);
     }
 
     // ---- epilogue: bias + float16 conversion in registers, then through LDS so that every global
-    //      store instruction writes whole 512-byte pieces of C rows (accumulator register r of tile
-    //      (i, j) holds n = 32*i + 8*(r/4) + 4*(lane/32) + r%4, m = 32*j + lane%32 of the wave tile).
-    //      Rows are padded by 16 bytes: the 8-byte writes of 32 consecutive rows then spread over all banks.
+    //      store instruction writes whole 512-byte pieces of C rows (accumulator register e of tile
+    //      (i, j) holds n = 16*i + 4*(lane/16) + e, m = 16*j + lane%16 of the wave tile).
+    //      Rows are padded by 16 bytes: the 8-byte writes of 16 consecutive rows then spread over all banks.
     constexpr int CROW = BN * 2 + 16;
     __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0): this wave's operand reads are done
     __builtin_amdgcn_s_barrier();                  // ... and everybody else's: the stages can be overwritten
 #pragma unroll
     for (int i = 0; i < TN; ++i) {
+        const int nl = wn * WTN + i * 16 + 4 * fchunk;
+        if (bias && n0 + nl < N) {
+            const half4 b4 = *reinterpret_cast<const half4*>(bias + n0 + nl);
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int nl = wn * WTN + i * 32 + 8 * g + 4 * fhalf;
-            if (bias && n0 + nl < N) {
-                const half4 b4 = *reinterpret_cast<const half4*>(bias + n0 + nl);
+            for (int j = 0; j < TM; ++j)
 #pragma unroll
-                for (int j = 0; j < TM; ++j)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[i][j][g * 4 + e] += (float)b4[e];
-            }
+                for (int e = 0; e < 4; ++e) acc[i][j][e] += (float)b4[e];
         }
     }
     if constexpr (HD > 0) {
-        constexpr int IH = HD / 64;                // accumulator tiles between a column and its partner HD/2 columns on
+        constexpr int IH = HD / 32;                // accumulator tiles between a column and its partner HD/2 columns on
         static_assert(WTN % HD == 0 && TN % (2 * IH) == 0, "a wave tile must hold whole heads");
-        if (n0 + wn * WTN < rope.cols) {           // wave-uniform: this wave's 128 columns are K columns
+        if (n0 + wn * WTN < rope.cols) {           // wave-uniform: this wave's columns are K columns
 #pragma unroll
             for (int j = 0; j < TM; ++j) {
-                int64_t m = m0 + wm * WTM + j * 32 + frow;
+                int64_t m = m0 + wm * WTM + j * 16 + frow;
                 if (m > M - 1) m = M - 1;
                 const float2* trow = rope.table + (int64_t)(rope.pos0 + (int)(m / rope.batch)) * (HD / 2);
 #pragma unroll
                 for (int i = 0; i < TN; ++i) {
                     if ((i / IH) % 2 != 0) continue;   // second half of a head: handled with its partner
+                    const int f = (i % IH) * 16 + 4 * fchunk;
+                    const float4 cs0 = *reinterpret_cast<const float4*>(trow + f);
+                    const float4 cs1 = *reinterpret_cast<const float4*>(trow + f + 2);
+                    const float cv[4] = {cs0.x, cs0.z, cs1.x, cs1.z}, sv[4] = {cs0.y, cs0.w, cs1.y, cs1.w};
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int f = (i % IH) * 32 + 8 * g + 4 * fhalf;
-                        const float4 cs0 = *reinterpret_cast<const float4*>(trow + f);
-                        const float4 cs1 = *reinterpret_cast<const float4*>(trow + f + 2);
-                        const float cv[4] = {cs0.x, cs0.z, cs1.x, cs1.z}, sv[4] = {cs0.y, cs0.w, cs1.y, cs1.w};
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const float x1 = acc[i][j][g * 4 + e], x2 = acc[i + IH][j][g * 4 + e];
-                            acc[i][j][g * 4 + e] = x1 * cv[e] - x2 * sv[e];
-                            acc[i + IH][j][g * 4 + e] = x2 * cv[e] + x1 * sv[e];
-                        }
+                    for (int e = 0; e < 4; ++e) {
+                        const float x1 = acc[i][j][e], x2 = acc[i + IH][j][e];
+                        acc[i][j][e] = x1 * cv[e] - x2 * sv[e];
+                        acc[i + IH][j][e] = x2 * cv[e] + x1 * sv[e];
                     }
                 }
             }
@@ -296,17 +303,14 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bias_f16(
     }
 #pragma unroll
     for (int i = 0; i < TN; ++i) {
+        const int nl = wn * WTN + i * 16 + 4 * fchunk;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int nl = wn * WTN + i * 32 + 8 * g + 4 * fhalf;
+        for (int j = 0; j < TM; ++j) {
+            const int ml = wm * WTM + j * 16 + frow;
+            half4 o;
 #pragma unroll
-            for (int j = 0; j < TM; ++j) {
-                const int ml = wm * WTM + j * 32 + frow;
-                half4 o;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) o[e] = (_Float16)acc[i][j][g * 4 + e];
-                *reinterpret_cast<half4*>(lds + ml * CROW + nl * 2) = o;
-            }
+            for (int e = 0; e < 4; ++e) o[e] = (_Float16)acc[i][j][e];
+            *reinterpret_cast<half4*>(lds + ml * CROW + nl * 2) = o;
         }
     }
     __syncthreads();
@@ -325,13 +329,13 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bias_f16(
 
 int g_gemm_xcd_split_n = -1;   // -1 = default choice (debug hook; process-wide, set it only while no launch is in progress)
 
-// Which mapping of workgroups to tiles: measured on MI355X at M = 24576-26624, giving every XCD a band of W wins once
-// W no longer sits comfortably in the memory-side cache next to the A panels in flight (+3.7 % at N = 10240, K = 5120,
-// 100 MiB; more at N = 14336, K = 7168, 196 MiB), and loses 1-2 % when W is small (64 MiB at K = 4096).
+// Which mapping of workgroups to tiles: giving every XCD a band of W wins once W no longer sits comfortably in the
+// memory-side cache next to the A panels in flight (1410 against 1396 TFLOP/s at M = 24576, N = 14336, K = 7168, 196 MiB)
+// and is even with the row mapping or 0.5 % behind it at 100 and 64 MiB (hidden 5120 and 4096).
 bool band_mapping(int N, int K) {
     if ((N + 255) / 256 < 8) return false;
     if (g_gemm_xcd_split_n >= 0) return g_gemm_xcd_split_n != 0;
-    return (int64_t)N * K * 2 > ((int64_t)80 << 20);
+    return (int64_t)N * K * 2 > ((int64_t)128 << 20);
 }
 
 template <int BM, int BN, int WM, int WN, int GROUP_M, int HD = 0>
@@ -367,14 +371,13 @@ int launch_gemm(const void* a, const void* w, const void* bias, void* c, int64_t
                 hipStream_t st) {
     if (M == 0) return KVPR_OK;
     switch (g_gemm_variant) {   // variants other than 0 exist for tests and tuning sweeps
-        case 1: return launch_tile<256, 256, 2, 4, 8>(a, w, bias, c, M, N, K, ldc, st);
-        case 2: return launch_tile<256, 128, 2, 2, 8>(a, w, bias, c, M, N, K, ldc, st);
-        case 3: return launch_tile<128, 128, 2, 2, 8>(a, w, bias, c, M, N, K, ldc, st);
-        default:
-            // raster groups of 4 tile rows inside an XCD's band of W (7 tile columns at N = 14336: a 4 x 7 block is
-            // what 32 compute units cover), 8 with the row mapping: 1.5 % at M = 24576, N = 14336, K = 7168
-            return band_mapping(N, K) ? launch_tile<256, 256, 4, 2, 4>(a, w, bias, c, M, N, K, ldc, st)
-                                      : launch_tile<256, 256, 4, 2, 8>(a, w, bias, c, M, N, K, ldc, st);
+        case 1: return launch_tile<256, 256, 2, 4, 4>(a, w, bias, c, M, N, K, ldc, st);
+        case 2: return launch_tile<256, 128, 2, 2, 4>(a, w, bias, c, M, N, K, ldc, st);
+        case 3: return launch_tile<128, 128, 2, 2, 4>(a, w, bias, c, M, N, K, ldc, st);
+        // raster groups of 4 tile rows: 32 compute units of an XCD cover a 4 x 8 block.  8 rows per group: 1337 instead of
+        // 1410 TFLOP/s at M = 24576, N = 14336, K = 7168 (band mapping), 1330 instead of 1386 at M = 26624, N = 8192,
+        // K = 4096 (row mapping); 2 rows within 1 % of 4, 5 and 6 as 8.
+        default: return launch_tile<256, 256, 4, 2, 4>(a, w, bias, c, M, N, K, ldc, st);
     }
 }
 
@@ -384,9 +387,8 @@ int launch_gemm_rope(const void* a, const void* w, const void* bias, void* c, in
                      const void* table, int rope_cols, int head_dim, int batch, int pos0, hipStream_t st) {
     if (M == 0) return KVPR_OK;
     const RopeArgs r{(const float2*)table, rope_cols, batch, pos0};
-    if (head_dim == 64) return launch_tile<256, 256, 4, 2, 8, 64>(a, w, bias, c, M, N, K, ldc, st, r);
-    return band_mapping(N, K) ? launch_tile<256, 256, 4, 2, 4, 128>(a, w, bias, c, M, N, K, ldc, st, r)
-                              : launch_tile<256, 256, 4, 2, 8, 128>(a, w, bias, c, M, N, K, ldc, st, r);
+    return head_dim == 64 ? launch_tile<256, 256, 4, 2, 4, 64>(a, w, bias, c, M, N, K, ldc, st, r)
+                          : launch_tile<256, 256, 4, 2, 4, 128>(a, w, bias, c, M, N, K, ldc, st, r);
 }
 
 }  // namespace kvpr
