@@ -259,44 +259,41 @@ extern "C" int kvpr_profile_step(kvpr_ctx* c, int batch, int seq, kvpr_profile_t
 }
 
 // ---- MFMA ceiling probe (debug hook, used by `bench.py --power-probe`) ----
-// A register-only loop of the recompute GEMM's MFMA (v_mfma_f32_32x32x16_f16, a 4 x 2 tile of accumulators per wave,
-// two k-steps of fragments) on operand fragments read once from a_dev / w_dev: no LDS, no memory traffic in the
-// loop.  Its rate on given data is what the chip's power limit leaves to any fp16 GEMM on that data.
+// A register-only loop of the recompute GEMM's MFMA (v_mfma_f32_16x16x32_f16, the kernel's 4 x 8 tiles of accumulators per
+// wave, one k-step of fragments) on operand fragments read once from a_dev / w_dev: no LDS, no memory traffic in the
+// loop.  Its rate on given data is what the chip's power limit leaves to any fp16 GEMM on that data: 1835 TFLOP/s on
+// N(0, 1) x N(0, 0.02) operands (the 32x32x16 form: 1625).
 namespace {
 
 typedef _Float16 probe_half8 __attribute__((ext_vector_type(8)));
 typedef float probe_floatx16 __attribute__((ext_vector_type(16)));
+typedef float probe_floatx4 __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(512) void mfma_loop_kernel(const _Float16* __restrict__ xa, const _Float16* __restrict__ xw,
                                                          size_t n_a, size_t n_w, float* __restrict__ out, int iters) {
-    probe_half8 w[2][4], a[2][2];
+    probe_half8 w[8], a[4];
     const size_t t = (size_t)blockIdx.x * 512 + threadIdx.x;
-    for (int s = 0; s < 2; ++s) {
-        for (int i = 0; i < 4; ++i) w[s][i] = *reinterpret_cast<const probe_half8*>(xw + ((((t * 8 + s * 4 + i) * 8) % (n_w - 7)) & ~(size_t)7));
-        for (int j = 0; j < 2; ++j) a[s][j] = *reinterpret_cast<const probe_half8*>(xa + ((((t * 4 + s * 2 + j) * 8) % (n_a - 7)) & ~(size_t)7));
-    }
-    probe_floatx16 c[4][2];
-    for (int i = 0; i < 4; ++i)
-        for (int j = 0; j < 2; ++j)
-            for (int r = 0; r < 16; ++r) c[i][j][r] = 0.f;
+    for (int i = 0; i < 8; ++i) w[i] = *reinterpret_cast<const probe_half8*>(xw + ((((t * 8 + i) * 8) % (n_w - 7)) & ~(size_t)7));
+    for (int j = 0; j < 4; ++j) a[j] = *reinterpret_cast<const probe_half8*>(xa + ((((t * 4 + j) * 8) % (n_a - 7)) & ~(size_t)7));
+    probe_floatx4 c[8][4];
+    for (int i = 0; i < 8; ++i)
+        for (int j = 0; j < 4; ++j) c[i][j] = probe_floatx4{0.f, 0.f, 0.f, 0.f};
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+        for (int i = 0; i < 8; ++i)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) c[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[s][i], a[s][j], c[i][j], 0, 0, 0);
+            for (int j = 0; j < 4; ++j) c[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[i], a[j], c[i][j], 0, 0, 0);
     }
     float sum = 0.f;
-    for (int i = 0; i < 4; ++i)
-        for (int j = 0; j < 2; ++j)
-            for (int r = 0; r < 16; ++r) sum += c[i][j][r];
+    for (int i = 0; i < 8; ++i)
+        for (int j = 0; j < 4; ++j)
+            for (int r = 0; r < 4; ++r) sum += c[i][j][r];
     out[t] = sum;
 }
 
 }  // namespace
 
-// a_dev / w_dev: float16 arrays of n_a / n_w elements (>= 8 each); out_dev: float32 [256 * 512]; flops = 256 * 8 * iters * 16 * 32768
+// a_dev / w_dev: float16 arrays of n_a / n_w elements (>= 8 each); out_dev: float32 [256 * 512]; flops = 256 * 8 * iters * 32 * 16384
 extern "C" int kvpr_debug_mfma_loop(const void* a_dev, const void* w_dev, int64_t n_a, int64_t n_w, void* out_dev, int iters, void* stream) {
     if (!a_dev || !w_dev || !out_dev || n_a < 8 || n_w < 8 || iters < 1) return fail(KVPR_E_INVAL, "bad mfma loop arguments");
     hipLaunchKernelGGL(mfma_loop_kernel, dim3(256), dim3(512), 0, (hipStream_t)stream, (const _Float16*)a_dev, (const _Float16*)w_dev,
@@ -306,7 +303,7 @@ extern "C" int kvpr_debug_mfma_loop(const void* a_dev, const void* w_dev, int64_
 }
 
 // ---- clock keep-alive (kvpr_set_keep_warm) ----
-// The same register-only MFMA loop, bounded by wall time: every wave leaves once `budget_ticks` of the constant-rate
+// A register-only MFMA loop (32x32x16 form: it is meant to draw power), bounded by wall time: every wave leaves once `budget_ticks` of the constant-rate
 // wall clock have passed since it started, and after max_iters iterations at the latest.
 namespace {
 
