@@ -37,6 +37,17 @@
 #include <mutex>
 
 namespace kvpr {
+
+int compute_units() {
+    static int n = 0;
+    if (n == 0) {
+        int dev = 0, v = 0;
+        if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) n = v;
+        else n = 256;
+    }
+    return n;
+}
+
 namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
@@ -360,16 +371,6 @@ int launch_t(const void* x, const void* w, const void* bias, void* y32, void* y1
 // minimises rounds x (tiles + 1.5) (ties: the wider workgroup), bounded by the LDS reduction buffer (TPW * MT <= 8 keeps it
 // at 64 KiB) and by the accumulator registers.  The model orders all 32 measured (shape, tiles per workgroup) pairs of
 // hidden 4096 / 7168, batch 32 correctly; e.g. q|k|v at hidden 7168 (1344 tiles): 3 per workgroup 85 us, 2: 95 us, 4: 110 us.
-int compute_units() {
-    static int n = 0;
-    if (n == 0) {
-        int dev = 0, v = 0;
-        if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) n = v;
-        else n = 256;
-    }
-    return n;
-}
-
 template <int MT>
 int launch_mt(const void* x, const void* w, const void* bias, void* y32, void* y16, int M, int N, int K,
               int out_f32_cols, int64_t ld16, int relu, void* ws, size_t ws_bytes, hipStream_t st) {

@@ -17,6 +17,8 @@ int fail(int code, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
                                 hipGetErrorString(e_), __FILE__, __LINE__);               \
     } while (0)
 
+int compute_units();   // of the current device, read once
+
 // kernels (each validates nothing: callers check shapes first)
 int launch_gemm(const void* a, const void* w, const void* bias, void* c, int64_t M, int N, int K,
                 int64_t ldc, hipStream_t st);
