@@ -45,8 +45,8 @@ struct kvpr_ctx {
     void* attn_ws = nullptr;
     void* tok_ws = nullptr;              // token GEMM K-slice workspace (tickets, then partial tiles)
     size_t tok_ws_bytes = 0;
-    // hidden-state scratch of the full decoder layer
-    half *hid = nullptr, *xn = nullptr, *attn_out = nullptr, *ffn1 = nullptr, *ffn2 = nullptr;
+    // hidden-state scratch of the full decoder layer; resid: the residual stream between attention block and FFN
+    half *hid = nullptr, *xn = nullptr, *resid = nullptr, *ffn1 = nullptr;
     // fences (timing disabled)
     hipEvent_t ev_x[2]{}, ev_kv[2]{}, ev_free[2]{}, ev_proj = nullptr, ev_store = nullptr, ev_begin = nullptr;
     static constexpr int kMaxChunks = 32;

@@ -85,7 +85,7 @@ struct WeightFence {
 };
 
 int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weights* w, const half* x_new, half* out,
-                  int buf, LayerEvents* ev, bool fence_copy_to_start, const WeightFence* wf = nullptr) {
+                  int buf, LayerEvents* ev, bool fence_copy_to_start, const WeightFence* wf = nullptr, const half* residual = nullptr) {
     const int b = c->d.batch, h = c->d.hidden;
     const size_t xr = c->x_row_halfs(), kr = c->kv_row_halfs();
     const size_t xsb = c->x_store_bytes(), ksb = c->kv_store_bytes();
@@ -264,8 +264,9 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
     c->free_recorded[buf] = true;
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::a1], c->compute));
 
-    // ---- output projection (Eq. 3) ----
-    if (int rc = kvpr::launch_token_gemm_flags(c->z16, w->wo, w->bo, nullptr, out, b, h, h, 0, h, 0, c->compute, c->tok_ws, c->tok_ws_bytes))
+    // ---- output projection (Eq. 3); in a decoder layer with the residual stream added ----
+    if (int rc = kvpr::launch_token_gemm_flags(c->z16, w->wo, w->bo, nullptr, out, b, h, h, 0, h, 0, c->compute, c->tok_ws, c->tok_ws_bytes,
+                                                 residual))
         return rc;
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::o1], c->compute));
     KVPR_HIP(hipStreamWaitEvent(c->compute, c->ev_store, 0));
@@ -395,7 +396,7 @@ void destroy_impl(kvpr_ctx* c) {
         for (hipEvent_t e : we) if (e) (void)hipEventDestroy(e);
     }
     if (c->wstream) (void)hipStreamDestroy(c->wstream);
-    void* dev[] = {c->qk32, c->rope_tab, c->q32, c->z16, c->attn_ws, c->tok_ws, c->hid, c->xn, c->attn_out, c->ffn1, c->ffn2, c->dw[0], c->dw[1], c->hid_all};
+    void* dev[] = {c->qk32, c->rope_tab, c->q32, c->z16, c->attn_ws, c->tok_ws, c->hid, c->xn, c->resid, c->ffn1, c->dw[0], c->dw[1], c->hid_all};
     for (void* p : dev) if (p) (void)hipFree(p);
     hipEvent_t evs[] = {c->ev_proj, c->ev_store, c->ev_begin};
     for (hipEvent_t e : evs) if (e) (void)hipEventDestroy(e);
@@ -623,7 +624,7 @@ int create_impl(const kvpr_model_desc* d, int n_gpu_batches, void* compute_strea
             return bail(KVPR_E_HIP, "rotary table upload", e);
     }
     if (d->ffn_dim > 0) {
-        half** bufs[] = {&c->hid, &c->xn, &c->attn_out, &c->ffn2};
+        half** bufs[] = {&c->hid, &c->xn, &c->resid};
         for (half** p : bufs)
             if ((e = hipMalloc((void**)p, bh * sizeof(half))) != hipSuccess) return bail(KVPR_E_NOMEM, "hidden-state buffer", e);
         // gated FFN: [gate | up] (2 ffn columns) followed by their gated product (ffn columns)
@@ -800,24 +801,21 @@ int pre_attention_norm(kvpr_ctx* c, const kvpr_layer_weights* w, const half* hid
     return kvpr::launch_layernorm(hid_in, w->ln1_g, w->ln1_b, c->xn, b, h, c->compute);
 }
 
-// hid_out = r + FFN(norm(r)),  r = hid_in + attn_out.  OPT: LayerNorm, ReLU FFN with biases (Eq. 4);
+// hid_out = r + FFN(norm(r)), r = c->resid.  OPT: LayerNorm, ReLU FFN with biases (Eq. 4);
 // LLaMA: RMSNorm, down(silu(gate) * up) with w1 = [gate; up] stacked
-int residual_and_ffn(kvpr_ctx* c, const kvpr_layer_weights* w, const half* hid_in, half* hid_out) {
+int ffn_block(kvpr_ctx* c, const kvpr_layer_weights* w, half* hid_out) {
     const int b = c->d.batch, h = c->d.hidden, f = c->d.ffn_dim;
-    const size_t bh = (size_t)b * h;
-    if (int rc = kvpr::launch_add(hid_in, c->attn_out, c->ffn2, bh, c->compute)) return rc;      // ffn2 = residual stream
     if (c->llama) {
         half* prod = c->ffn1 + (size_t)b * 2 * f;
-        if (int rc = kvpr::launch_rmsnorm(c->ffn2, w->ln2_g, c->xn, b, h, c->compute)) return rc;
+        if (int rc = kvpr::launch_rmsnorm(c->resid, w->ln2_g, c->xn, b, h, c->compute)) return rc;
         if (int rc = kvpr::launch_token_gemm_flags(c->xn, w->w1, nullptr, nullptr, c->ffn1, b, 2 * f, h, 0, 2 * (int64_t)f, 0, c->compute, c->tok_ws, c->tok_ws_bytes)) return rc;
         if (int rc = kvpr::launch_silu_mul(c->ffn1, prod, b, f, c->compute)) return rc;
-        if (int rc = kvpr::launch_token_gemm_flags(prod, w->w2, nullptr, nullptr, c->attn_out, b, h, f, 0, h, 0, c->compute, c->tok_ws, c->tok_ws_bytes)) return rc;
+        return kvpr::launch_token_gemm_flags(prod, w->w2, nullptr, nullptr, hid_out, b, h, f, 0, h, 0, c->compute, c->tok_ws, c->tok_ws_bytes, c->resid);
     } else {
-        if (int rc = kvpr::launch_layernorm(c->ffn2, w->ln2_g, w->ln2_b, c->xn, b, h, c->compute)) return rc;
+        if (int rc = kvpr::launch_layernorm(c->resid, w->ln2_g, w->ln2_b, c->xn, b, h, c->compute)) return rc;
         if (int rc = kvpr::launch_token_gemm_flags(c->xn, w->w1, w->b1, nullptr, c->ffn1, b, f, h, 0, f, 1, c->compute, c->tok_ws, c->tok_ws_bytes)) return rc;
-        if (int rc = kvpr::launch_token_gemm_flags(c->ffn1, w->w2, w->b2, nullptr, c->attn_out, b, h, f, 0, h, 0, c->compute, c->tok_ws, c->tok_ws_bytes)) return rc;
+        return kvpr::launch_token_gemm_flags(c->ffn1, w->w2, w->b2, nullptr, hid_out, b, h, f, 0, h, 0, c->compute, c->tok_ws, c->tok_ws_bytes, c->resid);
     }
-    return kvpr::launch_add(c->ffn2, c->attn_out, hid_out, bh, c->compute);
 }
 
 }  // namespace
@@ -863,9 +861,10 @@ extern "C" int kvpr_decode_step(kvpr_ctx* c, int seq, const kvpr_layer_weights* 
         half* hid_out = (i == L - 1) ? (half*)x_out_dev : c->hid;
         // pre-norm -> attention block -> residual -> norm -> FFN -> residual
         if (int rc = pre_attention_norm(c, w, hid_in)) return rc;
-        if (int rc = enqueue_layer(c, i, seq, ls[i], w, c->xn, c->attn_out, i % c->nbuf, per_layer ? &c->tev[i] : nullptr, false))
+        if (int rc = enqueue_layer(c, i, seq, ls[i], w, c->xn, c->resid, i % c->nbuf, per_layer ? &c->tev[i] : nullptr, false, nullptr,
+                                   hid_in))
             return rc;
-        if (int rc = residual_and_ffn(c, w, hid_in, hid_out)) return rc;
+        if (int rc = ffn_block(c, w, hid_out)) return rc;
         hid_in = hid_out;
     }
     if (int rc = step_end(c)) return rc;
@@ -888,9 +887,7 @@ extern "C" int kvpr_greedy_next(const void* hidden_dev, const void* w_lm_dev, co
     if ((emb_dev == nullptr) != (x_next_dev == nullptr)) return fail(KVPR_E_INVAL, "emb_dev and x_next_dev go together");
     hipStream_t st = (hipStream_t)stream;
     if (int rc = kvpr::launch_token_gemm_flags(hidden_dev, w_lm_dev, nullptr, logits_dev, nullptr, batch, vocab, hidden, vocab, 0, 0, st)) return rc;
-    if (int rc = kvpr::launch_argmax_rows((const float*)logits_dev, batch, vocab, tokens_dev, st)) return rc;
-    if (emb_dev) return kvpr::launch_gather_rows(emb_dev, tokens_dev, x_next_dev, batch, hidden, st);
-    return KVPR_OK;
+    return kvpr::launch_argmax_gather((const float*)logits_dev, batch, vocab, tokens_dev, emb_dev, x_next_dev, hidden, st);
 }
 
 // ---- column-by-column schedule with offloaded weights (Sec. 3.2, Sec. 3.3, Algorithm 1) ----
@@ -1000,10 +997,10 @@ extern "C" int kvpr_decode_step_columns(kvpr_ctx* c, int seq, const void* x_in_d
             // waits for Wq, Wo and the FFN matrices, which may still be on the link (Sec. 3.3 fine-grained MHA pipeline)
             KVPR_HIP(hipStreamWaitEvent(c->compute, c->weight_pipeline ? c->ev_wkv[wb] : c->ev_wall[wb], 0));
             if (int rc = pre_attention_norm(c, &w, hid_in)) return rc;
-            if (int rc = enqueue_layer(c, slot, seq, ls[slot], &w, c->xn, c->attn_out, slot % c->nbuf,
-                                       per_slot ? &c->tev[slot] : nullptr, false, &wf))
+            if (int rc = enqueue_layer(c, slot, seq, ls[slot], &w, c->xn, c->resid, slot % c->nbuf,
+                                       per_slot ? &c->tev[slot] : nullptr, false, &wf, hid_in))
                 return rc;
-            if (int rc = residual_and_ffn(c, &w, hid_in, hid_out)) return rc;
+            if (int rc = ffn_block(c, &w, hid_out)) return rc;
             if (c->hid_offload) {
                 if (j > 0) {
                     KVPR_HIP(hipEventRecord(c->ev_hin_free[par], c->compute));

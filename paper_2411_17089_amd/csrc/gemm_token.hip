@@ -56,13 +56,21 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 constexpr int SLAB = 128;   // K columns per wave step: 4 MFMA k-steps of 32
 constexpr int TG_WAVES = 8;
 
+// one float16 output; with a residual it is rounded once by itself and once more with the residual added, as the two
+// separate operations give it
+__device__ __forceinline__ void store16(_Float16* __restrict__ y, const _Float16* __restrict__ res, int64_t at, float v) {
+    _Float16 o = (_Float16)v;
+    if (res) o = (_Float16)((float)o + (float)res[at]);
+    y[at] = o;
+}
+
 template <int MT, int TPW>
 __global__ __launch_bounds__(TG_WAVES * 64) void token_gemm(const _Float16* __restrict__ x,
                                                             const _Float16* __restrict__ W,
                                                             const _Float16* __restrict__ bias,
                                                             float* __restrict__ y32, _Float16* __restrict__ y16,
                                                             int M, int N, int K, int out_f32_cols, int64_t ld16,
-                                                            int relu) {
+                                                            int relu, const _Float16* __restrict__ res) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane & 15, c = lane >> 4;
     const int n0 = blockIdx.x * (16 * TPW);
@@ -154,7 +162,7 @@ __global__ __launch_bounds__(TG_WAVES * 64) void token_gemm(const _Float16* __re
         if (n < out_f32_cols)
             y32[(int64_t)m * out_f32_cols + n] = v;
         else
-            y16[(int64_t)m * ld16 + (n - out_f32_cols)] = (_Float16)v;
+            store16(y16, res, (int64_t)m * ld16 + (n - out_f32_cols), v);
     }
 }
 
@@ -169,7 +177,8 @@ template <int RB, int MT>
 __global__ __launch_bounds__(256) void token_gemm_wide(const _Float16* __restrict__ x, const _Float16* __restrict__ W,
                                                        const _Float16* __restrict__ bias, float* __restrict__ y32,
                                                        _Float16* __restrict__ y16, int M, int N, int K, int out_f32_cols,
-                                                       int64_t ld16, int relu, float* part, unsigned* ticket) {
+                                                       int64_t ld16, int relu, float* part, unsigned* ticket,
+                                                       const _Float16* __restrict__ res) {
     constexpr int RT = RB / 64;                             // 16-row tiles of W per wave
     constexpr int WI = RB / 16;                             // W DMA instructions per wave and stage (4 rows each, 4 waves)
     constexpr int WBYTES = RB * WIDE_ROW_BYTES, XBYTES = MT * 16 * WIDE_ROW_BYTES, STAGE = WBYTES + XBYTES;
@@ -323,13 +332,13 @@ __global__ __launch_bounds__(256) void token_gemm_wide(const _Float16* __restric
                 if (n < out_f32_cols)
                     y32[(int64_t)m * out_f32_cols + n] = v;
                 else
-                    y16[(int64_t)m * ld16 + (n - out_f32_cols)] = (_Float16)v;
+                    store16(y16, res, (int64_t)m * ld16 + (n - out_f32_cols), v);
             }
 }
 
 template <int RB, int MT>
 int launch_wide(const void* x, const void* w, const void* bias, void* y32, void* y16, int M, int N, int K,
-                int out_f32_cols, int64_t ld16, int relu, int ks, void* ws, hipStream_t st) {
+                int out_f32_cols, int64_t ld16, int relu, int ks, void* ws, const void* res, hipStream_t st) {
     auto kern = token_gemm_wide<RB, MT>;
     constexpr int lds_bytes = 2 * (RB + MT * 16) * WIDE_ROW_BYTES;
     static std::once_flag configured;
@@ -341,7 +350,7 @@ int launch_wide(const void* x, const void* w, const void* bias, void* y32, void*
     const unsigned grid = (unsigned)((N + RB - 1) / RB);
     hipLaunchKernelGGL(kern, dim3(grid, (unsigned)ks), dim3(256), lds_bytes, st, (const _Float16*)x, (const _Float16*)w,
                        (const _Float16*)bias, (float*)y32, (_Float16*)y16, M, N, K, out_f32_cols, ld16, relu,
-                       (float*)((unsigned char*)ws + TOKEN_WS_TICKET_BYTES), (unsigned*)ws);
+                       (float*)((unsigned char*)ws + TOKEN_WS_TICKET_BYTES), (unsigned*)ws, (const _Float16*)res);
     KVPR_HIP(hipGetLastError());
     return KVPR_OK;
 }
@@ -357,11 +366,11 @@ size_t wide_ws_bytes(int rb, int mt, int N, int ks) {
 
 template <int MT, int TPW>
 int launch_t(const void* x, const void* w, const void* bias, void* y32, void* y16, int M, int N, int K,
-             int out_f32_cols, int64_t ld16, int relu, hipStream_t st) {
+             int out_f32_cols, int64_t ld16, int relu, const void* res, hipStream_t st) {
     const unsigned grid = (unsigned)((N + 16 * TPW - 1) / (16 * TPW));
     hipLaunchKernelGGL((token_gemm<MT, TPW>), dim3(grid), dim3(TG_WAVES * 64), 0, st, (const _Float16*)x,
                        (const _Float16*)w, (const _Float16*)bias, (float*)y32, (_Float16*)y16, M, N, K, out_f32_cols,
-                       ld16, relu);
+                       ld16, relu, (const _Float16*)res);
     KVPR_HIP(hipGetLastError());
     return KVPR_OK;
 }
@@ -373,7 +382,7 @@ int launch_t(const void* x, const void* w, const void* bias, void* y32, void* y1
 // hidden 4096 / 7168, batch 32 correctly; e.g. q|k|v at hidden 7168 (1344 tiles): 3 per workgroup 85 us, 2: 95 us, 4: 110 us.
 template <int MT>
 int launch_mt(const void* x, const void* w, const void* bias, void* y32, void* y16, int M, int N, int K,
-              int out_f32_cols, int64_t ld16, int relu, void* ws, size_t ws_bytes, hipStream_t st) {
+              int out_f32_cols, int64_t ld16, int relu, void* ws, size_t ws_bytes, const void* res, hipStream_t st) {
     // wide kernel: 128 (or 64) features per workgroup once that gives about 150 workgroups, over all of K; with a
     // workspace also for narrower outputs, K cut into slices until there are about two workgroups per compute unit
     if (K % WIDE_KB == 0 && g_token_tpw <= 0) {
@@ -403,8 +412,8 @@ int launch_mt(const void* x, const void* w, const void* bias, void* y32, void* y
             while (ks > 1 && wide_ws_bytes(rb, MT, N, ks) > ws_bytes) --ks;
             if (ks == 1 && g_token_wide < 0 && (N + rb - 1) / rb < 144) rb = 0;   // nothing to split after all: the narrow kernel
         }
-        if (rb == 128) return launch_wide<128, MT>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ks, ws, st);
-        if (rb == 64) return launch_wide<64, MT>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ks, ws, st);
+        if (rb == 128) return launch_wide<128, MT>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ks, ws, res, st);
+        if (rb == 64) return launch_wide<64, MT>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ks, ws, res, st);
     }
     const int tiles = (N + 15) / 16;
     const int cap = 8 / MT;
@@ -420,26 +429,27 @@ int launch_mt(const void* x, const void* w, const void* bias, void* y32, void* y
         }
     }
     if (tpw > cap) tpw = cap;
-    if (tpw >= 8) return launch_t<MT, (8 / MT >= 8 ? 8 : 1)>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, st);
-    if (tpw >= 4) return launch_t<MT, (8 / MT >= 4 ? 4 : 1)>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, st);
-    if (tpw == 3) return launch_t<MT, (8 / MT >= 3 ? 3 : 1)>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, st);
-    if (tpw == 2) return launch_t<MT, (8 / MT >= 2 ? 2 : 1)>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, st);
-    return launch_t<MT, 1>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, st);
+    if (tpw >= 8) return launch_t<MT, (8 / MT >= 8 ? 8 : 1)>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, res, st);
+    if (tpw >= 4) return launch_t<MT, (8 / MT >= 4 ? 4 : 1)>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, res, st);
+    if (tpw == 3) return launch_t<MT, (8 / MT >= 3 ? 3 : 1)>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, res, st);
+    if (tpw == 2) return launch_t<MT, (8 / MT >= 2 ? 2 : 1)>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, res, st);
+    return launch_t<MT, 1>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, res, st);
 }
 
 }  // namespace
 
-// flags bit 0: ReLU.  ws (optional, device): workspace that lets a narrow output split K over several workgroups; its
+// flags bit 0: ReLU.  residual (optional): float16, laid out as y16, added to the float16 outputs.  ws (optional, device): workspace that lets a narrow output split K over several workgroups; its
 // first 4096 bytes must be zero before the first launch that uses it and are zero again when a launch ends; launches
 // that share a workspace must not overlap.
 int launch_token_gemm_flags(const void* x, const void* w, const void* bias, void* y32, void* y16, int M, int N, int K,
-                            int out_f32_cols, int64_t ld16, int flags, hipStream_t st, void* ws, size_t ws_bytes) {
+                            int out_f32_cols, int64_t ld16, int flags, hipStream_t st, void* ws, size_t ws_bytes,
+                            const void* residual) {
     const int relu = flags & 1;
     if (ws_bytes <= TOKEN_WS_TICKET_BYTES) ws = nullptr;
-    if (M <= 16) return launch_mt<1>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ws, ws_bytes, st);
-    if (M <= 32) return launch_mt<2>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ws, ws_bytes, st);
-    if (M <= 48) return launch_mt<3>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ws, ws_bytes, st);
-    return launch_mt<4>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ws, ws_bytes, st);
+    if (M <= 16) return launch_mt<1>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ws, ws_bytes, residual, st);
+    if (M <= 32) return launch_mt<2>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ws, ws_bytes, residual, st);
+    if (M <= 48) return launch_mt<3>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ws, ws_bytes, residual, st);
+    return launch_mt<4>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ws, ws_bytes, residual, st);
 }
 
 // enough for 8 K slices of an output of `N` features and `M` rows

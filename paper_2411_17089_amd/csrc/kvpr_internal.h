@@ -29,13 +29,12 @@ int launch_attention_mixed(const void* q, const void* kv16, const void* kvq, voi
                            int hidden, int n_heads, int phase, hipStream_t st);
 int launch_token_gemm_flags(const void* x, const void* w, const void* bias, void* y32, void* y16, int M, int N,
                             int K, int out_f32_cols, int64_t ld16, int flags /*bit0: ReLU*/, hipStream_t st,
-                            void* ws = nullptr, size_t ws_bytes = 0);
+                            void* ws = nullptr, size_t ws_bytes = 0, const void* residual = nullptr);
 size_t token_gemm_workspace_bytes(int M, int N);
 int launch_fill_u16(void* p, size_t n_halfs, uint16_t pattern, hipStream_t st);
 int launch_fill_random(void* p, size_t n_halfs, float scale, uint32_t seed, hipStream_t st);
 int launch_layernorm(const void* x, const void* g, const void* b, void* y, int rows, int h, hipStream_t st);
-int launch_argmax_rows(const float* logits, int M, int N, int32_t* out, hipStream_t st);
-int launch_gather_rows(const void* table, const int32_t* idx, void* out, int M, int h, hipStream_t st);
+int launch_argmax_gather(const float* logits, int M, int N, int32_t* tokens, const void* table, void* x_next, int h, hipStream_t st);
 int launch_gemm_rope(const void* a, const void* w, const void* bias, void* c, int64_t M, int N, int K, int64_t ldc,
                      const void* table, int rope_cols, int head_dim, int batch, int pos0, hipStream_t st);
 int launch_rmsnorm(const void* x, const void* g, void* y, int rows, int h, hipStream_t st);
@@ -45,7 +44,6 @@ int launch_rope_token(const void* qk32, const void* table, int pos, int batch, i
 size_t int4_row_bytes(int cols);
 int launch_quant_int4(const void* src, void* dst, int64_t rows, int cols, hipStream_t st);
 int launch_dequant_int4(const void* src, void* dst, int64_t rows, int cols, hipStream_t st);
-int launch_add(const void* a, const void* b, void* y, size_t n, hipStream_t st);
 int launch_copy_bytes(const void* src, void* dst, size_t bytes, hipStream_t st);
 int launch_keep_warm(const void* w, size_t n_w, double seconds, double wall_clock_hz, void* sink, hipStream_t st);
 
