@@ -33,6 +33,7 @@ namespace kvpr {
 namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 
 constexpr int COLS_PER_GROUP = 64 * 8;   // columns one wave covers
@@ -151,32 +152,76 @@ __global__ __launch_bounds__(ATT_WAVES * 64) void attention_partial(
     }
 }
 
-// one thread per 8 columns: merge the per-split partials
-__global__ __launch_bounds__(256) void attention_combine(const float* __restrict__ ws_acc,
-                                                         const float* __restrict__ ws_ml,
-                                                         _Float16* __restrict__ z, int batch, int h, int splits) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int chunks = h / 8;
-    if (t >= (int64_t)batch * chunks) return;
-    const int n = (int)(t / chunks), c = (int)(t % chunks);
-    float m_tot = -INFINITY;
-    for (int sp = 0; sp < splits; ++sp) m_tot = fmaxf(m_tot, ws_ml[(((int64_t)sp * batch + n) * chunks + c) * 2]);
-    float l_tot = 0.f;
-    float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int sp = 0; sp < splits; ++sp) {
-        const float* ml = ws_ml + (((int64_t)sp * batch + n) * chunks + c) * 2;
-        const float wt = (ml[0] == -INFINITY) ? 0.f : exp2f(ml[0] - m_tot);
-        l_tot += ml[1] * wt;
-        const float* a = ws_acc + ((int64_t)sp * batch + n) * h + c * 8;
-        const float4 a0 = *reinterpret_cast<const float4*>(a), a1 = *reinterpret_cast<const float4*>(a + 4);
-        o[0] += a0.x * wt; o[1] += a0.y * wt; o[2] += a0.z * wt; o[3] += a0.w * wt;
-        o[4] += a1.x * wt; o[5] += a1.y * wt; o[6] += a1.z * wt; o[7] += a1.w * wt;
+// Merges the per-split partials.  A workgroup owns 256 columns of one sequence; its four waves share the splits, a lane
+// owns 4 columns.  The kernel is one round of latency: every wave asks for four splits at once and the partial sums meet
+// in LDS, where one thread per 8 columns walking all splits took 19.2 us for 32 splits of one sequence, hidden 4096
+// (2 workgroups, a chain of dependent loads).  The attention over 4097 positions: 34.4 -> 19.4 us.
+constexpr int COMBINE_COLS = 256, COMBINE_WAVES = 4;
+__global__ __launch_bounds__(COMBINE_WAVES * 64) void attention_combine(const float* __restrict__ ws_acc,
+                                                                        const float* __restrict__ ws_ml,
+                                                                        _Float16* __restrict__ z, int batch, int h, int splits) {
+    constexpr int U = 4;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = blockIdx.y;
+    const int col = blockIdx.x * COMBINE_COLS + lane * 4;
+    const int ccol = min(col, h - 4);                 // lanes beyond h shadow the last columns and never store
+    float m = -INFINITY, l = 0.f, o[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int sp0 = wave; sp0 < splits; sp0 += COMBINE_WAVES * U) {
+        float4 a[U];
+        float2 ml[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t row = (int64_t)min(sp0 + u * COMBINE_WAVES, splits - 1) * batch + n;
+            ml[u] = *reinterpret_cast<const float2*>(ws_ml + (row * (h / 8) + ccol / 8) * 2);
+            a[u] = *reinterpret_cast<const float4*>(ws_acc + row * h + ccol);
+        }
+        float m_new = m;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (sp0 + u * COMBINE_WAVES >= splits) ml[u].x = -INFINITY;
+            m_new = fmaxf(m_new, ml[u].x);
+        }
+        const float keep = m == -INFINITY ? 0.f : exp2f(m - m_new);
+        l *= keep;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] *= keep;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float wt = ml[u].x == -INFINITY ? 0.f : exp2f(ml[u].x - m_new);
+            l += ml[u].y * wt;
+            o[0] += a[u].x * wt; o[1] += a[u].y * wt; o[2] += a[u].z * wt; o[3] += a[u].w * wt;
+        }
+        m = m_new;
+    }
+    __shared__ float sm[COMBINE_WAVES][6][64];
+    sm[wave][0][lane] = m;
+    sm[wave][1][lane] = l;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sm[wave][2 + e][lane] = o[e];
+    __syncthreads();
+    if (wave != 0 || col >= h) return;
+    float m_tot = m;
+#pragma unroll
+    for (int w = 1; w < COMBINE_WAVES; ++w) m_tot = fmaxf(m_tot, sm[w][0][lane]);
+    float l_tot = 0.f, t[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < COMBINE_WAVES; ++w) {
+        const float wt = sm[w][0][lane] == -INFINITY ? 0.f : exp2f(sm[w][0][lane] - m_tot);
+        l_tot += sm[w][1][lane] * wt;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] += sm[w][2 + e][lane] * wt;
     }
     const float inv = 1.f / l_tot;
-    half8 out;
+    half4 out;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) out[e] = (_Float16)(o[e] * inv);
-    *reinterpret_cast<half8*>(z + (int64_t)n * h + c * 8) = out;
+    for (int e = 0; e < 4; ++e) out[e] = (_Float16)(t[e] * inv);
+    *reinterpret_cast<half4*>(z + (int64_t)n * h + col) = out;
+}
+
+int launch_combine(const float* ws_acc, const float* ws_ml, void* z, int batch, int h, int splits, hipStream_t st) {
+    hipLaunchKernelGGL(attention_combine, dim3((unsigned)((h + COMBINE_COLS - 1) / COMBINE_COLS), (unsigned)batch),
+                       dim3(COMBINE_WAVES * 64), 0, st, ws_acc, ws_ml, (_Float16*)z, batch, h, splits);
+    KVPR_HIP(hipGetLastError());
+    return KVPR_OK;
 }
 
 // merge the waves' running (max, sum, acc) through LDS; wave 0 returns the workgroup's partial in (m, l, o)
@@ -471,7 +516,9 @@ int g_attn_cfg = 1;       // (unroll, waves per workgroup) choice, see launch_at
 int g_attn_force_splits = 0;
 
 struct SplitPlan { int chunk, splits; };
-SplitPlan plan_splits(int batch, int hidden, int S, int cols_per_group = COLS_PER_GROUP) {
+// whole: chunks in whole rounds of a workgroup's waves
+SplitPlan plan_splits(int batch, int hidden, int S, int cols_per_group = COLS_PER_GROUP, bool whole = true) {
+    constexpr int ROUND = 32;                          // positions a workgroup's waves take per round (4 x 8, packed rows 8 x 4)
     const int groups = (hidden + cols_per_group - 1) / cols_per_group;
     int64_t base = (int64_t)groups * batch;
     int want = g_attn_force_splits > 0 ? g_attn_force_splits : (int)((g_attn_target_blocks + base - 1) / base);
@@ -479,8 +526,26 @@ SplitPlan plan_splits(int batch, int hidden, int S, int cols_per_group = COLS_PE
     if (g_attn_force_splits <= 0 && want > max_splits) want = max_splits;
     if (want < 1) want = 1;
     if (want > S) want = S;
-    const int chunk = (S + want - 1) / want;
+    int chunk = (S + want - 1) / want;
+    // a chunk of 129 positions takes five rounds, the last one for a single position: down to whole rounds where that
+    // adds at most an eighth to the splits, up otherwise (4097 positions, batch 1, hidden 4096: 20.9 us with 32 splits of
+    // 129, 19.4 with 33 of 128).  From eight rounds on a partial one is lost in the rest and equal chunks are better
+    // (16000 positions: 46.3 us with 32 splits of 500, 49 with 34 of 480).
+    if (whole && want > 1 && chunk <= 8 * ROUND && g_attn_force_splits <= 0) {
+        const int down = chunk / ROUND * ROUND;
+        chunk = down > 0 && ((S + down - 1) / down) * 8 <= want * 9 ? down : (chunk + ROUND - 1) / ROUND * ROUND;
+    }
     return {chunk, (S + chunk - 1) / chunk};           // no empty split
+}
+
+// Workgroups of 8 waves over all positions instead of 4 waves, splits and a combine launch: when half the compute units or
+// more get a workgroup that way but none gets two (batch 20, 700 positions, hidden 5120: 46.9 -> 42.6 us; batch 10, 1000
+// positions, hidden 7168: 52.6 -> 47.7; with 320 workgroups it is the slower one, 121 against 105), and when there are
+// only two rounds to share (97 positions, batch 2, hidden 768: 9.8 -> 8.8).
+bool one_wide_workgroup(int batch, int hidden, int S) {
+    if (g_attn_force_splits > 0 || g_attn_cfg != 1) return false;
+    const int64_t base = (int64_t)((hidden + COLS_PER_GROUP - 1) / COLS_PER_GROUP) * batch;
+    return S <= 128 ? base <= g_attn_target_blocks : base * 2 >= g_attn_target_blocks && base <= g_attn_target_blocks;
 }
 
 }  // namespace
@@ -496,8 +561,9 @@ size_t attention_workspace_bytes(int batch, int hidden, int n_heads, int S) {
 namespace {
 
 // the split choice launch_attention makes, with the workspace bound applied
-SplitPlan attention_plan(int batch, int hidden, int S) {
-    SplitPlan sp = plan_splits(batch, hidden, S);
+SplitPlan attention_plan(int batch, int hidden, int S, bool whole = true) {
+    if (whole && one_wide_workgroup(batch, hidden, S)) return {S, 1};
+    SplitPlan sp = plan_splits(batch, hidden, S, COLS_PER_GROUP, whole);
     if (sp.splits > 512) {                            // workspace bound above
         sp.chunk = (S + 511) / 512;
         sp.splits = (S + sp.chunk - 1) / sp.chunk;
@@ -505,13 +571,11 @@ SplitPlan attention_plan(int batch, int hidden, int S) {
     return sp;
 }
 
-}  // namespace
-
-int launch_attention(const void* q, const void* kv, void* z, void* ws, int S, int batch, int hidden, int n_heads,
-                     hipStream_t st) {
+int launch_attention_plan(SplitPlan sp, const void* q, const void* kv, void* z, void* ws, int S, int batch, int hidden, int n_heads,
+                          hipStream_t st) {
     const int d = hidden / n_heads;
-    const SplitPlan sp = attention_plan(batch, hidden, S);
     const int groups = (hidden + COLS_PER_GROUP - 1) / COLS_PER_GROUP;
+    const int cfg = sp.splits == 1 && one_wide_workgroup(batch, hidden, S) ? 3 : g_attn_cfg;
     float* ws_acc = (float*)ws;
     float* ws_ml = ws_acc + (int64_t)sp.splits * batch * hidden;
     const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)d));
@@ -520,7 +584,7 @@ int launch_attention(const void* q, const void* kv, void* z, void* ws, int S, in
     hipLaunchKernelGGL((attention_partial<D_, U_, W_>), grid, dim3(64 * W_), 0, st, (const float*)q, (const _Float16*)kv, \
                        ws_acc, ws_ml, (_Float16*)z, S, batch, hidden, sp.chunk, sp.splits, scale_log2)
     if (d == 128) {
-        switch (g_attn_cfg) {
+        switch (cfg) {
             case 1: KVPR_LAUNCH_PART(128, 8, 4); break;
             case 2: KVPR_LAUNCH_PART(128, 4, 8); break;
             case 3: KVPR_LAUNCH_PART(128, 8, 8); break;
@@ -529,7 +593,8 @@ int launch_attention(const void* q, const void* kv, void* z, void* ws, int S, in
             default: KVPR_LAUNCH_PART(128, 4, 4); break;
         }
     } else {
-        switch (g_attn_cfg) {
+        switch (cfg) {
+            case 3: KVPR_LAUNCH_PART(64, 8, 8); break;
             case 0: KVPR_LAUNCH_PART(64, 4, 4); break;
             case 2: KVPR_LAUNCH_PART(64, 4, 8); break;
             default: KVPR_LAUNCH_PART(64, 8, 4); break;
@@ -537,13 +602,14 @@ int launch_attention(const void* q, const void* kv, void* z, void* ws, int S, in
     }
 #undef KVPR_LAUNCH_PART
     KVPR_HIP(hipGetLastError());
-    if (sp.splits > 1) {
-        const int64_t threads = (int64_t)batch * (hidden / 8);
-        hipLaunchKernelGGL(attention_combine, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, ws_acc, ws_ml,
-                           (_Float16*)z, batch, hidden, sp.splits);
-        KVPR_HIP(hipGetLastError());
-    }
-    return KVPR_OK;
+    return sp.splits > 1 ? launch_combine(ws_acc, ws_ml, z, batch, hidden, sp.splits, st) : KVPR_OK;
+}
+
+}  // namespace
+
+int launch_attention(const void* q, const void* kv, void* z, void* ws, int S, int batch, int hidden, int n_heads,
+                     hipStream_t st) {
+    return launch_attention_plan(attention_plan(batch, hidden, S), q, kv, z, ws, S, batch, hidden, n_heads, st);
 }
 
 // ---- mixed float16 / packed attention in two phases (see the header comment) ----
@@ -621,11 +687,7 @@ int launch_attention_mixed(const void* q, const void* kv16, const void* kvq, voi
                                          fuse ? 0 : -1, z))
             return rc;
     if (fuse) return KVPR_OK;
-    const int64_t threads = (int64_t)batch * (hidden / 8);
-    hipLaunchKernelGGL(attention_combine, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, ws_acc, ws_ml,
-                       (_Float16*)z, batch, hidden, p.total);
-    KVPR_HIP(hipGetLastError());
-    return KVPR_OK;
+    return launch_combine(ws_acc, ws_ml, z, batch, hidden, p.total, st);
 }
 
 }  // namespace kvpr
@@ -666,14 +728,19 @@ extern "C" int kvpr_decode_attention_static(const void* q, const void* kv, void*
         return kvpr::fail(KVPR_E_INVAL, "head_dim must be 64 or 128");
     if (!q || !kv || !z) return kvpr::fail(KVPR_E_INVAL, "q / kv / z is null");
     // what this launch would keep in the workspace: (acc[h] float32 + (m, l) per 8 columns) per split and sequence
-    const kvpr::SplitPlan sp = kvpr::attention_plan(batch, hidden, S);
-    const int64_t need = sp.splits > 1 ? (int64_t)sp.splits * batch * ((int64_t)hidden * 4 + (int64_t)(hidden / 8) * 8) : 0;
-    if (need > (int64_t)KVPR_ATTENTION_STATIC_SCRATCH_BYTES)
+    // (which shapes fit is a property of the entry point: it goes by the fewest equal splits; whole rounds where they fit too)
+    auto bytes = [&](kvpr::SplitPlan p) {
+        return p.splits > 1 ? (int64_t)p.splits * batch * ((int64_t)hidden * 4 + (int64_t)(hidden / 8) * 8) : 0;
+    };
+    const kvpr::SplitPlan plain = kvpr::attention_plan(batch, hidden, S, false), whole = kvpr::attention_plan(batch, hidden, S);
+    constexpr int64_t room = KVPR_ATTENTION_STATIC_SCRATCH_BYTES;
+    if (bytes(plain) > room)
         return kvpr::fail(KVPR_E_RANGE, "this shape needs %lld bytes of partial results, the static scratch holds %lld: use "
-                          "kvpr_decode_attention with a workspace", (long long)need, (long long)KVPR_ATTENTION_STATIC_SCRATCH_BYTES);
+                          "kvpr_decode_attention with a workspace", (long long)bytes(plain), (long long)room);
     void* ws = nullptr;
     if (int rc = scratch_for_current_device(&ws)) return rc;
-    return kvpr::launch_attention(q, kv, z, ws, S, batch, hidden, n_heads, (hipStream_t)stream);
+    return kvpr::launch_attention_plan(bytes(whole) <= room ? whole : plain, q, kv, z, ws, S, batch, hidden, n_heads,
+                                       (hipStream_t)stream);
 }
 
 extern "C" int kvpr_debug_set_attention_kernel(int v) {
