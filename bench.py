@@ -567,7 +567,7 @@ def run_layer(args, model, b, s, split_arg=-1, sweep=(), attention=True, extensi
         "ms_total_events_min_median_max": [float(np.min([t.ms_total for t in tim])), float(np.median([t.ms_total for t in tim])),
                                            float(np.max([t.ms_total for t in tim]))],
         "bounds": {
-            "which": "builder = cost form '%s', l a multiple of %d, GEMM charged in whole 256-tile rounds; plain = Eq. 10 as "
+            "which": "builder = cost form '%s', l a multiple of %d, GEMM charged in whole rounds of one 64x128 tile per compute unit; plain = Eq. 10 as "
                      "printed (every integer l, divisible work); both with the start-up profile's constants" % (args.cost_model, args.granularity),
             "builder_bound_ms_at_split": t_bound_split * 1e3,
             "builder_eq10_bound_ms_at_its_optimum": t_eq10 * 1e3, "builder_eq10_l_star": l_eq10,

@@ -118,8 +118,9 @@ typedef struct {
     double h2d_peak_bytes_per_s; /* reported only: best rate over a 64 KiB .. 1 GiB sweep    */
     double gemm_alone_flops_per_s; /* reported only: the same GEMM with nothing else running             */
     int64_t gemm_round_flops;    /* extension of Eq. 9 (0 = the paper's divisible work): the recompute GEMM runs in
-                                    rounds of one 256 x 256 tile per compute unit; N_KV is charged rounded up to a
-                                    multiple of this many flops.  kvpr_profile fills it (n_CU * 2*256*256*hidden) */
+                                    rounds of one tile per compute unit; N_KV is charged rounded up to a
+                                    multiple of this many flops.  kvpr_profile fills it (n_CU * 2*64*128*hidden,
+                                    the smallest tile) */
     double layer_other_s;        /* the rest of one layer's GPU work at this batch / context (token projections,
                                     attention, output projection, FFN if the context has one): used by
                                     KVPR_COST_PIPE only, where it shares the GPU with the recomputation; 0 = ignore */

@@ -91,10 +91,12 @@ extern "C" int kvpr_profile(kvpr_ctx* c, int batch, int seq, kvpr_profile_t* out
                                                      c->d.head_dim, c->d.batch, 0, c->compute)
                             : kvpr::launch_gemm(c->dx[0], wtmp, nullptr, dkv, rows, 2 * h, h, 2 * (int64_t)h, c->compute); }, &t);
     const double gemm_flops = 4.0 * (double)rows * h * h;
-    {   // the GEMM's work quantum: one 256 x 256 output tile (2 * 256 * 256 * K flops) on each compute unit
+    {   // the GEMM's work quantum: one output tile of the smallest size (2 * 64 * 128 * K flops) on each compute unit.  No
+        // product costs less, and above that the choice among six tile sizes keeps the cost near proportional to the rows;
+        // charged in rounds of 256 x 256, 120 rows at hidden 1024 came out as 3.1e15 flop/s
         int dev = 0, n_cu = 0;
         if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n_cu > 0)
-            p.gemm_round_flops = (int64_t)n_cu * 2 * 256 * 256 * h;
+            p.gemm_round_flops = (int64_t)n_cu * 2 * 64 * 128 * h;
     }
     if (!rc) p.gemm_alone_flops_per_s = p.gemm_flops_per_s = gemm_flops / t;
     // v_gpu as the cost model uses it: Eq. 10's max() term has the GEMM and a cache copy running together, and the
