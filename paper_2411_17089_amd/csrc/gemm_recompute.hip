@@ -320,8 +320,9 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bias_f16(
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float x1 = acc[i][j][e], x2 = acc[i + IH][j][e];
-                        acc[i][j][e] = x1 * cv[e] - x2 * sv[e];
-                        acc[i + IH][j][e] = x2 * cv[e] + x1 * sv[e];
+                        // which product is rounded first is spelled out: left to contraction it differs between tiles
+                        acc[i][j][e] = fmaf(x1, cv[e], -(x2 * sv[e]));
+                        acc[i + IH][j][e] = fmaf(x2, cv[e], x1 * sv[e]);
                     }
                 }
             }

@@ -74,3 +74,18 @@ def test_tiles_agree_bit_for_bit(k, force):
         k.kvpr_recompute_gemm(A, W, None, c, M, N, K, N)
         first = c if first is None else first
         assert torch.equal(c, first), tile
+
+
+@pytest.mark.parametrize("heads,width", [(3, 128), (6, 64)])
+def test_rotary_tiles_agree_bit_for_bit(k, force, heads, width):
+    batch, l, pos0, h = 3, 100, 2, heads * width
+    g = torch.Generator().manual_seed(2)
+    A, W = torch.randn(batch * l, h, generator=g).half().cuda(), (torch.randn(2 * h, h, generator=g) * 0.05).half().cuda()
+    tab = dev(k.kvpr_rope_table(pos0 + l, width), torch.float32)
+    first = None
+    for tile in TILES:
+        c = torch.empty((batch * l, 2 * h), dtype=torch.float16, device="cuda")
+        force(tile)
+        k.kvpr_recompute_gemm_rope(A, W, None, c, batch * l, 2 * h, h, 2 * h, tab, pos0 + l, h, width, batch, pos0)
+        first = c if first is None else first
+        assert torch.equal(c, first), tile
