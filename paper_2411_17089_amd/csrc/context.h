@@ -46,9 +46,10 @@ struct kvpr_ctx {
     void* tok_ws = nullptr;              // token GEMM K-slice workspace (tickets, then partial tiles)
     size_t tok_ws_bytes = 0;
     // hidden-state scratch of the full decoder layer; resid: the residual stream between attention block and FFN
-    half *hid = nullptr, *xn = nullptr, *resid = nullptr, *ffn1 = nullptr;
+    // xn: the attention block's normalised input, by layer parity; xf: the FFN's
+    half *hid = nullptr, *xn[2] = {nullptr, nullptr}, *xf = nullptr, *resid = nullptr, *ffn1 = nullptr;
     // fences (timing disabled)
-    hipEvent_t ev_x[2]{}, ev_kv[2]{}, ev_free[2]{}, ev_proj = nullptr, ev_store = nullptr, ev_begin = nullptr;
+    hipEvent_t ev_x[2]{}, ev_kv[2]{}, ev_free[2]{}, ev_recomputed[2]{}, ev_proj = nullptr, ev_store = nullptr, ev_begin = nullptr;
     static constexpr int kMaxChunks = 32;
     hipEvent_t ev_chunk[2][kMaxChunks]{};   // per device buffer: "activation chunk j has landed"
     int chunks = 1;                          // 1 = the paper's schedule: all of X[0:l], then one GEMM
@@ -99,6 +100,10 @@ struct kvpr_ctx {
     // bytes of one position (all sequences of the batch) as the host store holds it and as it crosses the link
     size_t x_store_bytes() const { return qx ? d.batch * kvpr::int4_row_bytes(d.hidden) : x_row_halfs() * sizeof(half); }
     size_t kv_store_bytes() const { return qkv ? d.batch * kvpr::int4_row_bytes(2 * d.hidden) : kv_row_halfs() * sizeof(half); }
+    // The new token's rows go back to the host on the compute stream, right behind the projections, while they are few: the
+    // copy kernel takes 4 - 8 us there, a hand-over to the store stream costs 15 us of the host's time for each of its two
+    // waits and about 6 us on the compute stream for each of its two markers.  From 256 KiB on the copy is the longer one.
+    bool inline_store() const { return x_store_bytes() + kv_store_bytes() <= 256 * 1024; }
     int64_t flops_per_pos() const { return 4 * (int64_t)d.batch * d.hidden * d.hidden; }   // Eq. 8
     int plan_chunks() const { return (chunks > 1 && cost_model == KVPR_COST_EQ10) ? chunks : 1; }
 };

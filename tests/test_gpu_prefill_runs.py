@@ -1,0 +1,51 @@
+"""The prefill helper in runs of positions that overlap: rows as one product over all positions gives them, for one run, two,
+and the largest number with a remainder, float16 and packed, both architectures."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from kvpr_testlib import dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def k():
+    import paper_2411_17089_amd as k
+    return k
+
+
+@pytest.mark.parametrize("rotary", [False, True])
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("b,s", [(3, 41), (64, 150), (61, 601)])
+def test_rows_equal_one_product(k, b, s, packed, rotary):
+    h, H = 512, 4
+    rng = np.random.default_rng(s)
+    x = rng.standard_normal((s, b, h)).astype(np.float16)
+    w = {"wqkv": dev((rng.standard_normal((3 * h, h)) * 0.05).astype(np.float16)), "wo": dev(np.zeros((h, h), np.float16))}
+    if not rotary:
+        w["bqkv"] = dev((rng.standard_normal(3 * h) * 0.1).astype(np.float16))
+    ctx = k.kvpr_create(1, h, H, h // H, 0, b, s + 2, dtype=k.KVPR_F16 | (k.KVPR_KV_INT4 if packed else 0),
+                        arch=k.KVPR_ARCH_LLAMA if rotary else k.KVPR_ARCH_OPT)
+    try:
+        k.kvpr_store_write(ctx, 0, 0, s, x, None)
+        for _ in range(2):                                      # the second call reuses the events and the buffers
+            k.kvpr_store_prefill_kv(ctx, 0, s, k.make_weights(**w))
+        row = k.kvpr_int4_row_bytes(2 * h) if packed else 4 * h
+        address = k.kvpr_store_ptrs(ctx, 0)[1]
+        got = np.frombuffer((ctypes.c_ubyte * (s * b * row)).from_address(address), np.uint8).copy()
+    finally:
+        k.kvpr_destroy(ctx)
+    xd, out, wkv = dev(x.reshape(s * b, h)), torch.empty((s * b, 2 * h), dtype=torch.float16, device="cuda"), w["wqkv"][h:].contiguous()
+    if rotary:
+        tab = dev(k.kvpr_rope_table(s + 2, h // H), torch.float32)
+        k.kvpr_recompute_gemm_rope(xd, wkv, None, out, s * b, 2 * h, h, 2 * h, tab, s + 2, h, h // H, b, 0)
+    else:
+        k.kvpr_recompute_gemm(xd, wkv, w["bqkv"][h:].contiguous(), out, s * b, 2 * h, h, 2 * h)
+    if packed:
+        want = torch.empty((s * b, row), dtype=torch.uint8, device="cuda")
+        k.kvpr_quant_int4(out, want, s * b, 2 * h)
+        out = want
+    assert np.array_equal(got, out.cpu().numpy().view(np.uint8).reshape(-1))
