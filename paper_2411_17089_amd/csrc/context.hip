@@ -835,8 +835,7 @@ int ffn_block(kvpr_ctx* c, const kvpr_layer_weights* w, half* hid_out) {
     if (c->llama) {
         half* prod = c->ffn1 + (size_t)b * 2 * f;
         if (int rc = kvpr::launch_rmsnorm(c->resid, w->ln2_g, c->xf, b, h, c->compute)) return rc;
-        if (int rc = kvpr::launch_token_gemm_flags(c->xf, w->w1, nullptr, nullptr, c->ffn1, b, 2 * f, h, 0, 2 * (int64_t)f, 0, c->compute, c->tok_ws, c->tok_ws_bytes)) return rc;
-        if (int rc = kvpr::launch_silu_mul(c->ffn1, prod, b, f, c->compute)) return rc;
+        if (int rc = kvpr::launch_token_gemm_gated(c->xf, w->w1, c->ffn1, prod, b, f, h, c->compute, c->tok_ws, c->tok_ws_bytes)) return rc;
         return kvpr::launch_token_gemm_flags(prod, w->w2, nullptr, nullptr, hid_out, b, h, f, 0, h, 0, c->compute, c->tok_ws, c->tok_ws_bytes, c->resid);
     } else {
         if (int rc = kvpr::launch_layernorm(c->resid, w->ln2_g, w->ln2_b, c->xf, b, h, c->compute)) return rc;

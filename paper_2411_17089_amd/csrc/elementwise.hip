@@ -194,8 +194,7 @@ __global__ void silu_mul_kernel(const _Float16* __restrict__ gu, _Float16* __res
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const size_t row = i / f, col = i - row * f;
-    const float gt = (float)gu[row * 2 * f + col], up = (float)gu[row * 2 * f + f + col];
-    y[i] = (_Float16)(gt / (1.0f + __expf(-gt)) * up);
+    y[i] = (_Float16)silu_mul((float)gu[row * 2 * f + col], (float)gu[row * 2 * f + f + col]);
 }
 
 // rotary embedding of the decode token: qk [batch, 2h] float32 = [q | k] before rotation, position `pos` for

@@ -35,6 +35,7 @@
 // and writes the outputs.
 #include "kvpr_internal.h"
 #include <mutex>
+#include <type_traits>
 
 namespace kvpr {
 
@@ -173,7 +174,10 @@ constexpr int WIDE_KB = 128;                    // K columns per stage
 constexpr size_t TOKEN_WS_TICKET_BYTES = 4096;  // head of the workspace: one arrival counter per block of output features
 constexpr int WIDE_ROW_BYTES = WIDE_KB * 2;     // one LDS row of a stage
 
-template <int RB, int MT>
+// GATED (RB = 128): W is [gate; up] of N / 2 features each.  A workgroup owns 64 features of both, a wave's two row tiles
+// are the gate and the up rows of the same 16 features, and silu(gate) * up is taken in the epilogue, with the gate and
+// the up value rounded to float16 as a product stored in between would have them.
+template <int RB, int MT, bool GATED = false>
 __global__ __launch_bounds__(256) void token_gemm_wide(const _Float16* __restrict__ x, const _Float16* __restrict__ W,
                                                        const _Float16* __restrict__ bias, float* __restrict__ y32,
                                                        _Float16* __restrict__ y16, int M, int N, int K, int out_f32_cols,
@@ -185,7 +189,8 @@ __global__ __launch_bounds__(256) void token_gemm_wide(const _Float16* __restric
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n0 = blockIdx.x * RB;
+    const int n0 = blockIdx.x * (GATED ? RB / 2 : RB);
+    static_assert(!GATED || RB == 128, "a wave must own one gate and one up tile");
 
     // DMA sources.  Instruction q covers stage rows [4q, 4q+4); lane L lands at row 4q + L/16, physical 16-byte chunk L%16,
     // and therefore fetches logical chunk (L%16) ^ (row%16).
@@ -193,7 +198,9 @@ __global__ __launch_bounds__(256) void token_gemm_wide(const _Float16* __restric
 #pragma unroll
     for (int i = 0; i < WI; ++i) {
         const int row = (wave + 4 * i) * 4 + (lane >> 4);
-        srcw[i] = W + (int64_t)min(n0 + row, N - 1) * K + (((lane & 15) ^ (row & 15)) << 3);
+        // gated: tiles of 16 rows alternate between gate and up (N / 2 is a multiple of 64: no remainder)
+        const int at = GATED ? ((row >> 4) & 1) * (N / 2) + n0 + (row >> 5) * 16 + (row & 15) : min(n0 + row, N - 1);
+        srcw[i] = W + (int64_t)at * K + (((lane & 15) ^ (row & 15)) << 3);
     }
     const _Float16* srcx[MT];
 #pragma unroll
@@ -316,6 +323,17 @@ __global__ __launch_bounds__(256) void token_gemm_wide(const _Float16* __restric
         if (threadIdx.x == 0) ticket[blockIdx.x] = 0;    // ready for the next launch on this stream
     }
 
+    if constexpr (GATED) {
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int n = n0 + 16 * wave + 4 * c + i, m = 16 * t + r;
+                if (m < M) y16[(int64_t)m * ld16 + n] = (_Float16)silu_mul((float)(_Float16)acc[0][t][i], (float)(_Float16)acc[1][t][i]);
+            }
+        return;
+    }
+
     // element i of (tile p, m-tile t) in lane L is  n = n0 + 16*(wave*RT + p) + 4*(L/16) + i,  m = 16*t + L%16
 #pragma unroll
     for (int p = 0; p < RT; ++p)
@@ -336,10 +354,10 @@ __global__ __launch_bounds__(256) void token_gemm_wide(const _Float16* __restric
             }
 }
 
-template <int RB, int MT>
+template <int RB, int MT, bool GATED = false>
 int launch_wide(const void* x, const void* w, const void* bias, void* y32, void* y16, int M, int N, int K,
                 int out_f32_cols, int64_t ld16, int relu, int ks, void* ws, const void* res, hipStream_t st) {
-    auto kern = token_gemm_wide<RB, MT>;
+    auto kern = token_gemm_wide<RB, MT, GATED>;
     constexpr int lds_bytes = 2 * (RB + MT * 16) * WIDE_ROW_BYTES;
     static std::once_flag configured;
     static hipError_t configure_status = hipSuccess;
@@ -450,6 +468,25 @@ int launch_token_gemm_flags(const void* x, const void* w, const void* bias, void
     if (M <= 32) return launch_mt<2>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ws, ws_bytes, residual, st);
     if (M <= 48) return launch_mt<3>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ws, ws_bytes, residual, st);
     return launch_mt<4>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ws, ws_bytes, residual, st);
+}
+
+// y[M, f] = silu(x Wg^T) * (x Wu^T), w = [Wg; Wu] of [2f, K], for f a multiple of 64.  One launch where the wide kernel takes
+// the product of 2f features in blocks of 128 anyway (the same 144 workgroups): the separate product of both halves was a
+// launch of 4.8 us and a round trip of 3 M f halfs (token through 3 rotary layers of hidden 4096, batch 3: 570 -> 557 us).  Below that
+// the halves go through `mid` [M, 2f].
+int launch_token_gemm_gated(const void* x, const void* w, void* mid, void* y, int M, int f, int K, hipStream_t st, void* ws,
+                            size_t ws_bytes) {
+    if (f % 64 || K % WIDE_KB || f / 64 < 144) {
+        if (int rc = launch_token_gemm_flags(x, w, nullptr, nullptr, mid, M, 2 * f, K, 0, 2 * (int64_t)f, 0, st, ws, ws_bytes)) return rc;
+        return launch_silu_mul(mid, y, M, f, st);
+    }
+    auto go = [&](auto mt) {
+        return launch_wide<128, decltype(mt)::value, true>(x, w, nullptr, nullptr, y, M, 2 * f, K, 0, f, 0, 1, nullptr, nullptr, st);
+    };
+    if (M <= 16) return go(std::integral_constant<int, 1>{});
+    if (M <= 32) return go(std::integral_constant<int, 2>{});
+    if (M <= 48) return go(std::integral_constant<int, 3>{});
+    return go(std::integral_constant<int, 4>{});
 }
 
 // enough for 8 K slices of an output of `N` features and `M` rows

@@ -30,6 +30,8 @@ int launch_attention_mixed(const void* q, const void* kv16, const void* kvq, voi
 int launch_token_gemm_flags(const void* x, const void* w, const void* bias, void* y32, void* y16, int M, int N,
                             int K, int out_f32_cols, int64_t ld16, int flags /*bit0: ReLU*/, hipStream_t st,
                             void* ws = nullptr, size_t ws_bytes = 0, const void* residual = nullptr);
+int launch_token_gemm_gated(const void* x, const void* w, void* mid, void* y, int M, int f, int K, hipStream_t st, void* ws,
+                            size_t ws_bytes);
 size_t token_gemm_workspace_bytes(int M, int N);
 int launch_fill_u16(void* p, size_t n_halfs, uint16_t pattern, hipStream_t st);
 int launch_fill_random(void* p, size_t n_halfs, float scale, uint32_t seed, hipStream_t st);
@@ -47,5 +49,8 @@ int launch_dequant_int4(const void* src, void* dst, int64_t rows, int cols, hipS
 int launch_copy_bytes(const void* src, void* dst, size_t bytes, hipStream_t st, const void* src2 = nullptr, void* dst2 = nullptr,
                       size_t bytes2 = 0);
 int launch_keep_warm(const void* w, size_t n_w, double seconds, double wall_clock_hz, void* sink, hipStream_t st);
+
+// middle of the gated FFN, one element
+__device__ __forceinline__ float silu_mul(float gate, float up) { return gate / (1.0f + __expf(-gate)) * up; }
 
 }  // namespace kvpr
