@@ -84,6 +84,13 @@ struct WeightFence {
     hipEvent_t all_ready;   // the whole layer has landed
 };
 
+// Single-layer call: up to here a layer's rows come in by a kernel that reads the mapped pinned arrays, in one launch for
+// activations and cache, instead of by two DMA copies, which take about 10 us each before their first byte.  Waited for, at
+// hidden 768: 96 KiB 85 -> 64 us, 456 KiB 84 -> 67, 960 KiB 96 -> 81, 1440 KiB 106 -> 103, 3840 KiB 149 either way.  In the
+// layer pipeline the DMA engine is the better one at every size (4 layers of hidden 4096, batch 1, 0.6 MiB a layer: 628
+// against 653 us): its copies run early and leave the compute units alone.
+constexpr size_t kSmallCopy = size_t(1) << 20;
+
 int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weights* w, const half* x_new, half* out,
                   int buf, LayerEvents* ev, bool fence_copy_to_start, const WeightFence* wf = nullptr, const half* residual = nullptr) {
     const int b = c->d.batch, h = c->d.hidden;
@@ -148,10 +155,19 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::c0], c->copy));
     // chunk boundaries: equal parts of [0, l) rounded down to multiples of 8 positions (whole GEMM tile rows
     // at batch 32); a single chunk is the paper's schedule
-    int nchunk = (l > 0) ? std::min(c->chunks, std::max(1, l / 8)) : 0;
+    const size_t x_bytes = (size_t)l * xsb, kv_bytes = (size_t)(seq - l) * ksb;
+    const bool small = fence_copy_to_start && x_bytes + kv_bytes <= kSmallCopy;
+    int nchunk = (l > 0) ? (small ? 1 : std::min(c->chunks, std::max(1, l / 8))) : 0;
     int bound[kvpr_ctx::kMaxChunks + 1];
     for (int j = 0; j <= nchunk; ++j) bound[j] = (j == nchunk) ? l : (int)((int64_t)l * j / nchunk) / 8 * 8;
-    for (int j = 0; j < nchunk; ++j) {
+    const void* rest_from = c->hkv[layer] + (size_t)l * ksb;
+    void* rest_to = kv_stage + (size_t)l * ksb;
+    const bool at_once = small && !ev;                   // timed: a launch each, with the event in between
+    if (small)
+        if (int rc = at_once ? kvpr::launch_copy_bytes(rest_from, rest_to, kv_bytes, c->copy, c->hx[layer], x_stage, x_bytes)
+                             : kvpr::launch_copy_bytes(c->hx[layer], x_stage, x_bytes, c->copy))
+            return rc;
+    for (int j = 0; j < nchunk && !small; ++j) {
         if (bound[j + 1] > bound[j])
             KVPR_HIP(hipMemcpyAsync(x_stage + (size_t)bound[j] * xsb, c->hx[layer] + (size_t)bound[j] * xsb,
                                     (size_t)(bound[j + 1] - bound[j]) * xsb, hipMemcpyHostToDevice, c->copy));
@@ -159,10 +175,13 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
     }
     KVPR_HIP(hipEventRecord(c->ev_x[buf], c->copy));
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::c_x], c->copy));
-    if (l < seq)
-        KVPR_HIP(hipMemcpyAsync(kv_stage + (size_t)l * ksb, c->hkv[layer] + (size_t)l * ksb, (size_t)(seq - l) * ksb,
-                                hipMemcpyHostToDevice, c->copy));
-    KVPR_HIP(hipEventRecord(c->ev_kv[buf], c->copy));
+    if (small) {
+        if (!at_once)
+            if (int rc = kvpr::launch_copy_bytes(rest_from, rest_to, kv_bytes, c->copy)) return rc;
+    } else if (l < seq) {
+        KVPR_HIP(hipMemcpyAsync(rest_to, rest_from, kv_bytes, hipMemcpyHostToDevice, c->copy));
+    }
+    if (!at_once) KVPR_HIP(hipEventRecord(c->ev_kv[buf], c->copy));
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::c_kv], c->copy));
     if (int rc = debug_sync(c)) return rc;
 
@@ -277,7 +296,7 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
         if (int rc = kvpr::launch_attention_mixed(c->q32, dkv, packed, c->z16, c->attn_ws, seq + 1, l, b, h, c->d.n_heads, 0, c->compute))
             return rc;
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::e1], c->compute));
-    KVPR_HIP(hipStreamWaitEvent(c->compute, c->ev_kv[buf], 0));
+    if (!at_once) KVPR_HIP(hipStreamWaitEvent(c->compute, c->ev_kv[buf], 0));   // else it came with ev_x
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::a0], c->compute));
     if (int rc = two_phase ? kvpr::launch_attention_mixed(c->q32, dkv, packed, c->z16, c->attn_ws, seq + 1, l, b, h, c->d.n_heads, 1, c->compute)
                            : kvpr::launch_attention(c->q32, dkv, c->z16, c->attn_ws, seq + 1, b, h, c->d.n_heads, c->compute))
