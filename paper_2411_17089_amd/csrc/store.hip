@@ -72,7 +72,7 @@ extern "C" int kvpr_store_prefill_kv(kvpr_ctx* c, int layer, int seq, const kvpr
     KVPR_HIP(hipDeviceSynchronize());
     // Up to 8 runs of positions, at least 2 MiB of activations each, so that activations coming in, projection and rows going
     // out overlap: the link carries both directions at once, and the rows out are the longest of the three.  512 positions,
-    // batch 8, hidden 4096 in one run: 2000 us (590 in, 200, 1180 out); in 8: @P@.
+    // batch 8, hidden 4096 in one run: 2000 us (590 in, 200, 1180 out); in 8: 1540.
     // The activations are what the store returns (dequantised if it keeps them packed).
     const int runs = (int)std::clamp<size_t>((size_t)seq * xsb >> 21, 1, std::min(8, seq));
     const hipStream_t in = runs > 1 ? c->copy : c->compute, out = runs > 1 ? c->store : c->compute;
