@@ -70,42 +70,28 @@ extern "C" int kvpr_store_prefill_kv(kvpr_ctx* c, int layer, int seq, const kvpr
     const int h = c->d.hidden;
     const size_t xsb = c->x_store_bytes(), ksb = c->kv_store_bytes();
     KVPR_HIP(hipDeviceSynchronize());
-    // Up to 8 runs of positions, at least 2 MiB of activations each, so that activations coming in, projection and rows going
-    // out overlap: the link carries both directions at once, and the rows out are the longest of the three.  512 positions,
-    // batch 8, hidden 4096 in one run: 2000 us (590 in, 200, 1180 out); in 8: 1540.
-    // The activations are what the store returns (dequantised if it keeps them packed).
-    const int runs = (int)std::clamp<size_t>((size_t)seq * xsb >> 21, 1, std::min(8, seq));
-    const hipStream_t in = runs > 1 ? c->copy : c->compute, out = runs > 1 ? c->store : c->compute;
-    auto first = [&](int j) { return (size_t)((int64_t)seq * j / runs); };
-    char* x_stage = c->qx ? c->dxq[0] : (char*)c->dx[0];
-    char* kv_stage = c->qkv ? c->dkvq[0] : (char*)c->dkv[0];
-    for (int j = 0; j < runs; ++j) {
-        const size_t t = first(j);
-        KVPR_HIP(hipMemcpyAsync(x_stage + t * xsb, c->hx[layer] + t * xsb, (first(j + 1) - t) * xsb, hipMemcpyHostToDevice, in));
-        if (runs > 1) KVPR_HIP(hipEventRecord(c->ev_chunk[0][j], in));
-    }
+    // One copy in, one product, one copy out, all on the compute stream.  Cut into runs of positions on several streams the
+    // three overlap (512 positions, batch 8, hidden 4096: 2.00 -> 1.54 ms, batch 32, 1024, 7168: 30.5 -> 19.2), but the copy
+    // streams come out of that with another choice of copy engines: host-to-device copies of the decodes that follow ran at
+    // 30 instead of 57 GB/s for one to three calls in a quarter to a half of fresh contexts (headline layer 14.1 - 19.5 ms
+    // instead of 10.7), and the helper itself took up to twice as long (batch 2, 300 positions, hidden 4096: 0.33 -> 0.57).  With activations
+    // coming in on the store stream and rows going out on this one the decodes were spared, but the helper still ran at
+    // one of two speeds, by context (batch 4, 768 positions, hidden 4096 as 4 runs: 1.3 or 2.7 ms, as one: 1.5).
+    // the activations as the store returns them (dequantised if it keeps them packed)
+    KVPR_HIP(hipMemcpyAsync(c->qx ? (void*)c->dxq[0] : (void*)c->dx[0], c->hx[layer], (size_t)seq * xsb, hipMemcpyHostToDevice, c->compute));
+    if (c->qx)
+        if (int rc = kvpr::launch_dequant_int4(c->dxq[0], c->dx[0], (int64_t)seq * c->d.batch, h, c->compute)) return rc;
     const half* wkv = (const half*)w->wqkv + (size_t)h * h;
     const half* bkv = w->bqkv ? (const half*)w->bqkv + h : nullptr;
-    for (int j = 0; j < runs; ++j) {
-        const size_t t = first(j), n = first(j + 1) - t;
-        const int64_t rows = (int64_t)n * c->d.batch;
-        half *x = c->dx[0] + t * c->x_row_halfs(), *kv = c->dkv[0] + t * c->kv_row_halfs();
-        if (runs > 1) KVPR_HIP(hipStreamWaitEvent(c->compute, c->ev_chunk[0][j], 0));
-        if (c->qx)
-            if (int rc = kvpr::launch_dequant_int4(x_stage + t * xsb, x, rows, h, c->compute)) return rc;
-        if (int rc = c->llama ? kvpr::launch_gemm_rope(x, wkv, bkv, kv, rows, 2 * h, h, 2 * (int64_t)h, c->rope_tab, h, c->d.head_dim,
-                                                       c->d.batch, (int)t, c->compute)
-                              : kvpr::launch_gemm(x, wkv, bkv, kv, rows, 2 * h, h, 2 * (int64_t)h, c->compute))
-            return rc;
-        if (c->qkv)
-            if (int rc = kvpr::launch_quant_int4(kv, kv_stage + t * ksb, rows, 2 * h, c->compute)) return rc;
-        if (runs > 1) {
-            KVPR_HIP(hipEventRecord(c->ev_chunk[1][j], c->compute));
-            KVPR_HIP(hipStreamWaitEvent(out, c->ev_chunk[1][j], 0));
-        }
-        KVPR_HIP(hipMemcpyAsync(c->hkv[layer] + t * ksb, kv_stage + t * ksb, n * ksb, hipMemcpyDeviceToHost, out));
-    }
-    KVPR_HIP(hipStreamSynchronize(out));
+    if (int rc = c->llama ? kvpr::launch_gemm_rope(c->dx[0], wkv, bkv, c->dkv[0], (int64_t)seq * c->d.batch, 2 * h, h, 2 * (int64_t)h,
+                                                   c->rope_tab, h, c->d.head_dim, c->d.batch, 0, c->compute)
+                          : kvpr::launch_gemm(c->dx[0], wkv, bkv, c->dkv[0], (int64_t)seq * c->d.batch, 2 * h, h, 2 * (int64_t)h, c->compute))
+        return rc;
+    if (c->qkv)
+        if (int rc = kvpr::launch_quant_int4(c->dkv[0], c->dkvq[0], (int64_t)seq * c->d.batch, 2 * h, c->compute)) return rc;
+    KVPR_HIP(hipMemcpyAsync(c->hkv[layer], c->qkv ? (const void*)c->dkvq[0] : (const void*)c->dkv[0], (size_t)seq * ksb,
+                            hipMemcpyDeviceToHost, c->compute));
+    KVPR_HIP(hipStreamSynchronize(c->compute));
     c->kv_rows[layer] = std::max(c->kv_rows[layer], seq);
     return KVPR_OK;
 }
