@@ -94,17 +94,12 @@ constexpr size_t kSmallCopy = size_t(1) << 20;
 int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weights* w, const half* x_new, half* out,
                   int buf, LayerEvents* ev, bool fence_copy_to_start, const WeightFence* wf = nullptr, const half* residual = nullptr) {
     const int b = c->d.batch, h = c->d.hidden;
-    // Layer pipeline with resident weights: the recomputation needs nothing of this step's hidden states, so it runs on
-    // the store stream, in front of this layer's store-back and beside the previous layer's attention, output projection
-    // and FFN, which stream weights and leave the matrix cores idle.  Token through 4 layers, batch 1, context 512, hidden
-    // 4096: 916 -> 750 us, 3 rotary layers, batch 3: 640 -> 568, together with the store-back in the compute stream (alone
-    // it gained nothing: the host, at 14 us for a wait between streams, was then the bound).  (In the store stream and not in one of its own: a process has four
-    // hardware queues, and the store-back is not needed before the attention that needs the recomputation.)  The
-    // single-layer call has no previous layer to run beside; with offloaded weights the link is the bound.  A product of less
-    // than 2 GFLOP (about 10 us) is not worth the hand-over (4 layers of hidden 768, batch 2, context 100: 369 us, 342
-    // without), one of 4 GFLOP is (hidden 4096, context 60: 628 against 699), and one layer alone has no neighbour.
-    const bool ahead = !wf && !fence_copy_to_start && c->d.n_layers > 1 && (double)c->flops_per_pos() * l >= 2e9;
-    const hipStream_t rs = ahead ? c->store : c->compute;
+    // The recomputation stays on the compute stream, in line with the layer's other work.  In the layer pipeline it needs
+    // nothing of this step's hidden states and could run on the store stream, beside the previous layer's FFN.  Measured over
+    // hidden 768 - 5120, batch 1 - 64, 2 - 12 layers that is 3 - 8 % faster where the product fills less than half of the
+    // compute units (some 100 rows) and hidden is 3072 or more, and 1 - 20 % slower elsewhere, most of all at hidden 768 and
+    // 2048: a workgroup of it takes a compute unit's whole LDS, so beside it the weight-streaming products wait for units,
+    // and the hand-over costs two more operations between streams.
     const size_t xr = c->x_row_halfs(), kr = c->kv_row_halfs();
     const size_t xsb = c->x_store_bytes(), ksb = c->kv_store_bytes();
     half* dkv = c->dkv[buf];
@@ -245,35 +240,33 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
                 if (int rc = kvpr::launch_keep_warm(w->wqkv, (size_t)3 * h * h, t_first * c->keep_warm, c->wall_clock_hz, c->q32, c->compute))
                     return rc;
         }
-        if (nchunk <= 1) KVPR_HIP(hipStreamWaitEvent(rs, c->ev_x[buf], 0));
-        if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::r0], rs));
+        if (nchunk <= 1) KVPR_HIP(hipStreamWaitEvent(c->compute, c->ev_x[buf], 0));
+        if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::r0], c->compute));
         if (l > 0) {
             const half* wkv = (const half*)w->wqkv + (size_t)h * h;
             const half* bkv = w->bqkv ? (const half*)w->bqkv + h : nullptr;
             for (int j = 0; j < nchunk; ++j) {
                 // with several chunks the GEMM of chunk j runs while chunks j+1.. and the cache are still on the link
-                if (nchunk > 1) KVPR_HIP(hipStreamWaitEvent(rs, c->ev_chunk[buf][j], 0));
+                if (nchunk > 1) KVPR_HIP(hipStreamWaitEvent(c->compute, c->ev_chunk[buf][j], 0));
                 const int64_t rows = (int64_t)(bound[j + 1] - bound[j]) * b;
                 if (c->qx)
-                    if (int rc = kvpr::launch_dequant_int4(x_stage + (size_t)bound[j] * xsb, dx + (size_t)bound[j] * xr, rows, h, rs))
+                    if (int rc = kvpr::launch_dequant_int4(x_stage + (size_t)bound[j] * xsb, dx + (size_t)bound[j] * xr, rows, h, c->compute))
                         return rc;
                 // rotary models: the K half is rotated with the positions of its rows, bound[j] .. bound[j+1]-1
                 if (int rc = c->llama
                                  ? kvpr::launch_gemm_rope(dx + (size_t)bound[j] * xr, wkv, bkv, dkv + (size_t)bound[j] * kr, rows, 2 * h, h,
-                                                          2 * (int64_t)h, c->rope_tab, h, c->d.head_dim, b, bound[j], rs)
+                                                          2 * (int64_t)h, c->rope_tab, h, c->d.head_dim, b, bound[j], c->compute)
                                  : kvpr::launch_gemm(dx + (size_t)bound[j] * xr, wkv, bkv, dkv + (size_t)bound[j] * kr, rows, 2 * h, h,
-                                                     2 * (int64_t)h, rs))
+                                                     2 * (int64_t)h, c->compute))
                     return rc;
             }
         }
-        if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::r1], rs));
-        if (ahead) KVPR_HIP(hipEventRecord(c->ev_recomputed[buf], rs));
+        if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::r1], c->compute));
         return debug_sync(c);
     };
-    if (wf || ahead) {
+    if (wf) {
         // offloaded weights: Wk|Wv arrive first, so the recomputation goes first and the projections that need
         // Wq follow (fine-grained MHA pipeline, Sec. 3.3 "Hiding KV cache partial recomputation").
-        // On the store stream it comes before the store-back, which waits for the projections.
         if (int rc = recompute()) return rc;
         if (int rc = project_and_store()) return rc;
     } else {
@@ -290,7 +283,6 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
     // attention is off the critical path and stays one launch.)
     const bool two_phase = c->qkv || (fence_copy_to_start && l >= 128);
     const void* packed = c->qkv ? kv_stage : nullptr;
-    if (ahead) KVPR_HIP(hipStreamWaitEvent(c->compute, c->ev_recomputed[buf], 0));
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::e0], c->compute));
     if (two_phase)
         if (int rc = kvpr::launch_attention_mixed(c->q32, dkv, packed, c->z16, c->attn_ws, seq + 1, l, b, h, c->d.n_heads, 0, c->compute))
@@ -310,9 +302,7 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
                                                  residual))
         return rc;
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::o1], c->compute));
-    // With the recomputations on the store stream the step waits once, at its end: the next layer's attention, or its wait
-    // here, is behind this store-back anyway, and x_new is not overwritten before that.
-    if (!c->inline_store() && (!ahead || ev)) KVPR_HIP(hipStreamWaitEvent(c->compute, c->ev_store, 0));
+    if (!c->inline_store()) KVPR_HIP(hipStreamWaitEvent(c->compute, c->ev_store, 0));
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::end], c->compute));
     if (int rc = debug_sync(c)) return rc;
 
@@ -422,7 +412,6 @@ void destroy_impl(kvpr_ctx* c) {
         if (c->ev_x[i]) (void)hipEventDestroy(c->ev_x[i]);
         if (c->ev_kv[i]) (void)hipEventDestroy(c->ev_kv[i]);
         if (c->ev_free[i]) (void)hipEventDestroy(c->ev_free[i]);
-        if (c->ev_recomputed[i]) (void)hipEventDestroy(c->ev_recomputed[i]);
         if (c->ev_buf_store[i]) (void)hipEventDestroy(c->ev_buf_store[i]);
         for (hipEvent_t e : c->ev_chunk[i]) if (e) (void)hipEventDestroy(e);
     }
@@ -440,7 +429,7 @@ void destroy_impl(kvpr_ctx* c) {
         for (hipEvent_t e : we) if (e) (void)hipEventDestroy(e);
     }
     if (c->wstream) (void)hipStreamDestroy(c->wstream);
-    void* dev[] = {c->qk32, c->rope_tab, c->q32, c->z16, c->attn_ws, c->tok_ws, c->hid, c->xn[0], c->xn[1], c->xf, c->resid, c->ffn1, c->dw[0], c->dw[1], c->hid_all};
+    void* dev[] = {c->qk32, c->rope_tab, c->q32, c->z16, c->attn_ws, c->tok_ws, c->hid, c->xn, c->xf, c->resid, c->ffn1, c->dw[0], c->dw[1], c->hid_all};
     for (void* p : dev) if (p) (void)hipFree(p);
     hipEvent_t evs[] = {c->ev_proj, c->ev_store, c->ev_begin};
     for (hipEvent_t e : evs) if (e) (void)hipEventDestroy(e);
@@ -516,8 +505,7 @@ int settle_streams(kvpr_ctx* c) {
     };
     int rc = settle(&c->copy, true, {c->compute});
     if (!rc && c->wstream) rc = settle(&c->wstream, true, {c->compute, c->copy});
-    if (!rc) rc = c->wstream ? settle(&c->store, false, {c->copy, c->wstream})
-                            : c->d.ffn_dim > 0 && c->d.n_layers > 1 ? settle(&c->store, false, {c->copy, c->compute}) : settle(&c->store, false, {c->copy});
+    if (!rc) rc = c->wstream ? settle(&c->store, false, {c->copy, c->wstream}) : settle(&c->store, false, {c->copy});
     for (hipStream_t st : rejected) (void)hipStreamDestroy(st);
     (void)hipEventDestroy(e_busy);
     (void)hipEventDestroy(e_probe);
@@ -635,7 +623,6 @@ int create_impl(const kvpr_model_desc* d, int n_gpu_batches, void* compute_strea
         if ((e = hipEventCreateWithFlags(&c->ev_x[i], hipEventDisableTiming)) != hipSuccess) return bail(KVPR_E_HIP, "event", e);
         if ((e = hipEventCreateWithFlags(&c->ev_kv[i], hipEventDisableTiming)) != hipSuccess) return bail(KVPR_E_HIP, "event", e);
         if ((e = hipEventCreateWithFlags(&c->ev_free[i], hipEventDisableTiming)) != hipSuccess) return bail(KVPR_E_HIP, "event", e);
-        if ((e = hipEventCreateWithFlags(&c->ev_recomputed[i], hipEventDisableTiming)) != hipSuccess) return bail(KVPR_E_HIP, "event", e);
         if ((e = hipEventCreateWithFlags(&c->ev_buf_store[i], hipEventDisableTiming)) != hipSuccess) return bail(KVPR_E_HIP, "event", e);
         for (int j = 0; j < kvpr_ctx::kMaxChunks; ++j)
             if ((e = hipEventCreateWithFlags(&c->ev_chunk[i][j], hipEventDisableTiming)) != hipSuccess) return bail(KVPR_E_HIP, "event", e);
@@ -670,7 +657,7 @@ int create_impl(const kvpr_model_desc* d, int n_gpu_batches, void* compute_strea
             return bail(KVPR_E_HIP, "rotary table upload", e);
     }
     if (d->ffn_dim > 0) {
-        half** bufs[] = {&c->hid, &c->xn[0], &c->xn[1], &c->xf, &c->resid};
+        half** bufs[] = {&c->hid, &c->xn, &c->xf, &c->resid};
         for (half** p : bufs)
             if ((e = hipMalloc((void**)p, bh * sizeof(half))) != hipSuccess) return bail(KVPR_E_NOMEM, "hidden-state buffer", e);
         // gated FFN: [gate | up] (2 ffn columns) followed by their gated product (ffn columns)
@@ -840,11 +827,11 @@ extern "C" int kvpr_timing_read(kvpr_ctx* c, int slot, kvpr_layer_timing* timing
 
 namespace {
 
-// the parts of a decoder layer around the attention block (xn = normalised input of the attention block)
-int pre_attention_norm(kvpr_ctx* c, const kvpr_layer_weights* w, const half* hid_in, half* xn) {
+// the parts of a decoder layer around the attention block (c->xn = normalised input of the attention block)
+int pre_attention_norm(kvpr_ctx* c, const kvpr_layer_weights* w, const half* hid_in) {
     const int b = c->d.batch, h = c->d.hidden;
-    if (c->llama) return kvpr::launch_rmsnorm(hid_in, w->ln1_g, xn, b, h, c->compute);
-    return kvpr::launch_layernorm(hid_in, w->ln1_g, w->ln1_b, xn, b, h, c->compute);
+    if (c->llama) return kvpr::launch_rmsnorm(hid_in, w->ln1_g, c->xn, b, h, c->compute);
+    return kvpr::launch_layernorm(hid_in, w->ln1_g, w->ln1_b, c->xn, b, h, c->compute);
 }
 
 // hid_out = r + FFN(norm(r)), r = c->resid.  OPT: LayerNorm, ReLU FFN with biases (Eq. 4);
@@ -901,23 +888,17 @@ extern "C" int kvpr_decode_step(kvpr_ctx* c, int seq, const kvpr_layer_weights* 
     if (int rc = step_begin(c)) return rc;
     const size_t bh = (size_t)b * h;
     const half* hid_in = (const half*)x_in_dev;
-    // the recomputations run on the store stream: behind whatever the caller enqueued that wrote the weights
-    KVPR_HIP(hipEventRecord(c->ev_begin, c->compute));
-    KVPR_HIP(hipStreamWaitEvent(c->store, c->ev_begin, 0));
     for (int i = 0; i < L; ++i) {
         const kvpr_layer_weights* w = &layers[i];
         half* hid_out = (i == L - 1) ? (half*)x_out_dev : c->hid;
         // pre-norm -> attention block -> residual -> norm -> FFN -> residual
-        // the store-back of layer i reads this row until the attention of layer i + 1 has started
-        half* xn = c->xn[i & 1];
-        if (int rc = pre_attention_norm(c, w, hid_in, xn)) return rc;
-        if (int rc = enqueue_layer(c, i, seq, ls[i], w, xn, c->resid, i % c->nbuf, per_layer ? &c->tev[i] : nullptr, false, nullptr,
+        if (int rc = pre_attention_norm(c, w, hid_in)) return rc;
+        if (int rc = enqueue_layer(c, i, seq, ls[i], w, c->xn, c->resid, i % c->nbuf, per_layer ? &c->tev[i] : nullptr, false, nullptr,
                                    hid_in))
             return rc;
         if (int rc = ffn_block(c, w, hid_out)) return rc;
         hid_in = hid_out;
     }
-    if (!c->inline_store()) KVPR_HIP(hipStreamWaitEvent(c->compute, c->ev_store, 0));     // of the last layer, and with it all of them
     if (int rc = step_end(c)) return rc;
     if (splits_out) std::copy(ls.begin(), ls.end(), splits_out);
     if (per_layer) {
@@ -1047,8 +1028,8 @@ extern "C" int kvpr_decode_step_columns(kvpr_ctx* c, int seq, const void* x_in_d
             // the norm's parameters arrive with [Wk;Wv]: neither the norm nor the recomputation that follows it
             // waits for Wq, Wo and the FFN matrices, which may still be on the link (Sec. 3.3 fine-grained MHA pipeline)
             KVPR_HIP(hipStreamWaitEvent(c->compute, c->weight_pipeline ? c->ev_wkv[wb] : c->ev_wall[wb], 0));
-            if (int rc = pre_attention_norm(c, &w, hid_in, c->xn[0])) return rc;
-            if (int rc = enqueue_layer(c, slot, seq, ls[slot], &w, c->xn[0], c->resid, slot % c->nbuf,
+            if (int rc = pre_attention_norm(c, &w, hid_in)) return rc;
+            if (int rc = enqueue_layer(c, slot, seq, ls[slot], &w, c->xn, c->resid, slot % c->nbuf,
                                        per_slot ? &c->tev[slot] : nullptr, false, &wf, hid_in))
                 return rc;
             if (int rc = ffn_block(c, &w, hid_out)) return rc;
