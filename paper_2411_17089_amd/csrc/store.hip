@@ -13,10 +13,13 @@ extern "C" int kvpr_store_write(kvpr_ctx* c, int layer, int t0, int t1, const vo
     if (!c) return fail(KVPR_E_INVAL, "ctx is null");
     if (layer < 0 || layer >= c->slots()) return fail(KVPR_E_RANGE, "layer %d outside [0, %d)", layer, c->slots());
     if (t0 < 0 || t1 < t0 || t1 > c->d.max_seq) return fail(KVPR_E_RANGE, "rows [%d, %d) outside [0, %d]", t0, t1, c->d.max_seq);
-    // decodes may still be touching the store
-    KVPR_HIP(hipStreamSynchronize(c->compute));
+    // decodes may still be touching the store: reading it on the copy stream, writing new rows on the store stream or, while
+    // those are few, on the compute stream in front of ev_free (inline_store).  The caller's other work on the compute
+    // stream is not waited for.
     KVPR_HIP(hipStreamSynchronize(c->copy));
     KVPR_HIP(hipStreamSynchronize(c->store));
+    for (int i = 0; i < c->nbuf; ++i)
+        if (c->free_recorded[i]) KVPR_HIP(hipEventSynchronize(c->ev_free[i]));
     const size_t xr = c->x_row_halfs(), kr = c->kv_row_halfs();
     const size_t xsb = c->x_store_bytes(), ksb = c->kv_store_bytes();
     const size_t n = (size_t)(t1 - t0);

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import kvpr_inputs
-from kvpr_testlib import dev
+from kvpr_testlib import dev, upload_layer
 from test_gpu_stack import Stack
 
 pytestmark = pytest.mark.gpu
@@ -150,3 +150,38 @@ def test_adaptation_in_a_stack_sees_the_product_alone(k):
         assert stack >= 0.85 * layer                            # the same launches; in a stack the clocks are no lower
     finally:
         st.close()
+
+
+@pytest.mark.parametrize("b,h,H", [(4, 512, 4), (64, 1024, 8)])     # new rows stored on the compute stream, on the store stream
+def test_store_write_waits_for_decodes_only(k, b, h, H):
+    """A row written right behind the decode that stores it holds what was written last, and the call does not wait for what
+    the caller enqueued on the compute stream behind the decode."""
+    s = 40
+    L = kvpr_inputs.make_layer(760, b, s, h, H)
+    d = upload_layer(L)
+    w = k.make_weights(**{f: d[f] for f in ("wqkv", "bqkv", "wo", "bo")})
+    ctx = k.kvpr_create(2, h, H, h // H, 0, b, s + 3)
+    try:
+        for i in range(2):
+            k.kvpr_store_write(ctx, i, 0, s, np.ascontiguousarray(L["X"]), None)
+            k.kvpr_store_prefill_kv(ctx, i, s, w)
+        row_x, row_kv = np.full((1, b, h), 3.0, np.float16), np.full((1, b, 2 * h), 5.0, np.float16)
+        out = torch.empty((b, h), dtype=torch.float16, device="cuda")
+        big, done = torch.randn(8192, 8192, device="cuda"), torch.cuda.Event()
+        big @ big
+        torch.cuda.synchronize()
+        for _ in range(3):
+            for i in range(2):
+                k.kvpr_layer_decode(ctx, i, s, s // 2, w, d["x_new"], out)
+            for _ in range(20):                                     # some 200 ms
+                big @ big
+            done.record()
+            k.kvpr_store_write(ctx, 1, s, s + 1, row_x, row_kv)
+            early = not done.query()
+            torch.cuda.synchronize()
+            x, kv = (np.frombuffer((ctypes.c_ubyte * (b * c * 2)).from_address(a + s * b * c * 2), np.float16)
+                     for a, c in zip(k.kvpr_store_ptrs(ctx, 1), (h, 2 * h)))
+            assert (x == 3.0).all() and (kv == 5.0).all()
+            assert early, "the call waited for unrelated work"
+    finally:
+        k.kvpr_destroy(ctx)
