@@ -541,11 +541,16 @@ SplitPlan plan_splits(int batch, int hidden, int S, int cols_per_group = COLS_PE
 // Workgroups of 8 waves over all positions instead of 4 waves, splits and a combine launch: when half the compute units or
 // more get a workgroup that way but none gets two (batch 20, 700 positions, hidden 5120: 46.9 -> 42.6 us; batch 10, 1000
 // positions, hidden 7168: 52.6 -> 47.7; with 320 workgroups it is the slower one, 121 against 105), and when there are
-// only two rounds to share (97 positions, batch 2, hidden 768: 9.8 -> 8.8).
+// only two rounds to share (97 positions, batch 2, hidden 768: 9.8 -> 8.8).  On exactly half of them two splits fill the chip
+// without a rest, and the combine launch is soon worth it (batch 16, hidden 4096: 257 positions 13.2 against 15.6 us with
+// splits, 500: 23.5 against 24.0, 4097: 180 against 156; batch 64, hidden 768, 500 positions: 23.3 against 22.5); on all of
+// them there is nothing to split, and 4 waves are the better workgroup (batch 32, hidden 4096, 500 positions: 42.4 against
+// 40.5).
 bool one_wide_workgroup(int batch, int hidden, int S) {
     if (g_attn_force_splits > 0 || g_attn_cfg != 1) return false;
-    const int64_t base = (int64_t)((hidden + COLS_PER_GROUP - 1) / COLS_PER_GROUP) * batch;
-    return S <= 128 ? base <= g_attn_target_blocks : base * 2 >= g_attn_target_blocks && base <= g_attn_target_blocks;
+    const int64_t base = (int64_t)((hidden + COLS_PER_GROUP - 1) / COLS_PER_GROUP) * batch, all = g_attn_target_blocks;
+    if (S <= 128) return base <= all;
+    return base < all && (base * 2 > all || (base * 2 == all && S <= 384));
 }
 
 }  // namespace
@@ -741,6 +746,15 @@ extern "C" int kvpr_decode_attention_static(const void* q, const void* kv, void*
     if (int rc = scratch_for_current_device(&ws)) return rc;
     return kvpr::launch_attention_plan(bytes(whole) <= room ? whole : plain, q, kv, z, ws, S, batch, hidden, n_heads,
                                        (hipStream_t)stream);
+}
+
+// what kvpr_decode_attention launches for a shape: positions per workgroup, splits, waves per workgroup
+extern "C" int kvpr_debug_attention_plan(int batch, int hidden, int S, int32_t* chunk, int32_t* splits, int32_t* waves) {
+    const kvpr::SplitPlan p = kvpr::attention_plan(batch, hidden, S);
+    *chunk = p.chunk;
+    *splits = p.splits;
+    *waves = p.splits == 1 && kvpr::one_wide_workgroup(batch, hidden, S) ? 8 : 4;
+    return KVPR_OK;
 }
 
 extern "C" int kvpr_debug_set_attention_kernel(int v) {

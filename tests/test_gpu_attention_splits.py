@@ -31,3 +31,9 @@ def test_against_oracle(k, S, b, h, H):
     z2 = torch.full_like(z, float("nan"))
     k.kvpr_decode_attention_static(dev(q, torch.float32), dev(kv), z2, S, b, h, H)
     assert torch.equal(z, z2)
+
+
+@pytest.mark.parametrize("S,b", [(384, 128), (385, 128), (385, 129), (129, 255), (129, 256)])
+def test_against_oracle_where_the_workgroup_changes(k, S, b):
+    """Half the compute units busy without splits and one more, nearly all and all."""
+    test_against_oracle(k, S, b, 64, 1)
