@@ -88,8 +88,10 @@ struct WeightFence {
 // activations and cache, instead of by two DMA copies, which take about 10 us each before their first byte.  Waited for, at
 // hidden 768: 96 KiB 85 -> 64 us, 456 KiB 84 -> 67, 960 KiB 96 -> 81, 1440 KiB 106 -> 103, 3840 KiB 149 either way.  In the
 // layer pipeline the DMA engine is the better one at every size (4 layers of hidden 4096, batch 1, 0.6 MiB a layer: 628
-// against 653 us): its copies run early and leave the compute units alone.
-constexpr size_t kSmallCopy = size_t(1) << 20;
+// against 653 us): its copies run early and leave the compute units alone.  Where a float16 cache is all that comes in there is
+// no recomputation that the first copy could release early, and the kernel stays the better one for longer (calls in a row,
+// batch 2, 256 positions, hidden 768, 1.5 MiB: 88 -> 77 us; batch 8, 32 positions, hidden 2048, 2 MiB: 97 -> 84).
+constexpr size_t kSmallCopy = size_t(1) << 20, kSmallCacheCopy = 2 * kSmallCopy;
 
 int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weights* w, const half* x_new, half* out,
                   int buf, LayerEvents* ev, bool fence_copy_to_start, const WeightFence* wf = nullptr, const half* residual = nullptr) {
@@ -151,7 +153,7 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
     // chunk boundaries: equal parts of [0, l) rounded down to multiples of 8 positions (whole GEMM tile rows
     // at batch 32); a single chunk is the paper's schedule
     const size_t x_bytes = (size_t)l * xsb, kv_bytes = (size_t)(seq - l) * ksb;
-    const bool small = fence_copy_to_start && x_bytes + kv_bytes <= kSmallCopy;
+    const bool small = fence_copy_to_start && x_bytes + kv_bytes <= (l == 0 && !c->qkv ? kSmallCacheCopy : kSmallCopy);
     int nchunk = (l > 0) ? (small ? 1 : std::min(c->chunks, std::max(1, l / 8))) : 0;
     int bound[kvpr_ctx::kMaxChunks + 1];
     for (int j = 0; j <= nchunk; ++j) bound[j] = (j == nchunk) ? l : (int)((int64_t)l * j / nchunk) / 8 * 8;
