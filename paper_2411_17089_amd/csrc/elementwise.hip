@@ -1,5 +1,6 @@
 // Small memory-bound helpers around the attention block: norms, greedy sampling, pattern fill.
 #include "kvpr_internal.h"
+#include "silu.h"
 #include <algorithm>
 #include <cstdint>
 #include <math.h>

@@ -404,7 +404,7 @@ constexpr TileCost kTiles[] = {{256, 256, 1537, 1114}, {192, 256, 1199, 926}, {2
                                {192, 128, 661, 530},   {128, 128, 529, 444},  {64, 128, 358, 383}};
 
 // One workgroup per compute unit at a time: whole rounds cost `full`, the last one in proportion to what it fills but not
-// less than `least`; six stages a round stand for the first loads and the epilogue.  The costs are a fit to 378 timings
+// less than `least`.  (K is a common factor: all tiles take the same number of stages.)  The costs are a fit to 378 timings
 // (hidden 4096 / 5120 / 7168, N = 2 hidden, M = 1 .. 4096, all six tiles): they predict them to 9 % (rms), and the tile they
 // pick is within 0.2 % of the fastest on average and 8 % at worst.
 int pick_tile(int64_t M, int N) {

@@ -34,6 +34,7 @@
 // of K stages, the float32 partial tiles meet in a workspace and the workgroup that arrives last adds them in slice order
 // and writes the outputs.
 #include "kvpr_internal.h"
+#include "silu.h"
 #include <mutex>
 #include <type_traits>
 
@@ -456,9 +457,9 @@ int launch_mt(const void* x, const void* w, const void* bias, void* y32, void* y
 
 }  // namespace
 
-// flags bit 0: ReLU.  residual (optional): float16, laid out as y16, added to the float16 outputs.  ws (optional, device): workspace that lets a narrow output split K over several workgroups; its
-// first 4096 bytes must be zero before the first launch that uses it and are zero again when a launch ends; launches
-// that share a workspace must not overlap.
+// flags bit 0: ReLU.  residual (optional): float16, laid out as y16, added to the float16 outputs.  ws (optional, device):
+// workspace that lets a narrow output split K over several workgroups; its first 4096 bytes must be zero before the first
+// launch that uses it and are zero again when a launch ends; launches that share a workspace must not overlap.
 int launch_token_gemm_flags(const void* x, const void* w, const void* bias, void* y32, void* y16, int M, int N, int K,
                             int out_f32_cols, int64_t ld16, int flags, hipStream_t st, void* ws, size_t ws_bytes,
                             const void* residual) {
@@ -472,11 +473,11 @@ int launch_token_gemm_flags(const void* x, const void* w, const void* bias, void
 
 // y[M, f] = silu(x Wg^T) * (x Wu^T), w = [Wg; Wu] of [2f, K], for f a multiple of 64.  One launch where the wide kernel takes
 // the product of 2f features in blocks of 128 anyway (the same 144 workgroups): the separate product of both halves was a
-// launch of 4.8 us and a round trip of 3 M f halfs (token through 3 rotary layers of hidden 4096, batch 3: 570 -> 557 us).  Below that
-// the halves go through `mid` [M, 2f].
+// launch of 4.8 us and a round trip of 3 M f halfs (token through 3 rotary layers of hidden 4096, batch 3: 570 -> 557 us).
+// Below that, and while a kernel choice is forced, the halves go through `mid` [M, 2f].
 int launch_token_gemm_gated(const void* x, const void* w, void* mid, void* y, int M, int f, int K, hipStream_t st, void* ws,
                             size_t ws_bytes) {
-    if (f % 64 || K % WIDE_KB || f / 64 < 144) {
+    if (f % 64 || K % WIDE_KB || f / 64 < 144 || g_token_tpw > 0 || g_token_wide >= 0) {
         if (int rc = launch_token_gemm_flags(x, w, nullptr, nullptr, mid, M, 2 * f, K, 0, 2 * (int64_t)f, 0, st, ws, ws_bytes)) return rc;
         return launch_silu_mul(mid, y, M, f, st);
     }

@@ -50,7 +50,4 @@ int launch_copy_bytes(const void* src, void* dst, size_t bytes, hipStream_t st, 
                       size_t bytes2 = 0);
 int launch_keep_warm(const void* w, size_t n_w, double seconds, double wall_clock_hz, void* sink, hipStream_t st);
 
-// middle of the gated FFN, one element
-__device__ __forceinline__ float silu_mul(float gate, float up) { return gate / (1.0f + __expf(-gate)) * up; }
-
 }  // namespace kvpr
