@@ -727,7 +727,7 @@ def mfma_ceiling(seconds=1.5):
         n += 10
     dt = time.perf_counter() - t0
     return {"TFLOPs": flops * n / dt / 1e12, "frac_of_mfma_peak": flops * n / dt / 1e12 / PEAK_MFMA_F16_TFLOPS, "launches": n, "seconds": dt,
-            "what": "register-only loop of v_mfma_f32_32x32x16_f16 on N(0,1) x N(0,0.02) operands, 256 workgroups of 8 waves, "
+            "what": "register-only loop of v_mfma_f32_16x16x32_f16 on N(0,1) x N(0,0.02) operands, 256 workgroups of 8 waves, "
                     "back-to-back launches of about 4 ms: the rate the board's power management grants the MFMA unit "
                     "with no data movement at all"}
 

@@ -167,7 +167,9 @@ typedef struct {
 const char* kvpr_last_error(void);
 
 /* Create a context for `desc`.  compute_stream is a hipStream_t (may be null = the
- * null stream) owned by the caller; all kernels are launched on it.  Allocates the
+ * null stream) owned by the caller.  The kernels that compute run on it; kernels that only move rows between the pinned
+ * store and the device (small inputs, the new rows of a large batch) run on the context's own streams, and every call's
+ * results and store-backs are complete when what it enqueued on compute_stream is.  Allocates the
  * pinned host store: n_layers * max_seq * batch * 3*hidden * 2 bytes (9/32 of that for
  * an array kept 4-bit compressed), and device staging buffers for min(n_layers, 2)
  * layers (float16 X and KV, plus packed copies of the arrays kept compressed).
