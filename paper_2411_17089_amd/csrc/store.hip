@@ -74,12 +74,12 @@ extern "C" int kvpr_store_prefill_kv(kvpr_ctx* c, int layer, int seq, const kvpr
     const size_t xsb = c->x_store_bytes(), ksb = c->kv_store_bytes();
     KVPR_HIP(hipDeviceSynchronize());
     // One copy in, one product, one copy out, all on the compute stream.  Cut into runs of positions on several streams the
-    // three overlap (512 positions, batch 8, hidden 4096: 2.00 -> 1.54 ms, batch 32, 1024, 7168: 30.5 -> 19.2), but the copy
-    // streams come out of that with another choice of copy engines: host-to-device copies of the decodes that follow ran at
-    // 30 instead of 57 GB/s for one to three calls in a quarter to a half of fresh contexts (headline layer 14.1 - 19.5 ms
-    // instead of 10.7), and the helper itself took up to twice as long (batch 2, 300 positions, hidden 4096: 0.33 -> 0.57).  With activations
-    // coming in on the store stream and rows going out on this one the decodes were spared, but the helper still ran at
-    // one of two speeds, by context (batch 4, 768 positions, hidden 4096 as 4 runs: 1.3 or 2.7 ms, as one: 1.5).
+    // three overlap (512 positions, batch 8, hidden 4096: 2.00 -> 1.54 ms; 1024, batch 32, hidden 7168: 30.5 -> 19.2).  But in
+    // a quarter to a half of fresh contexts the host-to-device copies of the one to three decodes that followed then ran at
+    // 30 instead of 57 GB/s, with no kernel beside them (layer of that size 14.1 - 19.5 ms instead of 10.7), and the helper
+    // itself took up to twice as long (300 positions, batch 2, hidden 4096: 0.33 -> 0.57).  With activations coming in on the
+    // store stream and rows going out on this one the decodes were spared, but the helper still ran at one of two speeds,
+    // by context (768 positions, batch 4, hidden 4096 as 4 runs: 1.3 or 2.7 ms, as one: 1.5).
     // the activations as the store returns them (dequantised if it keeps them packed)
     KVPR_HIP(hipMemcpyAsync(c->qx ? (void*)c->dxq[0] : (void*)c->dx[0], c->hx[layer], (size_t)seq * xsb, hipMemcpyHostToDevice, c->compute));
     if (c->qx)
