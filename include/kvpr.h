@@ -259,7 +259,8 @@ int kvpr_plan_split_linear(const kvpr_profile_t* prof, int cost_model, int chunk
  * kvpr_set_adaptive: alpha in (0, 1] makes every layer that is decoded without a timing request record HIP
  * events around its copies and its recompute GEMM (no waiting); the next planned split (split = -1) first
  * folds the samples of all finished layers into the context's profile with kvpr_adapt_update.  alpha = 0
- * (the default) turns it off.  With a chunked activation copy only the link rate is adapted.
+ * (the default) turns it off.  With a chunked activation copy only the link rate is adapted; where kvpr_decode_step runs
+ * recomputations beside the previous layer, the first layer's stays in line and gives the GEMM rate.
  * kvpr_get_profile: the context's current profile, after folding in finished samples. */
 int kvpr_adapt_update(kvpr_profile_t* prof, double alpha, int64_t link_bytes, double link_seconds,
                       int64_t gemm_flops, double gemm_seconds);
@@ -302,6 +303,8 @@ int kvpr_timing_read(kvpr_ctx* ctx, int slot, kvpr_layer_timing* timing);
  * layer's transfers prefetched into the other device buffer while this layer computes
  * (Sec. 4 "Implementation": double buffering across decoder layers).
  * x_in_dev / x_out_dev [batch, hidden] hidden states; splits_in [n_layers] or null (= plan).
+ * Where a layer streams enough weights and its recomputation leaves compute units free, the recomputation runs beside the
+ * previous layer.  With per_layer non-null every layer's work stays in line instead, so that its times are its own.
  * Asynchronous, with bounded run-ahead: at most two steps of a context are in flight; a further call (this one or
  * kvpr_decode_step_columns) first blocks the calling thread until the step before the previous one has finished on
  * the GPU.  Deeper queues gain nothing and made steps slower (the runtime stalls the caller by itself, later and

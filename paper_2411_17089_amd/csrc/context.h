@@ -16,6 +16,7 @@ struct LayerEvents {
     hipEvent_t at[count]{};
     int seq = -1, split = -1;            // what the slot last recorded
     bool has_w_all = false;              // w_all was recorded for the step being timed
+    bool ahead = false;                  // the recomputation ran beside the previous layer
 };
 
 }  // namespace kvpr
@@ -46,10 +47,10 @@ struct kvpr_ctx {
     void* tok_ws = nullptr;              // token GEMM K-slice workspace (tickets, then partial tiles)
     size_t tok_ws_bytes = 0;
     // hidden-state scratch of the full decoder layer; resid: the residual stream between attention block and FFN
-    // xn: the attention block's normalised input; xf: the FFN's
-    half *hid = nullptr, *xn = nullptr, *xf = nullptr, *resid = nullptr, *ffn1 = nullptr;
+    // xn: the attention block's normalised input, by layer parity; xf: the FFN's
+    half *hid = nullptr, *xn[2] = {nullptr, nullptr}, *xf = nullptr, *resid = nullptr, *ffn1 = nullptr;
     // fences (timing disabled)
-    hipEvent_t ev_x[2]{}, ev_kv[2]{}, ev_free[2]{}, ev_proj = nullptr, ev_store = nullptr, ev_begin = nullptr;
+    hipEvent_t ev_x[2]{}, ev_kv[2]{}, ev_free[2]{}, ev_recomputed[2]{}, ev_proj = nullptr, ev_store = nullptr, ev_begin = nullptr;
     static constexpr int kMaxChunks = 32;
     hipEvent_t ev_chunk[2][kMaxChunks]{};   // per device buffer: "activation chunk j has landed"
     int chunks = 1;                          // 1 = the paper's schedule: all of X[0:l], then one GEMM
@@ -92,6 +93,7 @@ struct kvpr_ctx {
     // MFMA loop before it waits for the activations (0 = off)
     double keep_warm = 0.0;
     double wall_clock_hz = 0.0;
+    int64_t layers_ahead = 0;            // recomputations that ran beside the previous layer (read by tests)
     int cost_model = KVPR_COST_EQ10, granularity = 1;
     int debug = 0;
 

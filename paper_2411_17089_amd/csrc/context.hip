@@ -93,15 +93,28 @@ struct WeightFence {
 // batch 2, 256 positions, hidden 768, 1.5 MiB: 88 -> 77 us; batch 8, 32 positions, hidden 2048, 2 MiB: 97 -> 84).
 constexpr size_t kSmallCopy = size_t(1) << 20, kSmallCacheCopy = 2 * kSmallCopy;
 
-int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weights* w, const half* x_new, half* out,
-                  int buf, LayerEvents* ev, bool fence_copy_to_start, const WeightFence* wf = nullptr, const half* residual = nullptr) {
+// Layer pipeline with resident weights: the recomputation needs nothing of this step's hidden states, so it may run on the
+// store stream, in front of this layer's store-back and beside the previous layer's attention, output projection and FFN,
+// which stream weights and leave the matrix cores idle.  (In the store stream and not in one of its own: a process has four
+// hardware queues, and the store-back is not needed before the attention that needs the recomputation.)  It pays where
+//   - the previous layer streams long enough: hidden 3072, 170 MB of FFN and output projection, gains, hidden 2048, 75 MB,
+//     loses 1 - 19 % (two more operations between streams);
+//   - the product leaves it compute units to stream with, a quarter of them: a GEMM workgroup takes the LDS of a whole unit.
+//     Over hidden 3072 - 5120, batch 1 - 32, contexts 30 - 512, 4 layers, steps in a row: 0.90 - 0.98 of the time in line with
+//     up to 192 workgroups on 256 units, 0.97 - 1.08 with 240 and more; waited for one by one 0.94 - 1.04 and 1.00 - 1.11;
+//   - it takes longer than the hand-over: 2 GFLOP, about 10 us;
+//   - there is a previous layer.  (With offloaded weights the link is the bound.)
+bool runs_ahead(const kvpr_ctx* c, int l) {
+    const int64_t h = c->d.hidden, streamed = 2 * h * (h + (c->llama ? 3 : 2) * (int64_t)c->d.ffn_dim);
+    if (c->d.n_layers < 2 || streamed < 128000000 || c->flops_per_pos() * l < 2000000000) return false;
+    const int64_t rows = (int64_t)l * c->d.batch / std::min(c->chunks, std::max(1, l / 8));
+    return kvpr::gemm_workgroups(rows, 2 * c->d.hidden) * 4 <= 3 * kvpr::compute_units();
+}
+
+int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weights* w, const half* x_new, half* out, int buf,
+                  LayerEvents* ev, bool fence_copy_to_start, const WeightFence* wf = nullptr, const half* residual = nullptr,
+                  bool may_run_ahead = false) {
     const int b = c->d.batch, h = c->d.hidden;
-    // The recomputation stays on the compute stream, in line with the layer's other work.  In the layer pipeline it needs
-    // nothing of this step's hidden states and could run on the store stream, beside the previous layer's FFN.  Measured over
-    // hidden 768 - 5120, batch 1 - 64, 2 - 12 layers that is 3 - 8 % faster where the product fills less than half of the
-    // compute units (some 100 rows) and hidden is 3072 or more, and 1 - 20 % slower elsewhere, most of all at hidden 768 and
-    // 2048: a workgroup of it takes a compute unit's whole LDS, so beside it the weight-streaming products wait for units,
-    // and the hand-over costs two more operations between streams.
     const size_t xr = c->x_row_halfs(), kr = c->kv_row_halfs();
     const size_t xsb = c->x_store_bytes(), ksb = c->kv_store_bytes();
     half* dkv = c->dkv[buf];
@@ -112,6 +125,7 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
 
     // adaptive profile: an untimed layer borrows a probe event set (if one is free) so that its copy and
     // GEMM durations can be read later without any synchronisation
+    const bool timed = ev != nullptr;
     int probe_slot = -1;
     if (!ev && c->adapt_alpha > 0.0 && c->have_prof) {
         if (!c->probe_made) {
@@ -126,9 +140,16 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
         }
     }
 
+    // A layer that runs ahead is not timed: the intervals of a timed one are its own and follow one another.  Of the layers
+    // that adapt the profile the first of a step stays in line, for a GEMM rate that is the product's alone.
+    const bool ahead = may_run_ahead && !timed && !(probe_slot >= 0 && layer == 0) && runs_ahead(c, l);
+    const hipStream_t rs = ahead ? c->store : c->compute;
+    c->layers_ahead += ahead;
+
     if (ev) {
         ev->seq = seq;
         ev->split = l;
+        ev->ahead = ahead;
         KVPR_HIP(hipEventRecord(ev->at[LayerEvents::start], c->compute));
     }
     if (c->debug & KVPR_DEBUG_POISON) {
@@ -242,33 +263,35 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
                 if (int rc = kvpr::launch_keep_warm(w->wqkv, (size_t)3 * h * h, t_first * c->keep_warm, c->wall_clock_hz, c->q32, c->compute))
                     return rc;
         }
-        if (nchunk <= 1) KVPR_HIP(hipStreamWaitEvent(c->compute, c->ev_x[buf], 0));
-        if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::r0], c->compute));
+        if (nchunk <= 1) KVPR_HIP(hipStreamWaitEvent(rs, c->ev_x[buf], 0));
+        if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::r0], rs));
         if (l > 0) {
             const half* wkv = (const half*)w->wqkv + (size_t)h * h;
             const half* bkv = w->bqkv ? (const half*)w->bqkv + h : nullptr;
             for (int j = 0; j < nchunk; ++j) {
                 // with several chunks the GEMM of chunk j runs while chunks j+1.. and the cache are still on the link
-                if (nchunk > 1) KVPR_HIP(hipStreamWaitEvent(c->compute, c->ev_chunk[buf][j], 0));
+                if (nchunk > 1) KVPR_HIP(hipStreamWaitEvent(rs, c->ev_chunk[buf][j], 0));
                 const int64_t rows = (int64_t)(bound[j + 1] - bound[j]) * b;
                 if (c->qx)
-                    if (int rc = kvpr::launch_dequant_int4(x_stage + (size_t)bound[j] * xsb, dx + (size_t)bound[j] * xr, rows, h, c->compute))
+                    if (int rc = kvpr::launch_dequant_int4(x_stage + (size_t)bound[j] * xsb, dx + (size_t)bound[j] * xr, rows, h, rs))
                         return rc;
                 // rotary models: the K half is rotated with the positions of its rows, bound[j] .. bound[j+1]-1
                 if (int rc = c->llama
                                  ? kvpr::launch_gemm_rope(dx + (size_t)bound[j] * xr, wkv, bkv, dkv + (size_t)bound[j] * kr, rows, 2 * h, h,
-                                                          2 * (int64_t)h, c->rope_tab, h, c->d.head_dim, b, bound[j], c->compute)
+                                                          2 * (int64_t)h, c->rope_tab, h, c->d.head_dim, b, bound[j], rs)
                                  : kvpr::launch_gemm(dx + (size_t)bound[j] * xr, wkv, bkv, dkv + (size_t)bound[j] * kr, rows, 2 * h, h,
-                                                     2 * (int64_t)h, c->compute))
+                                                     2 * (int64_t)h, rs))
                     return rc;
             }
         }
-        if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::r1], c->compute));
+        if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::r1], rs));
+        if (ahead) KVPR_HIP(hipEventRecord(c->ev_recomputed[buf], rs));
         return debug_sync(c);
     };
-    if (wf) {
+    if (wf || ahead) {
         // offloaded weights: Wk|Wv arrive first, so the recomputation goes first and the projections that need
         // Wq follow (fine-grained MHA pipeline, Sec. 3.3 "Hiding KV cache partial recomputation").
+        // On the store stream it comes before the store-back, which waits for the projections.
         if (int rc = recompute()) return rc;
         if (int rc = project_and_store()) return rc;
     } else {
@@ -285,6 +308,7 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
     // attention is off the critical path and stays one launch.)
     const bool two_phase = c->qkv || (fence_copy_to_start && l >= 128);
     const void* packed = c->qkv ? kv_stage : nullptr;
+    if (ahead) KVPR_HIP(hipStreamWaitEvent(c->compute, c->ev_recomputed[buf], 0));
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::e0], c->compute));
     if (two_phase)
         if (int rc = kvpr::launch_attention_mixed(c->q32, dkv, packed, c->z16, c->attn_ws, seq + 1, l, b, h, c->d.n_heads, 0, c->compute))
@@ -304,7 +328,9 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
                                                  residual))
         return rc;
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::o1], c->compute));
-    if (!c->inline_store()) KVPR_HIP(hipStreamWaitEvent(c->compute, c->ev_store, 0));
+    // Behind a recomputation on the store stream the step waits once, at its end: the next layer's attention, or its wait
+    // here, is behind this store-back anyway, and x_new is not overwritten before that.
+    if (!c->inline_store() && (!ahead || ev)) KVPR_HIP(hipStreamWaitEvent(c->compute, c->ev_store, 0));
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::end], c->compute));
     if (int rc = debug_sync(c)) return rc;
 
@@ -330,9 +356,10 @@ int adapt_poll(kvpr_ctx* c) {
         KVPR_HIP(hipEventElapsedTime(&ms_rc, ev->at[LayerEvents::r0], ev->at[LayerEvents::r1]));
         const int64_t l = ev->split, s = ev->seq;
         const int64_t link_bytes = (int64_t)c->x_store_bytes() * l + (int64_t)c->kv_store_bytes() * (s - l);
-        // with a chunked activation copy the GEMM interval includes waiting for chunks: the link sample only
+        // with a chunked activation copy the GEMM interval includes waiting for chunks, and one that ran ahead shared the
+        // chip: the link sample only
         // (whole rounds of work when the profile says the GEMM works in rounds, as the cost model charges them)
-        int64_t flops = c->chunks > 1 ? 0 : c->flops_per_pos() * l;
+        int64_t flops = c->chunks > 1 || ev->ahead ? 0 : c->flops_per_pos() * l;
         if (const int64_t r = c->prof.gemm_round_flops; r > 0) flops = (flops + r - 1) / r * r;
         if (int rc = kvpr_adapt_update(&c->prof, c->adapt_alpha, link_bytes, ((double)ms_x + (double)ms_kv) * 1e-3, flops,
                                        (double)ms_rc * 1e-3))
@@ -414,6 +441,7 @@ void destroy_impl(kvpr_ctx* c) {
         if (c->ev_x[i]) (void)hipEventDestroy(c->ev_x[i]);
         if (c->ev_kv[i]) (void)hipEventDestroy(c->ev_kv[i]);
         if (c->ev_free[i]) (void)hipEventDestroy(c->ev_free[i]);
+        if (c->ev_recomputed[i]) (void)hipEventDestroy(c->ev_recomputed[i]);
         if (c->ev_buf_store[i]) (void)hipEventDestroy(c->ev_buf_store[i]);
         for (hipEvent_t e : c->ev_chunk[i]) if (e) (void)hipEventDestroy(e);
     }
@@ -431,7 +459,7 @@ void destroy_impl(kvpr_ctx* c) {
         for (hipEvent_t e : we) if (e) (void)hipEventDestroy(e);
     }
     if (c->wstream) (void)hipStreamDestroy(c->wstream);
-    void* dev[] = {c->qk32, c->rope_tab, c->q32, c->z16, c->attn_ws, c->tok_ws, c->hid, c->xn, c->xf, c->resid, c->ffn1, c->dw[0], c->dw[1], c->hid_all};
+    void* dev[] = {c->qk32, c->rope_tab, c->q32, c->z16, c->attn_ws, c->tok_ws, c->hid, c->xn[0], c->xn[1], c->xf, c->resid, c->ffn1, c->dw[0], c->dw[1], c->hid_all};
     for (void* p : dev) if (p) (void)hipFree(p);
     hipEvent_t evs[] = {c->ev_proj, c->ev_store, c->ev_begin};
     for (hipEvent_t e : evs) if (e) (void)hipEventDestroy(e);
@@ -507,7 +535,8 @@ int settle_streams(kvpr_ctx* c) {
     };
     int rc = settle(&c->copy, true, {c->compute});
     if (!rc && c->wstream) rc = settle(&c->wstream, true, {c->compute, c->copy});
-    if (!rc) rc = c->wstream ? settle(&c->store, false, {c->copy, c->wstream}) : settle(&c->store, false, {c->copy});
+    if (!rc) rc = c->wstream ? settle(&c->store, false, {c->copy, c->wstream})
+                            : c->d.ffn_dim > 0 && c->d.n_layers > 1 ? settle(&c->store, false, {c->copy, c->compute}) : settle(&c->store, false, {c->copy});
     for (hipStream_t st : rejected) (void)hipStreamDestroy(st);
     (void)hipEventDestroy(e_busy);
     (void)hipEventDestroy(e_probe);
@@ -625,6 +654,7 @@ int create_impl(const kvpr_model_desc* d, int n_gpu_batches, void* compute_strea
         if ((e = hipEventCreateWithFlags(&c->ev_x[i], hipEventDisableTiming)) != hipSuccess) return bail(KVPR_E_HIP, "event", e);
         if ((e = hipEventCreateWithFlags(&c->ev_kv[i], hipEventDisableTiming)) != hipSuccess) return bail(KVPR_E_HIP, "event", e);
         if ((e = hipEventCreateWithFlags(&c->ev_free[i], hipEventDisableTiming)) != hipSuccess) return bail(KVPR_E_HIP, "event", e);
+        if ((e = hipEventCreateWithFlags(&c->ev_recomputed[i], hipEventDisableTiming)) != hipSuccess) return bail(KVPR_E_HIP, "event", e);
         if ((e = hipEventCreateWithFlags(&c->ev_buf_store[i], hipEventDisableTiming)) != hipSuccess) return bail(KVPR_E_HIP, "event", e);
         for (int j = 0; j < kvpr_ctx::kMaxChunks; ++j)
             if ((e = hipEventCreateWithFlags(&c->ev_chunk[i][j], hipEventDisableTiming)) != hipSuccess) return bail(KVPR_E_HIP, "event", e);
@@ -659,7 +689,7 @@ int create_impl(const kvpr_model_desc* d, int n_gpu_batches, void* compute_strea
             return bail(KVPR_E_HIP, "rotary table upload", e);
     }
     if (d->ffn_dim > 0) {
-        half** bufs[] = {&c->hid, &c->xn, &c->xf, &c->resid};
+        half** bufs[] = {&c->hid, &c->xn[0], &c->xn[1], &c->xf, &c->resid};
         for (half** p : bufs)
             if ((e = hipMalloc((void**)p, bh * sizeof(half))) != hipSuccess) return bail(KVPR_E_NOMEM, "hidden-state buffer", e);
         // gated FFN: [gate | up] (2 ffn columns) followed by their gated product (ffn columns)
@@ -693,6 +723,7 @@ int create_impl(const kvpr_model_desc* d, int n_gpu_batches, void* compute_strea
 }  // namespace
 
 extern "C" int kvpr_debug_streams_replaced(void) { return g_streams_replaced; }
+extern "C" int64_t kvpr_debug_layers_ahead(kvpr_ctx* c) { return c->layers_ahead; }   // since the context was created
 
 extern "C" int kvpr_destroy(kvpr_ctx* c) {
     if (!c) return fail(KVPR_E_INVAL, "ctx is null");
@@ -829,11 +860,11 @@ extern "C" int kvpr_timing_read(kvpr_ctx* c, int slot, kvpr_layer_timing* timing
 
 namespace {
 
-// the parts of a decoder layer around the attention block (c->xn = normalised input of the attention block)
-int pre_attention_norm(kvpr_ctx* c, const kvpr_layer_weights* w, const half* hid_in) {
+// the parts of a decoder layer around the attention block (xn = normalised input of the attention block)
+int pre_attention_norm(kvpr_ctx* c, const kvpr_layer_weights* w, const half* hid_in, half* xn) {
     const int b = c->d.batch, h = c->d.hidden;
-    if (c->llama) return kvpr::launch_rmsnorm(hid_in, w->ln1_g, c->xn, b, h, c->compute);
-    return kvpr::launch_layernorm(hid_in, w->ln1_g, w->ln1_b, c->xn, b, h, c->compute);
+    if (c->llama) return kvpr::launch_rmsnorm(hid_in, w->ln1_g, xn, b, h, c->compute);
+    return kvpr::launch_layernorm(hid_in, w->ln1_g, w->ln1_b, xn, b, h, c->compute);
 }
 
 // hid_out = r + FFN(norm(r)), r = c->resid.  OPT: LayerNorm, ReLU FFN with biases (Eq. 4);
@@ -890,17 +921,28 @@ extern "C" int kvpr_decode_step(kvpr_ctx* c, int seq, const kvpr_layer_weights* 
     if (int rc = step_begin(c)) return rc;
     const size_t bh = (size_t)b * h;
     const half* hid_in = (const half*)x_in_dev;
+    // recomputations on the store stream: behind whatever the caller enqueued that wrote the weights
+    if (!per_layer && std::any_of(ls.begin(), ls.end(), [&](int l) { return runs_ahead(c, l); })) {
+        KVPR_HIP(hipEventRecord(c->ev_begin, c->compute));
+        KVPR_HIP(hipStreamWaitEvent(c->store, c->ev_begin, 0));
+    }
+    int64_t ahead_before = 0;
     for (int i = 0; i < L; ++i) {
+        ahead_before = c->layers_ahead;
         const kvpr_layer_weights* w = &layers[i];
         half* hid_out = (i == L - 1) ? (half*)x_out_dev : c->hid;
         // pre-norm -> attention block -> residual -> norm -> FFN -> residual
-        if (int rc = pre_attention_norm(c, w, hid_in)) return rc;
-        if (int rc = enqueue_layer(c, i, seq, ls[i], w, c->xn, c->resid, i % c->nbuf, per_layer ? &c->tev[i] : nullptr, false, nullptr,
-                                   hid_in))
+        // the store-back of layer i reads this row until the attention of layer i + 1 has started
+        half* xn = c->xn[i & 1];
+        if (int rc = pre_attention_norm(c, w, hid_in, xn)) return rc;
+        if (int rc = enqueue_layer(c, i, seq, ls[i], w, xn, c->resid, i % c->nbuf, per_layer ? &c->tev[i] : nullptr, false, nullptr,
+                                   hid_in, true))
             return rc;
         if (int rc = ffn_block(c, w, hid_out)) return rc;
         hid_in = hid_out;
     }
+    // the last layer's store-back, and with it all of them, unless that layer has waited for it itself
+    if (!c->inline_store() && c->layers_ahead != ahead_before) KVPR_HIP(hipStreamWaitEvent(c->compute, c->ev_store, 0));
     if (int rc = step_end(c)) return rc;
     if (splits_out) std::copy(ls.begin(), ls.end(), splits_out);
     if (per_layer) {
@@ -1030,8 +1072,8 @@ extern "C" int kvpr_decode_step_columns(kvpr_ctx* c, int seq, const void* x_in_d
             // the norm's parameters arrive with [Wk;Wv]: neither the norm nor the recomputation that follows it
             // waits for Wq, Wo and the FFN matrices, which may still be on the link (Sec. 3.3 fine-grained MHA pipeline)
             KVPR_HIP(hipStreamWaitEvent(c->compute, c->weight_pipeline ? c->ev_wkv[wb] : c->ev_wall[wb], 0));
-            if (int rc = pre_attention_norm(c, &w, hid_in)) return rc;
-            if (int rc = enqueue_layer(c, slot, seq, ls[slot], &w, c->xn, c->resid, slot % c->nbuf,
+            if (int rc = pre_attention_norm(c, &w, hid_in, c->xn[0])) return rc;
+            if (int rc = enqueue_layer(c, slot, seq, ls[slot], &w, c->xn[0], c->resid, slot % c->nbuf,
                                        per_slot ? &c->tev[slot] : nullptr, false, &wf, hid_in))
                 return rc;
             if (int rc = ffn_block(c, &w, hid_out)) return rc;

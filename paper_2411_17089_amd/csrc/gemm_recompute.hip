@@ -435,6 +435,11 @@ int launch_any(const void* a, const void* w, const void* bias, void* c, int64_t 
 
 }  // namespace
 
+int64_t gemm_workgroups(int64_t M, int N) {
+    const TileCost& t = kTiles[g_gemm_variant > 0 ? (g_gemm_variant <= 6 ? g_gemm_variant - 1 : 0) : pick_tile(M, N)];
+    return (M + t.bm - 1) / t.bm * ((N + t.bn - 1) / t.bn);
+}
+
 int launch_gemm(const void* a, const void* w, const void* bias, void* c, int64_t M, int N, int K, int64_t ldc,
                 hipStream_t st) {
     if (M == 0) return KVPR_OK;

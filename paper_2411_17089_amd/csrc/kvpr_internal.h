@@ -20,6 +20,7 @@ int fail(int code, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 int compute_units();   // of the current device, read once
 
 // kernels (each validates nothing: callers check shapes first)
+int64_t gemm_workgroups(int64_t M, int N);   // that launch_gemm and launch_gemm_rope make of a product
 int launch_gemm(const void* a, const void* w, const void* bias, void* c, int64_t M, int N, int K,
                 int64_t ldc, hipStream_t st);
 int launch_attention(const void* q, const void* kv, void* z, void* ws, int S, int batch, int hidden,
