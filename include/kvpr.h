@@ -123,7 +123,8 @@ typedef struct {
                                     the smallest tile) */
     double layer_other_s;        /* the rest of one layer's GPU work at this batch / context (token projections,
                                     attention, output projection, FFN if the context has one): used by
-                                    KVPR_COST_PIPE only, where it shares the GPU with the recomputation; 0 = ignore */
+                                    KVPR_COST_PIPE only, which charges it one behind the other with the recomputation
+                                    (also where kvpr_decode_step runs the two side by side); 0 = ignore */
 } kvpr_profile_t;
 
 /* Device pointers to one layer's parameters.  FFN / LayerNorm members may be null when ffn_dim == 0.
