@@ -51,8 +51,8 @@ class BigLayers:
 
 @pytest.mark.parametrize("b,s", [(16, 40), (64, 10)])         # new rows stored on the compute stream, on the store stream
 @pytest.mark.parametrize("poison", [False, True])
-@pytest.mark.parametrize("arch,store", [("opt", "f16"), ("opt", "int4"), ("llama", "f16"), ("llama", "int4")])
-def test_tokens_back_to_back(k, arch, store, poison, b, s):
+@pytest.mark.parametrize("arch,store,chunks", [("opt", "f16", 1), ("opt", "int4", 1), ("llama", "f16", 1), ("llama", "int4", 1), ("opt", "f16", 3), ("llama", "int4", 3)])
+def test_tokens_back_to_back(k, arch, store, chunks, poison, b, s):
     """Three tokens enqueued one behind the other give what the same tokens give one at a time, outputs and host rows: the
     second reads the rows the first one stored, buffers and scratch rows are used again without a wait in between.  Most
     layers recompute beside the previous one; the weights are written just before the first step."""
@@ -65,6 +65,7 @@ def test_tokens_back_to_back(k, arch, store, poison, b, s):
         splits = [[s - 1, s - 2, s], [s, s + 1, s - 1], [0, s + 2, s + 1]]
         final = [d["wqkv"].clone() for d in st.params]
         big = torch.randn(4096, 4096, device="cuda")
+        k.kvpr_set_chunks(st.ctx, chunks)
         k.kvpr_set_debug(st.ctx, k.KVPR_DEBUG_POISON if poison else 0)
         got, before = {}, st.ahead()
         for mode in ("waited", "free", "free again"):
