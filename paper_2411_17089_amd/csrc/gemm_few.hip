@@ -1,0 +1,243 @@
+// Token GEMM for gfx950 and at most 8 rows: y[M, N] = x[M, K] . W[N, K]^T + bias (decode with few sequences).
+//
+// With so few rows the product is a read of W and nothing else, so the kernel is laid out for the read: the rate to reach is
+// that of a plain loop of non-temporal 16-byte loads (6.4 - 6.9 TB/s over 100 - 400 MB here), against which the kernels for
+// up to 64 rows, which take W through LDS or in the operand layout of the 16 x 16 MFMA, reach 4.7 - 5.7.
+//   - v_mfma_f32_4x4x4_16b_f16: 16 independent products of 4 W rows by 4 tokens over 4 columns of K.  A lane owns 16 bytes
+//     of one W row, so a wave load covers 4 rows x 256 contiguous bytes and goes straight into operand registers: no LDS, no
+//     barrier, no transposition, and 4 tokens waste nothing where a 16 x 16 tile would waste three quarters.
+//   - x stays in registers: the 8 waves of a workgroup cut K among themselves, a wave holds its part of x (M x K / 8) and
+//     streams W rows past it, four at a time, the next four in flight.  Read again for every few rows, x cost as many
+//     requests as W (M = 3, W of 5120 x 20480: 40 us that way, 33 with x in registers, 38 with the kernel for 64 rows).
+//   - one workgroup per compute unit, each with an even share of the rows, strided by the grid so that the workgroups read
+//     neighbouring rows at any time; twice or three times as many are up to 4 % slower with 3 tokens or more.
+//   - the 16 partial products are folded over the lanes as they come (8 instructions for 4 rows x 4 tokens); the eight waves
+//     meet in LDS once, at the end, behind the only barrier.
+//   - where K / 8 is more than a wave can hold (P pieces of 128), W is walked in S column segments, the sums of a segment
+//     are added to the wave's own in LDS.
+// us per launch over rotating weights, the kernels for 64 rows -> this one, M = 1 / 4 / 8:
+//   4096 x 4096    9.8 ->  7.3,  9.8 ->  7.6,  9.8 ->  8.1       12288 x 4096  21.5 -> 16.8, 21.5 -> 17.0, 21.6 -> 17.7
+//   16384 x 4096  26.0 -> 21.6, 25.8 -> 21.8, 25.8 -> 22.5       4096 x 16384  27.4 -> 23.2, 27.4 -> 24.1, 27.5 -> 27.4
+//   50272 x 4096  72.2 -> 61.6, 72.9 -> 62.1, 75.2 -> 64.1       22016 x 4096  33.7 -> 28.4, 33.8 -> 28.7, 33.9 -> 29.6
+//   7168 x 7168   21.1 -> 17.6, 21.2 -> 18.1, 21.2 -> 18.7       7168 x 28672  72.5 -> 60.8, 72.8 -> 62.7, 72.9 -> 66.2
+#include "gemm_few.h"
+#include "silu.h"
+
+#include <algorithm>
+#include <type_traits>
+
+namespace kvpr {
+namespace {
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+constexpr int PIECE = 128;       // columns of K that a wave load covers
+
+template <int CTRL>
+__device__ __forceinline__ float rotate_row(float v) {   // within 16 lanes
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+// lanes 0 .. 31 get the sum of a over the two halves of the wave, lanes 32 .. 63 that of b
+__device__ __forceinline__ float fold32(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(a), __float_as_int(b), false, false);
+    return __int_as_float(r[0]) + __int_as_float(r[1]);
+}
+// as fold32 for the two rows of 16 lanes in each half
+__device__ __forceinline__ float fold16(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_int(a), __float_as_int(b), false, false);
+    return __int_as_float(r[0]) + __int_as_float(r[1]);
+}
+
+// MQ: tokens in fours.  P: pieces of K that a wave holds at a time (every wave has P or P - 1 of them in every segment).
+// A unit is 4 output features, or with PAIR 2 x 4: the gate and the up rows of 4 features of a gated FFN.
+template <int MQ, int P, bool PAIR, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void few_tokens(const FewTokens a, int units, int segments) {
+    // rows four at a time: enough of them that a wave has at least four loads in flight behind the ones it works on
+    constexpr int R = P == 1 ? 4 : P == 2 ? 2 : 1;
+    constexpr int PER_UNIT = PAIR ? 2 : 1;
+    extern __shared__ float red[];                            // [group of 4 rows][quad of tokens][row][token][wave]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r4 = lane & 3, chunk = lane >> 2;
+    const int groups = (units - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x * PER_UNIT;
+    const int steps = (groups + R - 1) / R;
+    auto row_of = [&](int g) {                                // first W row of this workgroup's group g
+        const int unit = blockIdx.x + g / PER_UNIT * gridDim.x;
+        return unit * 4 + (PAIR && (g & 1) ? a.N / 2 : 0);
+    };
+    const int pieces = a.K / PIECE, run0 = pieces * wave / WAVES, run = pieces * (wave + 1) / WAVES - run0;
+
+    for (int s = 0; s < segments; ++s) {
+        const int p0 = run0 + run * s / segments, len = run0 + run * (s + 1) / segments - p0;
+        const int k0 = p0 * PIECE + chunk * 8;
+        auto walk = [&](auto count) {
+            constexpr int CNT = decltype(count)::value;
+            if constexpr (CNT == 0) {                         // fewer pieces than waves: K < 1024
+                for (int i = lane; i < groups * MQ * 16; i += 64) red[i * WAVES + wave] = 0.f;
+            } else {
+                half8 xf[MQ][CNT];
+#pragma unroll
+                for (int q = 0; q < MQ; ++q)
+#pragma unroll
+                    for (int u = 0; u < CNT; ++u)
+                        xf[q][u] = *reinterpret_cast<const half8*>(a.x + (int64_t)min(q * 4 + r4, a.M - 1) * a.K + k0 + u * PIECE);
+                struct Rows { half8 w[R][CNT]; };
+                auto load = [&](Rows& f, int st) {            // beyond the last group or row: the last one again, not stored
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const _Float16* p = a.W + (int64_t)min(row_of(min(st * R + r, groups - 1)) + r4, a.N - 1) * a.K + k0;
+#pragma unroll
+                        for (int u = 0; u < CNT; ++u) f.w[r][u] = __builtin_nontemporal_load(reinterpret_cast<const half8*>(p + u * PIECE));
+                    }
+                };
+                auto multiply = [&](const Rows& f, int st) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        floatx4 acc[MQ];
+#pragma unroll
+                        for (int q = 0; q < MQ; ++q) acc[q] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int u = 0; u < CNT; ++u)
+#pragma unroll
+                            for (int q = 0; q < MQ; ++q) {
+                                const half8 w = f.w[r][u], x = xf[q][u];
+                                acc[q] = __builtin_amdgcn_mfma_f32_4x4x4f16(half4{w[0], w[1], w[2], w[3]}, half4{x[0], x[1], x[2], x[3]}, acc[q], 0, 0, 0);
+                                acc[q] = __builtin_amdgcn_mfma_f32_4x4x4f16(half4{w[4], w[5], w[6], w[7]}, half4{x[4], x[5], x[6], x[7]}, acc[q], 0, 0, 0);
+                            }
+                        const int g = st * R + r;
+                        // element e of a lane is W row e by token lane % 4, over the columns of its chunk: summed over the
+                        // chunks, row e ends up in the 16 lanes from 16 e
+#pragma unroll
+                        for (int q = 0; q < MQ; ++q) {
+                            float v = fold16(fold32(acc[q][0], acc[q][2]), fold32(acc[q][1], acc[q][3]));
+                            v += rotate_row<0x124>(v);        // row_ror:4
+                            v += rotate_row<0x128>(v);        // row_ror:8
+                            if ((lane & 15) < 4 && g < groups) {
+                                float* at = red + ((g * MQ + q) * 16 + (lane >> 4) * 4 + r4) * WAVES + wave;
+                                *at = s == 0 ? v : *at + v;
+                            }
+                        }
+                    }
+                };
+                Rows f0, f1;
+                load(f0, 0);
+                int st = 0;
+                for (; st + 2 < steps; st += 2) {
+                    load(f1, st + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    multiply(f0, st);
+                    __builtin_amdgcn_sched_barrier(0);
+                    load(f0, st + 2);
+                    __builtin_amdgcn_sched_barrier(0);
+                    multiply(f1, st + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (st + 1 < steps) {
+                    load(f1, st + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    multiply(f0, st);
+                    multiply(f1, st + 1);
+                } else {
+                    multiply(f0, st);
+                }
+            }
+        };
+        // two loops, so that the number of loads behind the ones that are waited for is known
+        if (len == P) walk(std::integral_constant<int, P>{});
+        else walk(std::integral_constant<int, P - 1>{});
+    }
+    __syncthreads();
+
+    auto sum = [&](int i) {                                   // over the waves
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < WAVES; w += 4) {
+            const float4 f = *reinterpret_cast<const float4*>(red + i * WAVES + w);
+            v += (f.x + f.y) + (f.z + f.w);
+        }
+        return v;
+    };
+    for (int t = threadIdx.x; t < groups / PER_UNIT * MQ * 16; t += WAVES * 64) {
+        const int m = (t >> 4) % MQ * 4 + (t & 3), unit = (t >> 4) / MQ, i = t & 15;
+        const int n = (blockIdx.x + unit * gridDim.x) * 4 + (i >> 2);
+        if (m >= a.M) continue;
+        const int at = (unit * PER_UNIT * MQ + (t >> 4) % MQ) * 16 + i;
+        if constexpr (PAIR) {
+            // both rounded to float16, as a product stored in between would have them
+            const float gate = (float)(_Float16)sum(at), up = (float)(_Float16)sum(at + MQ * 16);
+            a.y16[(int64_t)m * a.ld16 + n] = (_Float16)silu_mul(gate, up);
+        } else {
+            if (n >= a.N) continue;
+            float v = sum(at);
+            if (a.bias) v += (float)a.bias[n];
+            if (a.relu) v = fmaxf(v, 0.f);
+            if (n < a.out_f32_cols) {
+                a.y32[(int64_t)m * a.out_f32_cols + n] = v;
+            } else {
+                // with a residual: rounded once by itself and once more with the residual added
+                const int64_t to = (int64_t)m * a.ld16 + (n - a.out_f32_cols);
+                _Float16 o = (_Float16)v;
+                if (a.res) o = (_Float16)((float)o + (float)a.res[to]);
+                a.y16[to] = o;
+            }
+        }
+    }
+}
+
+template <int MQ, int P, bool PAIR, int WAVES>
+int launch(const FewTokens& a, int segments, hipStream_t st) {
+    const int units = PAIR ? a.N / 8 : (a.N + 3) / 4;
+    constexpr int per_unit = (PAIR ? 2 : 1) * MQ * 16 * WAVES * (int)sizeof(float), room = 64 * 1024;
+    // one workgroup per compute unit, more where the sums of one would take more than 64 KiB of LDS
+    const int cus = compute_units(), rounds = ((units + cus - 1) / cus * per_unit + room - 1) / room;
+    const int grid = std::min(units, cus * rounds), lds = (units + grid - 1) / grid * per_unit;
+    hipLaunchKernelGGL((few_tokens<MQ, P, PAIR, WAVES>), dim3((unsigned)grid), dim3(WAVES * 64), lds, st, a, units, segments);
+    KVPR_HIP(hipGetLastError());
+    return KVPR_OK;
+}
+
+template <int MQ, bool PAIR, int WAVES, int P>
+int launch_pieces(const FewTokens& a, int p, int segments, hipStream_t st) {
+    if constexpr (P > 1)
+        if (p < P) return launch_pieces<MQ, PAIR, WAVES, P - 1>(a, p, segments, st);
+    return launch<MQ, P, PAIR, WAVES>(a, segments, st);
+}
+
+// Waves and pieces.  A wave has 128 registers for its part of x and for two groups of rows: 8 pieces with up to 4 tokens,
+// 7 with up to 8.  One segment where that is enough (K = 7168, M = 8: 18.5 us against 18.9 in two), else with more than 4
+// tokens segments of at most 4 pieces, whose rows are fewer registers to wait for at the end of one (K = 11008: 18.9 against
+// 19.3 us, K = 20480: 37.1 against 38.0).  Where K is a multiple of 16384 the runs of 8 waves are multiples of 4 KiB apart and
+// crowd the same channels: 4 waves, of 7 pieces at a time (4096 x 16384, M = 1 / 3 / 8: 24.7 / 25.7 / 29.3 -> 23.3 / 23.3 / 27.1
+// us; elsewhere they are up to 3 % slower).
+template <int MQ, bool PAIR>
+int launch_split(const FewTokens& a, hipStream_t st) {
+    auto go = [&](auto waves, auto held, int most) {
+        constexpr int W = decltype(waves)::value, P = decltype(held)::value;
+        const int longest = (a.K / PIECE + W - 1) / W;
+        const int segments = longest <= P ? 1 : (longest + most - 1) / most;
+        return launch_pieces<MQ, PAIR, W, P>(a, (longest + segments - 1) / segments, segments, st);
+    };
+    if (a.K % 16384 == 0) return go(std::integral_constant<int, 4>{}, std::integral_constant<int, 7>{}, 7);
+    if constexpr (MQ == 1) return go(std::integral_constant<int, 8>{}, std::integral_constant<int, 8>{}, 8);
+    else return go(std::integral_constant<int, 8>{}, std::integral_constant<int, 7>{}, 4);
+}
+
+}  // namespace
+
+// Up to 8 rows, except where the other kernels are the better ones: 5 rows and more of less than 1024 columns, where the
+// launch is all there is (2304 x 768, M = 8: 3.8 us there, 4.0 here), and 7 or 8 rows in several segments of few steps, whose
+// ends are not hidden (4096 x 11008, M = 8: 18.5 there, in slices of K, and 19.2 here; 4096 x 16384: 27.5 and 27.4; with 5 rows
+// 18.6 and 17.7; 5120 x 13824, five steps: 27.2 and 26.2).
+bool takes_few_tokens(int M, int N, int K) {
+    if (M <= 4) return true;
+    if (M > 8 || K < 1024) return false;
+    return M <= 6 || K <= 7168 || N > 16 * compute_units();
+}
+
+int launch_few_tokens(const FewTokens& a, bool gated, hipStream_t st) {
+    if (a.M <= 4) return gated ? launch_split<1, true>(a, st) : launch_split<1, false>(a, st);
+    return gated ? launch_split<2, true>(a, st) : launch_split<2, false>(a, st);
+}
+
+}  // namespace kvpr

@@ -1,5 +1,6 @@
 // Token GEMM for gfx950: y[M, N] = x[M, K] . W[N, K]^T + bias for M <= 64 rows (the decode token's
-// q/k/v projection of Eq. 1 / Eq. 5, the output projection of Eq. 3, the FFN of Eq. 4).
+// q/k/v projection of Eq. 1 / Eq. 5, the output projection of Eq. 3, the FFN of Eq. 4).  Most products of at most 8 rows go
+// to gemm_few.hip.
 //
 // With so few rows the operation reads every weight once and is bound by HBM, so the kernel is a
 // weight streamer built around v_mfma_f32_16x16x32_f16 (W rows feed the row operand, x rows the
@@ -33,6 +34,7 @@
 // second FFN matrix of Eq. 4) are cut along K instead: gridDim.y workgroups share a block of features, each takes a run
 // of K stages, the float32 partial tiles meet in a workspace and the workgroup that arrives last adds them in slice order
 // and writes the outputs.
+#include "gemm_few.h"
 #include "kvpr_internal.h"
 #include "silu.h"
 #include <mutex>
@@ -376,6 +378,7 @@ int launch_wide(const void* x, const void* w, const void* bias, void* y32, void*
 
 int g_token_tpw = 0;   // 0 = choose from N; tests and sweeps can force 1..8
 int g_token_wide = -1; // -1 = choose from N; 0 = never, 64 / 128 = force that many features per workgroup (tests, sweeps)
+bool token_gemm_forced() { return g_token_tpw > 0 || g_token_wide >= 0; }
 int g_token_ks = 0;    // 0 = choose; 1..8 = force that many K slices (needs a workspace; tests, sweeps)
 
 // workspace bytes of a launch with `ks` K slices: the tickets, then ks partial tiles of float32 per block of RB features
@@ -464,6 +467,9 @@ int launch_token_gemm_flags(const void* x, const void* w, const void* bias, void
                             int out_f32_cols, int64_t ld16, int flags, hipStream_t st, void* ws, size_t ws_bytes,
                             const void* residual) {
     const int relu = flags & 1;
+    if (takes_few_tokens(M, N, K) && !token_gemm_forced())
+        return launch_few_tokens({(const _Float16*)x, (const _Float16*)w, (const _Float16*)bias, (float*)y32, (_Float16*)y16,
+                                  (const _Float16*)residual, ld16, M, N, K, out_f32_cols, relu}, false, st);
     if (ws_bytes <= TOKEN_WS_TICKET_BYTES) ws = nullptr;
     if (M <= 16) return launch_mt<1>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ws, ws_bytes, residual, st);
     if (M <= 32) return launch_mt<2>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ws, ws_bytes, residual, st);
@@ -477,7 +483,9 @@ int launch_token_gemm_flags(const void* x, const void* w, const void* bias, void
 // Below that, and while a kernel choice is forced, the halves go through `mid` [M, 2f].
 int launch_token_gemm_gated(const void* x, const void* w, void* mid, void* y, int M, int f, int K, hipStream_t st, void* ws,
                             size_t ws_bytes) {
-    if (f % 64 || K % WIDE_KB || f / 64 < 144 || g_token_tpw > 0 || g_token_wide >= 0) {
+    if (takes_few_tokens(M, 2 * f, K) && !token_gemm_forced())
+        return launch_few_tokens({(const _Float16*)x, (const _Float16*)w, nullptr, nullptr, (_Float16*)y, nullptr, f, M, 2 * f, K, 0, 0}, true, st);
+    if (f % 64 || K % WIDE_KB || f / 64 < 144 || token_gemm_forced()) {
         if (int rc = launch_token_gemm_flags(x, w, nullptr, nullptr, mid, M, 2 * f, K, 0, 2 * (int64_t)f, 0, st, ws, ws_bytes)) return rc;
         return launch_silu_mul(mid, y, M, f, st);
     }
