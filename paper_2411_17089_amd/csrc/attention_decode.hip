@@ -54,12 +54,22 @@ __device__ __forceinline__ float head_sum(float v) {
     return v;
 }
 
+// a copy job by the workgroups of grid layer z of a launch over (column groups, batch, ...)
+__device__ __forceinline__ void copy_along(const CopyJob& job, int z) {
+    const int block = (z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+    if (block < job.blocks) run_copy_job(job, block);
+}
+
 template <int D, int UNROLL, int ATT_WAVES>
 __global__ __launch_bounds__(ATT_WAVES * 64) void attention_partial(
     const float* __restrict__ q, const _Float16* __restrict__ kv, float* __restrict__ ws_acc,
     float* __restrict__ ws_ml, _Float16* __restrict__ z, int S, int batch, int h, int chunk, int splits,
-    float scale_log2) {
+    float scale_log2, const CopyJob beside) {
     const int cg = blockIdx.x, n = blockIdx.y, sp = blockIdx.z;
+    if (sp >= splits) {                           // behind the splits: copies that go along
+        copy_along(beside, sp - splits);
+        return;
+    }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col = cg * COLS_PER_GROUP + lane * 8;
     const bool active = col < h;
@@ -259,8 +269,12 @@ template <int D, int UNROLL, int ATT_WAVES>
 __global__ __launch_bounds__(ATT_WAVES * 64) void attention_partial_ranged(
     const float* __restrict__ q, const _Float16* __restrict__ kv16,
     float* __restrict__ ws_acc, float* __restrict__ ws_ml, int pos0, int n_pos, int extra_pos, int batch, int h,
-    int chunk, int split_base, float scale_log2, int fuse_slot, _Float16* __restrict__ z) {
+    int chunk, int splits, int split_base, float scale_log2, int fuse_slot, _Float16* __restrict__ z, const CopyJob beside) {
     const int cg = blockIdx.x, n = blockIdx.y, sp = blockIdx.z;
+    if (sp >= splits) {
+        copy_along(beside, sp - splits);
+        return;
+    }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col = cg * COLS_PER_GROUP + lane * 8;
     const bool active = col < h;
@@ -576,18 +590,21 @@ SplitPlan attention_plan(int batch, int hidden, int S, bool whole = true) {
     return sp;
 }
 
+// layers of workgroups behind the splits that a copy job needs
+unsigned layers_for(const CopyJob& job, int groups, int batch) { return (unsigned)((job.blocks + groups * batch - 1) / (groups * batch)); }
+
 int launch_attention_plan(SplitPlan sp, const void* q, const void* kv, void* z, void* ws, int S, int batch, int hidden, int n_heads,
-                          hipStream_t st) {
+                          hipStream_t st, const CopyJob& beside = CopyJob()) {
     const int d = hidden / n_heads;
     const int groups = (hidden + COLS_PER_GROUP - 1) / COLS_PER_GROUP;
     const int cfg = sp.splits == 1 && one_wide_workgroup(batch, hidden, S) ? 3 : g_attn_cfg;
     float* ws_acc = (float*)ws;
     float* ws_ml = ws_acc + (int64_t)sp.splits * batch * hidden;
     const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)d));
-    dim3 grid(groups, batch, sp.splits);
+    dim3 grid(groups, batch, sp.splits + layers_for(beside, groups, batch));
 #define KVPR_LAUNCH_PART(D_, U_, W_)                                                                                \
     hipLaunchKernelGGL((attention_partial<D_, U_, W_>), grid, dim3(64 * W_), 0, st, (const float*)q, (const _Float16*)kv, \
-                       ws_acc, ws_ml, (_Float16*)z, S, batch, hidden, sp.chunk, sp.splits, scale_log2)
+                       ws_acc, ws_ml, (_Float16*)z, S, batch, hidden, sp.chunk, sp.splits, scale_log2, beside)
     if (d == 128) {
         switch (cfg) {
             case 1: KVPR_LAUNCH_PART(128, 8, 4); break;
@@ -613,8 +630,8 @@ int launch_attention_plan(SplitPlan sp, const void* q, const void* kv, void* z, 
 }  // namespace
 
 int launch_attention(const void* q, const void* kv, void* z, void* ws, int S, int batch, int hidden, int n_heads,
-                     hipStream_t st) {
-    return launch_attention_plan(attention_plan(batch, hidden, S), q, kv, z, ws, S, batch, hidden, n_heads, st);
+                     hipStream_t st, const CopyJob& beside) {
+    return launch_attention_plan(attention_plan(batch, hidden, S), q, kv, z, ws, S, batch, hidden, n_heads, st, beside);
 }
 
 // ---- mixed float16 / packed attention in two phases (see the header comment) ----
@@ -639,18 +656,18 @@ MixedPlan plan_mixed(int batch, int hidden, int S, int split, bool packed) {
 
 int launch_ranged(const void* q, const void* kv16, float* ws_acc, float* ws_ml, int pos0, int n_pos,
                   int extra_pos, int batch, int hidden, int d, SplitPlan sp, int split_base, hipStream_t st,
-                  int fuse_slot = -1, void* z = nullptr) {
+                  int fuse_slot = -1, void* z = nullptr, const CopyJob& beside = CopyJob()) {
     const int groups = (hidden + COLS_PER_GROUP - 1) / COLS_PER_GROUP;
     const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)d));
-    dim3 grid(groups, batch, sp.splits);
+    dim3 grid(groups, batch, sp.splits + layers_for(beside, groups, batch));
     if (d == 128)
         hipLaunchKernelGGL((attention_partial_ranged<128, 8, 4>), grid, dim3(256), 0, st, (const float*)q,
                            (const _Float16*)kv16, ws_acc, ws_ml, pos0, n_pos, extra_pos, batch, hidden,
-                           sp.chunk, split_base, scale_log2, fuse_slot, (_Float16*)z);
+                           sp.chunk, sp.splits, split_base, scale_log2, fuse_slot, (_Float16*)z, beside);
     else
         hipLaunchKernelGGL((attention_partial_ranged<64, 8, 4>), grid, dim3(256), 0, st, (const float*)q,
                            (const _Float16*)kv16, ws_acc, ws_ml, pos0, n_pos, extra_pos, batch, hidden,
-                           sp.chunk, split_base, scale_log2, fuse_slot, (_Float16*)z);
+                           sp.chunk, sp.splits, split_base, scale_log2, fuse_slot, (_Float16*)z, beside);
     KVPR_HIP(hipGetLastError());
     return KVPR_OK;
 }
@@ -673,16 +690,16 @@ int launch_packed(const void* q, const void* kvq, float* ws_acc, float* ws_ml, i
 }  // namespace
 
 // phase 0: float16 rows [0, split) and row S-1 of kv16.  phase 1: rows [split, S-1), packed from kvq if it is not null
-// and float16 from kv16 otherwise, then the combine into z.  Both phases of one attention must be given the same S,
+// and float16 from kv16 otherwise, then the combine into z.  Copies go along with phase 0.  Both phases of one attention must be given the same S,
 // split, batch and hidden.
 int launch_attention_mixed(const void* q, const void* kv16, const void* kvq, void* z, void* ws, int S, int split, int batch,
-                           int hidden, int n_heads, int phase, hipStream_t st) {
+                           int hidden, int n_heads, int phase, hipStream_t st, const CopyJob& beside) {
     const int d = hidden / n_heads;
     const MixedPlan p = plan_mixed(batch, hidden, S, split, kvq != nullptr);
     float* ws_acc = (float*)ws;
     float* ws_ml = ws_acc + (int64_t)p.total * batch * hidden;
     if (phase == 0)
-        return launch_ranged(q, kv16, ws_acc, ws_ml, 0, split, S - 1, batch, hidden, d, p.a, 0, st);
+        return launch_ranged(q, kv16, ws_acc, ws_ml, 0, split, S - 1, batch, hidden, d, p.a, 0, st, -1, nullptr, beside);
     // one workgroup per (sequence, column group) in both phases: the second phase merges the first one's partial itself
     const bool fuse = p.a.splits == 1 && p.b.splits == 1;
     if (p.b.splits > 0)

@@ -1,6 +1,7 @@
 // Runtime module (Sec. 3.3): context life cycle, copy / store streams, event-fenced overlap of transfer and
 // recomputation, per-layer decode, the layer-pipelined decode step and the column-by-column schedule.
 #include "context.h"
+#include "gemm_few.h"
 
 #include <algorithm>
 #include <cmath>
@@ -84,14 +85,39 @@ struct WeightFence {
     hipEvent_t all_ready;   // the whole layer has landed
 };
 
-// Single-layer call: up to here a layer's rows come in by a kernel that reads the mapped pinned arrays, in one launch for
-// activations and cache, instead of by two DMA copies, which take about 10 us each before their first byte.  Waited for, at
-// hidden 768: 96 KiB 85 -> 64 us, 456 KiB 84 -> 67, 960 KiB 96 -> 81, 1440 KiB 106 -> 103, 3840 KiB 149 either way.  In the
-// layer pipeline the DMA engine is the better one at every size (4 layers of hidden 4096, batch 1, 0.6 MiB a layer: 628
-// against 653 us): its copies run early and leave the compute units alone.  Where a float16 cache is all that comes in there is
-// no recomputation that the first copy could release early, and the kernel stays the better one for longer (calls in a row,
-// batch 2, 256 positions, hidden 768, 1.5 MiB: 88 -> 77 us; batch 8, 32 positions, hidden 2048, 2 MiB: 97 -> 84).
+// Single-layer call: up to here a layer's rows come in by a kernel that reads the mapped pinned arrays, instead of by two DMA
+// copies, which take about 10 us each before their first byte.  In the layer pipeline the DMA engine is the better one at every
+// size (4 layers of hidden 4096, batch 1, 0.6 MiB a layer: 628 against 653 us): its copies run early and leave the compute
+// units alone.  Where a float16 cache is all that comes in there is no recomputation that the first copy could release early, and
+// the kernel stays the better one for longer (batch 8, 32 positions, hidden 2048, 2 MiB: 97 -> 84 us).
 constexpr size_t kSmallCopy = size_t(1) << 20, kSmallCacheCopy = 2 * kSmallCopy;
+
+// Single-layer call with few new rows (inline_store): everything on the compute stream.  The copies are workgroups of the
+// launches beside which they belong, activations of the token projection, cache of the recomputation, new rows of the attention;
+// four launches and one event are left of seven launches and ten operations on events (hidden 768, batch 2, 96 positions: 57
+// -> 29 us).  What it saves is fixed, about 40 us, and what it gives up is overlap: the cache comes in with the activations, in
+// front of the recomputation, where that leaves no compute units for the copy, and nothing runs beside the projection where
+// that is not the kernel for few rows.  Calls in a row / waited for, in order against DMA copies:
+//   hidden 768, batch 1 - 16: 1 MiB 0.5 / 0.6, 4 MiB 0.8 / 0.85, 8 MiB 0.85 / 0.95, 16 MiB 0.9 - 0.98 / 0.95 - 1.04, 32 MiB 0.96 - 1.03
+//   hidden 4096, batch 1, split 0.4: 4 - 8 MiB (recomputation 25 us, nothing beside it) 0.9 / 0.97; split 0.75: 8 MiB (45 us) 0.97 / 1.05,
+//   16 MiB (60 us) 1.07 / 1.11; batch 10 (no kernel for few rows), split 0.4: 1.02 / 1.08
+//   hidden 7168, batch 1, split 0.4: 1 MiB (cache 14 us) 0.96 / 0.87, 4 MiB (recomputation 43 us) 1.13 / 1.12
+//   hidden 7168, batch 3, split 0.75: 2 MiB (cache 15 us) 1.06 / 1.02 (DMA copies start up behind the projection's 47 us)
+// so: up to 1 MiB always, up to 16 MiB while less overlap is lost than the copies' start-up costs behind that projection.  Over
+// hidden 768 - 7168, batch 1 - 10, 0.3 - 16 MiB and four splits (487 calls): 0.80 / 0.84 of the time on average, 1.05 at most.
+constexpr size_t kInOrderCopy = 16 * kSmallCopy;
+constexpr double kStartUp = 32e-6, kHidden = 0.45, kLinkRate = 55e9, kFewRate = 6.5e12, kWeightRate = 4.6e12;
+
+bool runs_in_order(const kvpr_ctx* c, int l, size_t x_bytes, size_t kv_bytes, bool beside_recompute) {
+    if (!c->inline_store() || x_bytes + kv_bytes > kInOrderCopy) return false;
+    if (x_bytes + kv_bytes <= kSmallCopy) return true;
+    if (c->chunks > 1 || c->keep_warm > 0.0) return false;      // asked for: work while the activations are on the link
+    const int b = c->d.batch, h = c->d.hidden;
+    double lost = 0.0;
+    if (l > 0 && !beside_recompute) lost += std::min(kvpr::gemm_estimate_s((int64_t)l * b, 2 * h, h), (double)kv_bytes / kLinkRate);
+    if (!kvpr::takes_few_tokens(b, 3 * h, h)) lost += 4e-6 + 6.0 * h * h / kWeightRate;
+    return lost < kStartUp - kHidden * 6.0 * h * h / kFewRate;
+}
 
 // Layer pipeline with resident weights: the recomputation needs nothing of this step's hidden states, so it may run on the
 // store stream, in front of this layer's store-back and beside the previous layer's attention, output projection and FFN,
@@ -159,29 +185,46 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
         if (c->qx) if (int rc = kvpr::launch_fill_u16(x_stage, (size_t)seq * xsb / 2, 0xFFFF, c->compute)) return rc;
         if (c->qkv) if (int rc = kvpr::launch_fill_u16(kv_stage, (size_t)seq * ksb / 2, 0xFFFF, c->compute)) return rc;
     }
-    if (fence_copy_to_start || (c->debug & KVPR_DEBUG_POISON)) {
+    const size_t x_bytes = (size_t)l * xsb, kv_bytes = (size_t)(seq - l) * ksb;
+    const bool small_copy = fence_copy_to_start && x_bytes + kv_bytes <= (l == 0 && !c->qkv ? kSmallCacheCopy : kSmallCopy);
+    // the copy of the cache beside the recomputation, if that leaves it compute units (a GEMM workgroup takes a whole one)
+    const kvpr::CopyJob cache_in = kvpr::copy_job(kvpr::kCopyThreads, c->hkv[layer] + (size_t)l * ksb, kv_stage + (size_t)l * ksb, kv_bytes);
+    const bool beside_recompute = l > 0 && kvpr::gemm_workgroups((int64_t)l * b, 2 * h) + cache_in.blocks <= kvpr::compute_units();
+    const bool in_order = fence_copy_to_start && !ev && !wf && runs_in_order(c, l, x_bytes, kv_bytes, beside_recompute);
+    const bool small = small_copy || in_order;
+    const bool at_once = small && !ev;                   // timed: a launch each, with the event in between
+    // In order on the compute stream: behind everything that touched these buffers and rows, which that stream has waited for
+    // (copies in front of an attention, store-backs at the end of their layer or step).
+    if (!in_order && (fence_copy_to_start || (c->debug & KVPR_DEBUG_POISON))) {
         KVPR_HIP(hipEventRecord(c->ev_begin, c->compute));
         KVPR_HIP(hipStreamWaitEvent(c->copy, c->ev_begin, 0));
     }
 
     // ---- copy stream: activations first, then the rest of the cache (the order Eq. 10 assumes) ----
-    if (c->free_recorded[buf]) KVPR_HIP(hipStreamWaitEvent(c->copy, c->ev_free[buf], 0));
-    // ... and the previous user's store-back, which reads its new row out of this device buffer
-    if (c->buf_store_recorded[buf]) KVPR_HIP(hipStreamWaitEvent(c->copy, c->ev_buf_store[buf], 0));
-    // the previous token's store-back wrote host row seq-1 of this slot, which the copies below may read
-    if (c->slot_store_recorded[layer]) KVPR_HIP(hipStreamWaitEvent(c->copy, c->ev_slot_store[layer], 0));
+    if (!in_order) {
+        if (c->free_recorded[buf]) KVPR_HIP(hipStreamWaitEvent(c->copy, c->ev_free[buf], 0));
+        // ... and the previous user's store-back, which reads its new row out of this device buffer
+        if (c->buf_store_recorded[buf]) KVPR_HIP(hipStreamWaitEvent(c->copy, c->ev_buf_store[buf], 0));
+        // the previous token's store-back wrote host row seq-1 of this slot, which the copies below may read
+        if (c->slot_store_recorded[layer]) KVPR_HIP(hipStreamWaitEvent(c->copy, c->ev_slot_store[layer], 0));
+    }
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::c0], c->copy));
     // chunk boundaries: equal parts of [0, l) rounded down to multiples of 8 positions (whole GEMM tile rows
     // at batch 32); a single chunk is the paper's schedule
-    const size_t x_bytes = (size_t)l * xsb, kv_bytes = (size_t)(seq - l) * ksb;
-    const bool small = fence_copy_to_start && x_bytes + kv_bytes <= (l == 0 && !c->qkv ? kSmallCacheCopy : kSmallCopy);
     int nchunk = (l > 0) ? (small ? 1 : std::min(c->chunks, std::max(1, l / 8))) : 0;
     int bound[kvpr_ctx::kMaxChunks + 1];
     for (int j = 0; j <= nchunk; ++j) bound[j] = (j == nchunk) ? l : (int)((int64_t)l * j / nchunk) / 8 * 8;
     const void* rest_from = c->hkv[layer] + (size_t)l * ksb;
     void* rest_to = kv_stage + (size_t)l * ksb;
-    const bool at_once = small && !ev;                   // timed: a launch each, with the event in between
-    if (small)
+    kvpr::CopyJob with_projection, with_recompute, with_attention;
+    if (in_order) {
+        if (beside_recompute) {
+            with_projection = kvpr::copy_job(kvpr::kCopyThreads, c->hx[layer], x_stage, x_bytes);
+            with_recompute = cache_in;
+        } else {
+            with_projection = kvpr::copy_job(kvpr::kCopyThreads, rest_from, rest_to, kv_bytes, c->hx[layer], x_stage, x_bytes);
+        }
+    } else if (small)
         if (int rc = at_once ? kvpr::launch_copy_bytes(rest_from, rest_to, kv_bytes, c->copy, c->hx[layer], x_stage, x_bytes)
                              : kvpr::launch_copy_bytes(c->hx[layer], x_stage, x_bytes, c->copy))
             return rc;
@@ -191,7 +234,7 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
                                     (size_t)(bound[j + 1] - bound[j]) * xsb, hipMemcpyHostToDevice, c->copy));
         if (nchunk > 1) KVPR_HIP(hipEventRecord(c->ev_chunk[buf][j], c->copy));
     }
-    KVPR_HIP(hipEventRecord(c->ev_x[buf], c->copy));
+    if (!in_order) KVPR_HIP(hipEventRecord(c->ev_x[buf], c->copy));
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::c_x], c->copy));
     if (small) {
         if (!at_once)
@@ -210,13 +253,15 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
         if (c->llama) {
             // q and k stay float32 until they are rotated with position seq; v goes straight into the cache row
             if (int rc = kvpr::launch_token_gemm_flags(x_new, w->wqkv, w->bqkv, c->qk32, dkv + (size_t)seq * kr + h, b, 3 * h, h,
-                                                       2 * h, 2 * (int64_t)h, 0, c->compute, c->tok_ws, c->tok_ws_bytes))
+                                                       2 * h, 2 * (int64_t)h, 0, c->compute, c->tok_ws, c->tok_ws_bytes, nullptr,
+                                                       with_projection))
                 return rc;
             if (int rc = kvpr::launch_rope_token(c->qk32, c->rope_tab, seq, b, h, c->d.head_dim, c->q32, dkv + (size_t)seq * kr,
                                                  2 * (int64_t)h, c->compute))
                 return rc;
         } else if (int rc = kvpr::launch_token_gemm_flags(x_new, w->wqkv, w->bqkv, c->q32, dkv + (size_t)seq * kr, b, 3 * h, h, h,
-                                                          2 * (int64_t)h, 0, c->compute, c->tok_ws, c->tok_ws_bytes)) {
+                                                          2 * (int64_t)h, 0, c->compute, c->tok_ws, c->tok_ws_bytes, nullptr,
+                                                          with_projection)) {
             return rc;
         }
         // a compressed store receives the new rows packed (Sec. 4.4); attention below still reads the exact row
@@ -229,11 +274,16 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
         const void* kv_from = kv_stage + (size_t)seq * ksb;
         char *x_to = c->hx[layer] + (size_t)seq * xsb, *kv_to = c->hkv[layer] + (size_t)seq * ksb;
         if (c->inline_store()) {
-            // in order with everything else that touches these rows: the device buffer is released, and with it the slot's
-            // host rows to the copies of the next token, by ev_free behind the attention
-            if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::s0], c->compute));
+            // in order with everything else that touches these rows, beside the attention or (timed) by itself: the device
+            // buffer is released, and with it the slot's host rows to the copies of the next token, by ev_free behind the
+            // attention
+            if (!ev) {
+                with_attention = kvpr::copy_job(256, kv_from, kv_to, ksb, x_from, x_to, xsb);
+                return debug_sync(c);
+            }
+            KVPR_HIP(hipEventRecord(ev->at[LayerEvents::s0], c->compute));
             if (int rc = kvpr::launch_copy_bytes(kv_from, kv_to, ksb, c->compute, x_from, x_to, xsb)) return rc;
-            if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::s1], c->compute));
+            KVPR_HIP(hipEventRecord(ev->at[LayerEvents::s1], c->compute));
             return debug_sync(c);
         }
         KVPR_HIP(hipEventRecord(c->ev_proj, c->compute));
@@ -263,7 +313,7 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
                 if (int rc = kvpr::launch_keep_warm(w->wqkv, (size_t)3 * h * h, t_first * c->keep_warm, c->wall_clock_hz, c->q32, c->compute))
                     return rc;
         }
-        if (nchunk <= 1) KVPR_HIP(hipStreamWaitEvent(rs, c->ev_x[buf], 0));
+        if (nchunk <= 1 && !in_order) KVPR_HIP(hipStreamWaitEvent(rs, c->ev_x[buf], 0));
         if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::r0], rs));
         if (l > 0) {
             const half* wkv = (const half*)w->wqkv + (size_t)h * h;
@@ -278,9 +328,9 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
                 // rotary models: the K half is rotated with the positions of its rows, bound[j] .. bound[j+1]-1
                 if (int rc = c->llama
                                  ? kvpr::launch_gemm_rope(dx + (size_t)bound[j] * xr, wkv, bkv, dkv + (size_t)bound[j] * kr, rows, 2 * h, h,
-                                                          2 * (int64_t)h, c->rope_tab, h, c->d.head_dim, b, bound[j], rs)
+                                                          2 * (int64_t)h, c->rope_tab, h, c->d.head_dim, b, bound[j], rs, with_recompute)
                                  : kvpr::launch_gemm(dx + (size_t)bound[j] * xr, wkv, bkv, dkv + (size_t)bound[j] * kr, rows, 2 * h, h,
-                                                     2 * (int64_t)h, rs))
+                                                     2 * (int64_t)h, rs, with_recompute))
                     return rc;
             }
         }
@@ -311,13 +361,15 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
     if (ahead) KVPR_HIP(hipStreamWaitEvent(c->compute, c->ev_recomputed[buf], 0));
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::e0], c->compute));
     if (two_phase)
-        if (int rc = kvpr::launch_attention_mixed(c->q32, dkv, packed, c->z16, c->attn_ws, seq + 1, l, b, h, c->d.n_heads, 0, c->compute))
+        if (int rc = kvpr::launch_attention_mixed(c->q32, dkv, packed, c->z16, c->attn_ws, seq + 1, l, b, h, c->d.n_heads, 0, c->compute,
+                                                  with_attention))
             return rc;
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::e1], c->compute));
     if (!at_once) KVPR_HIP(hipStreamWaitEvent(c->compute, c->ev_kv[buf], 0));   // else it came with ev_x
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::a0], c->compute));
     if (int rc = two_phase ? kvpr::launch_attention_mixed(c->q32, dkv, packed, c->z16, c->attn_ws, seq + 1, l, b, h, c->d.n_heads, 1, c->compute)
-                           : kvpr::launch_attention(c->q32, dkv, c->z16, c->attn_ws, seq + 1, b, h, c->d.n_heads, c->compute))
+                           : kvpr::launch_attention(c->q32, dkv, c->z16, c->attn_ws, seq + 1, b, h, c->d.n_heads, c->compute,
+                                                    with_attention))
         return rc;
     KVPR_HIP(hipEventRecord(c->ev_free[buf], c->compute));
     c->free_recorded[buf] = true;

@@ -272,38 +272,19 @@ int launch_layernorm(const void* x, const void* g, const void* b, void* y, int r
     return launch_norm<false>(x, g, b, y, rows, h, st);
 }
 
-// plain copy of two ranges (used for rows that go to mapped pinned host memory) in pieces of sizeof(T) bytes, then the
-// tails byte-wise.  One launch for both: the new K|V row and the new activation row of a layer go to the host together,
-// and each launch is about 4 us of a call that launches bound.
-struct CopyRange {
-    const unsigned char* src;
-    unsigned char* dst;
-    size_t bytes;
-};
-template <class T>
-__global__ void copy_bytes_kernel(CopyRange a, CopyRange b) {
-    const CopyRange r = blockIdx.y ? b : a;
-    const size_t n = r.bytes / sizeof(T);
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
-        reinterpret_cast<T*>(r.dst)[i] = reinterpret_cast<const T*>(r.src)[i];
-    for (size_t i = n * sizeof(T) + (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < r.bytes; i += stride) r.dst[i] = r.src[i];
+// plain copy of up to two ranges, one launch for both: the new K|V row and the new activation row of a layer go to the host
+// together, and each launch is about 4 us of a call that launches bound
+__global__ void copy_kernel(CopyJob job) { run_copy_job(job, blockIdx.x); }
+
+int launch_copy(const CopyJob& job, int threads, hipStream_t st) {
+    if (job.blocks == 0) return KVPR_OK;
+    hipLaunchKernelGGL(copy_kernel, dim3((unsigned)job.blocks), dim3((unsigned)threads), 0, st, job);
+    KVPR_HIP(hipGetLastError());
+    return KVPR_OK;
 }
 
 int launch_copy_bytes(const void* src, void* dst, size_t bytes, hipStream_t st, const void* src2, void* dst2, size_t bytes2) {
-    if (bytes == 0 && bytes2 == 0) return KVPR_OK;
-    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
-    const CopyRange a{(const unsigned char*)src, (unsigned char*)dst, bytes}, b{(const unsigned char*)src2, (unsigned char*)dst2, bytes2};
-    const dim3 grid((unsigned)std::min<size_t>((std::max(bytes, bytes2) / 16 + 255) / 256 + 1, 256), bytes2 ? 2 : 1);
-    // widest piece all pointers are aligned to (packed 4-bit rows are multiples of 8 bytes, not always of 16)
-    const uintptr_t all = (uintptr_t)src | (uintptr_t)dst | (uintptr_t)src2 | (uintptr_t)dst2;
-    if ((all & 15) == 0) hipLaunchKernelGGL(copy_bytes_kernel<u4>, grid, dim3(256), 0, st, a, b);
-    else if ((all & 7) == 0) hipLaunchKernelGGL(copy_bytes_kernel<u2>, grid, dim3(256), 0, st, a, b);
-    else if ((all & 3) == 0) hipLaunchKernelGGL(copy_bytes_kernel<unsigned int>, grid, dim3(256), 0, st, a, b);
-    else hipLaunchKernelGGL(copy_bytes_kernel<unsigned char>, grid, dim3(256), 0, st, a, b);
-    KVPR_HIP(hipGetLastError());
-    return KVPR_OK;
+    return launch_copy(copy_job(256, src, dst, bytes, src2, dst2, bytes2, 512), 256, st);
 }
 
 }  // namespace kvpr

@@ -18,6 +18,6 @@ struct FewTokens {
 };
 
 // gated: W is [gate; up] of N / 2 features each (a multiple of 4), y16 [M, N / 2] = silu(x gate^T) * (x up^T); nothing else applies
-int launch_few_tokens(const FewTokens& a, bool gated, hipStream_t st);
+int launch_few_tokens(const FewTokens& a, bool gated, hipStream_t st, const CopyJob& beside = CopyJob());
 
 }  // namespace kvpr

@@ -53,17 +53,21 @@ __device__ __forceinline__ float fold16(float a, float b) {
 // MQ: tokens in fours.  P: pieces of K that a wave holds at a time (every wave has P or P - 1 of them in every segment).
 // A unit is 4 output features, or with PAIR 2 x 4: the gate and the up rows of 4 features of a gated FFN.
 template <int MQ, int P, bool PAIR, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void few_tokens(const FewTokens a, int units, int segments) {
+__global__ __launch_bounds__(WAVES * 64) void few_tokens(const FewTokens a, int units, int segments, int grid, const CopyJob beside) {
     // rows four at a time: enough of them that a wave has at least four loads in flight behind the ones it works on
     constexpr int R = P == 1 ? 4 : P == 2 ? 2 : 1;
     constexpr int PER_UNIT = PAIR ? 2 : 1;
+    if ((int)blockIdx.x >= grid) {                            // copies that go along
+        run_copy_job(beside, blockIdx.x - grid);
+        return;
+    }
     extern __shared__ float red[];                            // [group of 4 rows][quad of tokens][row][token][wave]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r4 = lane & 3, chunk = lane >> 2;
-    const int groups = (units - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x * PER_UNIT;
+    const int groups = (units - (int)blockIdx.x + grid - 1) / grid * PER_UNIT;
     const int steps = (groups + R - 1) / R;
     auto row_of = [&](int g) {                                // first W row of this workgroup's group g
-        const int unit = blockIdx.x + g / PER_UNIT * gridDim.x;
+        const int unit = blockIdx.x + g / PER_UNIT * grid;
         return unit * 4 + (PAIR && (g & 1) ? a.N / 2 : 0);
     };
     const int pieces = a.K / PIECE, run0 = pieces * wave / WAVES, run = pieces * (wave + 1) / WAVES - run0;
@@ -160,7 +164,7 @@ __global__ __launch_bounds__(WAVES * 64) void few_tokens(const FewTokens a, int 
     };
     for (int t = threadIdx.x; t < groups / PER_UNIT * MQ * 16; t += WAVES * 64) {
         const int m = (t >> 4) % MQ * 4 + (t & 3), unit = (t >> 4) / MQ, i = t & 15;
-        const int n = (blockIdx.x + unit * gridDim.x) * 4 + (i >> 2);
+        const int n = (blockIdx.x + unit * grid) * 4 + (i >> 2);
         if (m >= a.M) continue;
         const int at = (unit * PER_UNIT * MQ + (t >> 4) % MQ) * 16 + i;
         if constexpr (PAIR) {
@@ -186,22 +190,23 @@ __global__ __launch_bounds__(WAVES * 64) void few_tokens(const FewTokens a, int 
 }
 
 template <int MQ, int P, bool PAIR, int WAVES>
-int launch(const FewTokens& a, int segments, hipStream_t st) {
+int launch(const FewTokens& a, int segments, hipStream_t st, const CopyJob& beside) {
     const int units = PAIR ? a.N / 8 : (a.N + 3) / 4;
     constexpr int per_unit = (PAIR ? 2 : 1) * MQ * 16 * WAVES * (int)sizeof(float), room = 64 * 1024;
     // one workgroup per compute unit, more where the sums of one would take more than 64 KiB of LDS
     const int cus = compute_units(), rounds = ((units + cus - 1) / cus * per_unit + room - 1) / room;
     const int grid = std::min(units, cus * rounds), lds = (units + grid - 1) / grid * per_unit;
-    hipLaunchKernelGGL((few_tokens<MQ, P, PAIR, WAVES>), dim3((unsigned)grid), dim3(WAVES * 64), lds, st, a, units, segments);
+    hipLaunchKernelGGL((few_tokens<MQ, P, PAIR, WAVES>), dim3((unsigned)(grid + beside.blocks)), dim3(WAVES * 64), lds, st, a, units, segments,
+                       grid, beside);
     KVPR_HIP(hipGetLastError());
     return KVPR_OK;
 }
 
 template <int MQ, bool PAIR, int WAVES, int P>
-int launch_pieces(const FewTokens& a, int p, int segments, hipStream_t st) {
+int launch_pieces(const FewTokens& a, int p, int segments, hipStream_t st, const CopyJob& beside) {
     if constexpr (P > 1)
-        if (p < P) return launch_pieces<MQ, PAIR, WAVES, P - 1>(a, p, segments, st);
-    return launch<MQ, P, PAIR, WAVES>(a, segments, st);
+        if (p < P) return launch_pieces<MQ, PAIR, WAVES, P - 1>(a, p, segments, st, beside);
+    return launch<MQ, P, PAIR, WAVES>(a, segments, st, beside);
 }
 
 // Waves and pieces.  A wave has 128 registers for its part of x and for two groups of rows: 8 pieces with up to 4 tokens,
@@ -211,12 +216,12 @@ int launch_pieces(const FewTokens& a, int p, int segments, hipStream_t st) {
 // crowd the same channels: 4 waves, of 7 pieces at a time (4096 x 16384, M = 1 / 3 / 8: 24.7 / 25.7 / 29.3 -> 23.3 / 23.3 / 27.1
 // us; elsewhere they are up to 3 % slower).
 template <int MQ, bool PAIR>
-int launch_split(const FewTokens& a, hipStream_t st) {
+int launch_split(const FewTokens& a, hipStream_t st, const CopyJob& beside) {
     auto go = [&](auto waves, auto held, int most) {
         constexpr int W = decltype(waves)::value, P = decltype(held)::value;
         const int longest = (a.K / PIECE + W - 1) / W;
         const int segments = longest <= P ? 1 : (longest + most - 1) / most;
-        return launch_pieces<MQ, PAIR, W, P>(a, (longest + segments - 1) / segments, segments, st);
+        return launch_pieces<MQ, PAIR, W, P>(a, (longest + segments - 1) / segments, segments, st, beside);
     };
     if (a.K % 16384 == 0) return go(std::integral_constant<int, 4>{}, std::integral_constant<int, 7>{}, 7);
     if constexpr (MQ == 1) return go(std::integral_constant<int, 8>{}, std::integral_constant<int, 8>{}, 8);
@@ -235,9 +240,9 @@ bool takes_few_tokens(int M, int N, int K) {
     return M <= 6 || K <= 7168 || N > 16 * compute_units();
 }
 
-int launch_few_tokens(const FewTokens& a, bool gated, hipStream_t st) {
-    if (a.M <= 4) return gated ? launch_split<1, true>(a, st) : launch_split<1, false>(a, st);
-    return gated ? launch_split<2, true>(a, st) : launch_split<2, false>(a, st);
+int launch_few_tokens(const FewTokens& a, bool gated, hipStream_t st, const CopyJob& beside) {
+    if (a.M <= 4) return gated ? launch_split<1, true>(a, st, beside) : launch_split<1, false>(a, st, beside);
+    return gated ? launch_split<2, true>(a, st, beside) : launch_split<2, false>(a, st, beside);
 }
 
 }  // namespace kvpr

@@ -75,11 +75,11 @@ __device__ __forceinline__ void wait_counts() {
     __builtin_amdgcn_s_waitcnt((VM & 15) | ((VM >> 4) << 14) | 0x0070 | (LGKM0 ? 0 : 0x0F00));
 }
 
-template <int BM, int BN, int WM, int WN, int GROUP_M, int D, int HD>
+template <int BM, int BN, int WM, int WN, int GROUP_M, int D, int HD, bool BESIDE>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_bias_f16(
     const _Float16* __restrict__ A, const _Float16* __restrict__ W, const _Float16* __restrict__ bias,
     _Float16* __restrict__ C, int64_t M, int N, int K, int64_t ldc, int tiles_m, int tiles_n, int tiles_per_xcd,
-    int xcd_split_n, RopeArgs rope) {
+    int xcd_split_n, RopeArgs rope, const CopyJob beside) {
     constexpr int NW = WM * WN;
     constexpr int WTM = BM / WM, WTN = BN / WN;
     constexpr int TM = WTM / 16, TN = WTN / 16, TMH = TM / 2, TNH = TN / 2;
@@ -102,6 +102,13 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bias_f16(
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
 
     const int pid = blockIdx.x;
+    // behind the tiles: copies that go along.  (An instantiation of its own: the branch in all of them costs the large product
+    // 1.6 %, 3690 -> 3750 us at M = 24576, N = 14336, K = 7168.)
+    if constexpr (BESIDE)
+        if (pid >= tiles_per_xcd * 8) {
+            run_copy_job(beside, pid - tiles_per_xcd * 8);
+            return;
+        }
     int tile_m, tile_n;
     if (xcd_split_n) {
         const int xcd = pid & 7, i = pid >> 3;
@@ -365,13 +372,15 @@ bool band_mapping(int N, int K) {
     return (int64_t)N * K * 2 > ((int64_t)128 << 20);
 }
 
-template <int BM, int BN, int WM, int WN, int D, int HD>
+template <int BM, int BN, int WM, int WN, int D, int HD, bool BESIDE = false>
 int launch_tile(const void* a, const void* w, const void* bias, void* c, int64_t M, int N, int K, int64_t ldc,
-                hipStream_t st, RopeArgs rope) {
+                hipStream_t st, RopeArgs rope, const CopyJob& beside) {
     // raster groups of 4 tile rows: 32 compute units of an XCD cover a 4 x 8 block.  8 rows per group: 1337 instead of
     // 1410 TFLOP/s at M = 24576, N = 14336, K = 7168 (band mapping), 1330 instead of 1386 at M = 26624, N = 8192,
     // K = 4096 (row mapping); 2 rows within 1 % of 4, 5 and 6 as 8.
-    auto kern = gemm_bias_f16<BM, BN, WM, WN, 4, D, HD>;
+    if constexpr (!BESIDE)
+        if (beside.blocks > 0) return launch_tile<BM, BN, WM, WN, D, HD, true>(a, w, bias, c, M, N, K, ldc, st, rope, beside);
+    auto kern = gemm_bias_f16<BM, BN, WM, WN, 4, D, HD, BESIDE>;
     constexpr int ring_bytes = (D * (BM + BN) + (BM < BN ? BM : BN)) * ROW_BYTES, c_bytes = BM * (BN * 2 + 16);
     constexpr int lds_bytes = ring_bytes > c_bytes ? ring_bytes : c_bytes;
     static_assert(lds_bytes <= 160 * 1024, "LDS of a compute unit");
@@ -387,9 +396,10 @@ int launch_tile(const void* a, const void* w, const void* bias, void* c, int64_t
     const int xcd_split_n = band_mapping(N, K) ? 1 : 0;
     const int max_width = (tiles_n + 7) / 8;
     const int tiles_per_xcd = xcd_split_n ? max_width * tiles_m : (int)((total + 7) / 8);
-    const unsigned grid = (unsigned)(tiles_per_xcd * 8);
+    const unsigned grid = (unsigned)(tiles_per_xcd * 8 + beside.blocks);
+    static_assert(WM * WN * 64 == kCopyThreads, "copies are cut for workgroups of this size");
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WM * WN * 64), lds_bytes, st, (const _Float16*)a, (const _Float16*)w,
-                       (const _Float16*)bias, (_Float16*)c, M, N, K, ldc, tiles_m, tiles_n, tiles_per_xcd, xcd_split_n, rope);
+                       (const _Float16*)bias, (_Float16*)c, M, N, K, ldc, tiles_m, tiles_n, tiles_per_xcd, xcd_split_n, rope, beside);
     KVPR_HIP(hipGetLastError());
     return KVPR_OK;
 }
@@ -407,7 +417,7 @@ constexpr TileCost kTiles[] = {{256, 256, 1537, 1114}, {192, 256, 1199, 926}, {2
 // less than `least`.  (K is a common factor: all tiles take the same number of stages.)  The costs are a fit to 378 timings
 // (hidden 4096 / 5120 / 7168, N = 2 hidden, M = 1 .. 4096, all six tiles): they predict them to 9 % (rms), and the tile they
 // pick is within 0.2 % of the fastest on average and 8 % at worst.
-int pick_tile(int64_t M, int N) {
+int pick_tile(int64_t M, int N, int64_t* stage_ns = nullptr) {
     const int64_t cus = compute_units();
     int best = 0;
     int64_t best_cost = INT64_MAX;
@@ -417,19 +427,20 @@ int pick_tile(int64_t M, int N) {
         const int64_t cost = tiles / cus * t.full + (rem ? std::max<int64_t>(t.least, t.full * rem / cus) : 0);
         if (cost < best_cost) { best_cost = cost; best = i; }
     }
+    if (stage_ns) *stage_ns = best_cost;
     return best;
 }
 
 template <int HD>
 int launch_any(const void* a, const void* w, const void* bias, void* c, int64_t M, int N, int K, int64_t ldc, hipStream_t st,
-               RopeArgs rope) {
+               RopeArgs rope, const CopyJob& beside) {
     switch (g_gemm_variant > 0 ? g_gemm_variant - 1 : pick_tile(M, N)) {
-        case 1: return launch_tile<192, 256, 4, 2, 2, HD>(a, w, bias, c, M, N, K, ldc, st, rope);
-        case 2: return launch_tile<256, 128, 4, 2, 3, HD>(a, w, bias, c, M, N, K, ldc, st, rope);
-        case 3: return launch_tile<192, 128, 4, 2, 3, HD>(a, w, bias, c, M, N, K, ldc, st, rope);
-        case 4: return launch_tile<128, 128, 4, 2, 4, HD>(a, w, bias, c, M, N, K, ldc, st, rope);
-        case 5: return launch_tile<64, 128, 2, 4, 6, HD>(a, w, bias, c, M, N, K, ldc, st, rope);
-        default: return launch_tile<256, 256, 2, 4, 2, HD>(a, w, bias, c, M, N, K, ldc, st, rope);
+        case 1: return launch_tile<192, 256, 4, 2, 2, HD>(a, w, bias, c, M, N, K, ldc, st, rope, beside);
+        case 2: return launch_tile<256, 128, 4, 2, 3, HD>(a, w, bias, c, M, N, K, ldc, st, rope, beside);
+        case 3: return launch_tile<192, 128, 4, 2, 3, HD>(a, w, bias, c, M, N, K, ldc, st, rope, beside);
+        case 4: return launch_tile<128, 128, 4, 2, 4, HD>(a, w, bias, c, M, N, K, ldc, st, rope, beside);
+        case 5: return launch_tile<64, 128, 2, 4, 6, HD>(a, w, bias, c, M, N, K, ldc, st, rope, beside);
+        default: return launch_tile<256, 256, 2, 4, 2, HD>(a, w, bias, c, M, N, K, ldc, st, rope, beside);
     }
 }
 
@@ -440,19 +451,26 @@ int64_t gemm_workgroups(int64_t M, int N) {
     return (M + t.bm - 1) / t.bm * ((N + t.bn - 1) / t.bn);
 }
 
+double gemm_estimate_s(int64_t M, int N, int K) {
+    int64_t stage_ns = 0;
+    if (M > 0) pick_tile(M, N, &stage_ns);
+    return 1e-9 * (double)stage_ns * (K / BK);
+}
+
 int launch_gemm(const void* a, const void* w, const void* bias, void* c, int64_t M, int N, int K, int64_t ldc,
-                hipStream_t st) {
-    if (M == 0) return KVPR_OK;
-    return launch_any<0>(a, w, bias, c, M, N, K, ldc, st, RopeArgs{nullptr, 0, 1, 0});
+                hipStream_t st, const CopyJob& beside) {
+    if (M == 0) return launch_copy(beside, kCopyThreads, st);
+    return launch_any<0>(a, w, bias, c, M, N, K, ldc, st, RopeArgs{nullptr, 0, 1, 0}, beside);
 }
 
 // Eq. 7 for a rotary model: as launch_gemm, with columns [0, rope_cols) (the K half) rotated by the position
 // pos0 + row / batch of their row.  table: float2 [positions][head_dim/2] on the device.
 int launch_gemm_rope(const void* a, const void* w, const void* bias, void* c, int64_t M, int N, int K, int64_t ldc,
-                     const void* table, int rope_cols, int head_dim, int batch, int pos0, hipStream_t st) {
-    if (M == 0) return KVPR_OK;
+                     const void* table, int rope_cols, int head_dim, int batch, int pos0, hipStream_t st, const CopyJob& beside) {
+    if (M == 0) return launch_copy(beside, kCopyThreads, st);
     const RopeArgs r{(const float2*)table, rope_cols, batch, pos0};
-    return head_dim == 64 ? launch_any<64>(a, w, bias, c, M, N, K, ldc, st, r) : launch_any<128>(a, w, bias, c, M, N, K, ldc, st, r);
+    return head_dim == 64 ? launch_any<64>(a, w, bias, c, M, N, K, ldc, st, r, beside)
+                          : launch_any<128>(a, w, bias, c, M, N, K, ldc, st, r, beside);
 }
 
 }  // namespace kvpr

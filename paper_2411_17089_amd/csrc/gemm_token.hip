@@ -465,11 +465,12 @@ int launch_mt(const void* x, const void* w, const void* bias, void* y32, void* y
 // launch that uses it and are zero again when a launch ends; launches that share a workspace must not overlap.
 int launch_token_gemm_flags(const void* x, const void* w, const void* bias, void* y32, void* y16, int M, int N, int K,
                             int out_f32_cols, int64_t ld16, int flags, hipStream_t st, void* ws, size_t ws_bytes,
-                            const void* residual) {
+                            const void* residual, const CopyJob& beside) {
     const int relu = flags & 1;
     if (takes_few_tokens(M, N, K) && !token_gemm_forced())
         return launch_few_tokens({(const _Float16*)x, (const _Float16*)w, (const _Float16*)bias, (float*)y32, (_Float16*)y16,
-                                  (const _Float16*)residual, ld16, M, N, K, out_f32_cols, relu}, false, st);
+                                  (const _Float16*)residual, ld16, M, N, K, out_f32_cols, relu}, false, st, beside);
+    if (int rc = launch_copy(beside, kCopyThreads, st)) return rc;
     if (ws_bytes <= TOKEN_WS_TICKET_BYTES) ws = nullptr;
     if (M <= 16) return launch_mt<1>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ws, ws_bytes, residual, st);
     if (M <= 32) return launch_mt<2>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ws, ws_bytes, residual, st);

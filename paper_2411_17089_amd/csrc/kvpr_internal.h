@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stddef.h>
+#include "copy_job.h"
 #include "kvpr.h"
 
 namespace kvpr {
@@ -21,16 +22,18 @@ int compute_units();   // of the current device, read once
 
 // kernels (each validates nothing: callers check shapes first)
 int64_t gemm_workgroups(int64_t M, int N);   // that launch_gemm and launch_gemm_rope make of a product
+double gemm_estimate_s(int64_t M, int N, int K);   // how long, to about a tenth
+// `beside`: copies by extra workgroups of the launch, whose results the launch itself does not read
 int launch_gemm(const void* a, const void* w, const void* bias, void* c, int64_t M, int N, int K,
-                int64_t ldc, hipStream_t st);
+                int64_t ldc, hipStream_t st, const CopyJob& beside = CopyJob());
 int launch_attention(const void* q, const void* kv, void* z, void* ws, int S, int batch, int hidden,
-                     int n_heads, hipStream_t st);
+                     int n_heads, hipStream_t st, const CopyJob& beside = CopyJob());
 size_t attention_workspace_bytes(int batch, int hidden, int n_heads, int S);
 int launch_attention_mixed(const void* q, const void* kv16, const void* kvq, void* z, void* ws, int S, int split, int batch,
-                           int hidden, int n_heads, int phase, hipStream_t st);
+                           int hidden, int n_heads, int phase, hipStream_t st, const CopyJob& beside = CopyJob());
 int launch_token_gemm_flags(const void* x, const void* w, const void* bias, void* y32, void* y16, int M, int N,
                             int K, int out_f32_cols, int64_t ld16, int flags /*bit0: ReLU*/, hipStream_t st,
-                            void* ws = nullptr, size_t ws_bytes = 0, const void* residual = nullptr);
+                            void* ws = nullptr, size_t ws_bytes = 0, const void* residual = nullptr, const CopyJob& beside = CopyJob());
 int launch_token_gemm_gated(const void* x, const void* w, void* mid, void* y, int M, int f, int K, hipStream_t st, void* ws,
                             size_t ws_bytes);
 size_t token_gemm_workspace_bytes(int M, int N);
@@ -39,7 +42,7 @@ int launch_fill_random(void* p, size_t n_halfs, float scale, uint32_t seed, hipS
 int launch_layernorm(const void* x, const void* g, const void* b, void* y, int rows, int h, hipStream_t st);
 int launch_argmax_gather(const float* logits, int M, int N, int32_t* tokens, const void* table, void* x_next, int h, hipStream_t st);
 int launch_gemm_rope(const void* a, const void* w, const void* bias, void* c, int64_t M, int N, int K, int64_t ldc,
-                     const void* table, int rope_cols, int head_dim, int batch, int pos0, hipStream_t st);
+                     const void* table, int rope_cols, int head_dim, int batch, int pos0, hipStream_t st, const CopyJob& beside = CopyJob());
 int launch_rmsnorm(const void* x, const void* g, void* y, int rows, int h, hipStream_t st);
 int launch_silu_mul(const void* gu, void* y, int rows, int f, hipStream_t st);
 int launch_rope_token(const void* qk32, const void* table, int pos, int batch, int h, int head_dim, void* q32, void* k16,
@@ -47,6 +50,8 @@ int launch_rope_token(const void* qk32, const void* table, int pos, int batch, i
 size_t int4_row_bytes(int cols);
 int launch_quant_int4(const void* src, void* dst, int64_t rows, int cols, hipStream_t st);
 int launch_dequant_int4(const void* src, void* dst, int64_t rows, int cols, hipStream_t st);
+constexpr int kCopyThreads = 512;     // of the workgroups of the GEMM tiles and of the token GEMM that take copies along
+int launch_copy(const CopyJob& job, int threads, hipStream_t st);
 int launch_copy_bytes(const void* src, void* dst, size_t bytes, hipStream_t st, const void* src2 = nullptr, void* dst2 = nullptr,
                       size_t bytes2 = 0);
 int launch_keep_warm(const void* w, size_t n_w, double seconds, double wall_clock_hz, void* sink, hipStream_t st);
