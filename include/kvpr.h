@@ -145,7 +145,7 @@ typedef struct {
     float ms_act_copy;   /* H2D of X[0:l]                                              */
     float ms_kv_copy;    /* H2D of KV[l:s]                                             */
     float ms_recompute;  /* recompute GEMM (Eq. 7)                                     */
-    float ms_proj;       /* new-token q/k/v projection (Eq. 1, Eq. 5)                  */
+    float ms_proj;       /* new-token q/k/v projection (Eq. 1, Eq. 5), with the norm in front where one launch does both */
     float ms_attn;       /* decode attention (Eq. 2): both phases when it ran in two           */
     float ms_out;        /* output projection (Eq. 3)                                  */
     float ms_store;      /* the new X / KV rows written into the pinned host store    */

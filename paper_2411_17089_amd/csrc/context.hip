@@ -139,7 +139,7 @@ bool runs_ahead(const kvpr_ctx* c, int l) {
 
 int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weights* w, const half* x_new, half* out, int buf,
                   LayerEvents* ev, bool fence_copy_to_start, const WeightFence* wf = nullptr, const half* residual = nullptr,
-                  bool may_run_ahead = false) {
+                  bool may_run_ahead = false, const kvpr::TokenNorm* norm = nullptr) {
     const int b = c->d.batch, h = c->d.hidden;
     const size_t xr = c->x_row_halfs(), kr = c->kv_row_halfs();
     const size_t xsb = c->x_store_bytes(), ksb = c->kv_store_bytes();
@@ -251,17 +251,12 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
         if (wf) KVPR_HIP(hipStreamWaitEvent(c->compute, wf->all_ready, 0));
         if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::p0], c->compute));
         if (c->llama) {
-            // q and k stay float32 until they are rotated with position seq; v goes straight into the cache row
-            if (int rc = kvpr::launch_token_gemm_flags(x_new, w->wqkv, w->bqkv, c->qk32, dkv + (size_t)seq * kr + h, b, 3 * h, h,
-                                                       2 * h, 2 * (int64_t)h, 0, c->compute, c->tok_ws, c->tok_ws_bytes, nullptr,
-                                                       with_projection))
-                return rc;
-            if (int rc = kvpr::launch_rope_token(c->qk32, c->rope_tab, seq, b, h, c->d.head_dim, c->q32, dkv + (size_t)seq * kr,
-                                                 2 * (int64_t)h, c->compute))
+            if (int rc = kvpr::launch_token_qkv_rope(x_new, w->wqkv, w->bqkv, c->qk32, c->q32, dkv + (size_t)seq * kr, b, h, c->d.head_dim,
+                                                     c->rope_tab, seq, c->compute, c->tok_ws, c->tok_ws_bytes, with_projection, norm))
                 return rc;
         } else if (int rc = kvpr::launch_token_gemm_flags(x_new, w->wqkv, w->bqkv, c->q32, dkv + (size_t)seq * kr, b, 3 * h, h, h,
                                                           2 * (int64_t)h, 0, c->compute, c->tok_ws, c->tok_ws_bytes, nullptr,
-                                                          with_projection)) {
+                                                          with_projection, norm)) {
             return rc;
         }
         // a compressed store receives the new rows packed (Sec. 4.4); attention below still reads the exact row
@@ -912,25 +907,34 @@ extern "C" int kvpr_timing_read(kvpr_ctx* c, int slot, kvpr_layer_timing* timing
 
 namespace {
 
-// the parts of a decoder layer around the attention block (xn = normalised input of the attention block)
-int pre_attention_norm(kvpr_ctx* c, const kvpr_layer_weights* w, const half* hid_in, half* xn) {
-    const int b = c->d.batch, h = c->d.hidden;
-    if (c->llama) return kvpr::launch_rmsnorm(hid_in, w->ln1_g, xn, b, h, c->compute);
-    return kvpr::launch_layernorm(hid_in, w->ln1_g, w->ln1_b, xn, b, h, c->compute);
-}
+// The parts of a decoder layer around the attention block.
+
+// Its norm (xn = normalised input of the attention block) goes along with the projection, if it can, else in front of the layer.
+struct BlockNorm {
+    kvpr::TokenNorm norm;
+    const kvpr::TokenNorm* along = nullptr;
+    int begin(kvpr_ctx* c, const kvpr_layer_weights* w, const half* hid_in, half* xn) {
+        const int b = c->d.batch, h = c->d.hidden;
+        norm = {hid_in, w->ln1_g, c->llama ? nullptr : w->ln1_b, xn, true};
+        if (!kvpr::norm_goes_along(norm, b, 3 * h, h)) return kvpr::launch_norm(norm, b, h, c->compute);
+        along = &norm;
+        return KVPR_OK;
+    }
+};
 
 // hid_out = r + FFN(norm(r)), r = c->resid.  OPT: LayerNorm, ReLU FFN with biases (Eq. 4);
 // LLaMA: RMSNorm, down(silu(gate) * up) with w1 = [gate; up] stacked
 int ffn_block(kvpr_ctx* c, const kvpr_layer_weights* w, half* hid_out) {
     const int b = c->d.batch, h = c->d.hidden, f = c->d.ffn_dim;
+    const kvpr::TokenNorm norm{c->resid, w->ln2_g, c->llama ? nullptr : w->ln2_b, c->xf, false};
     if (c->llama) {
         half* prod = c->ffn1 + (size_t)b * 2 * f;
-        if (int rc = kvpr::launch_rmsnorm(c->resid, w->ln2_g, c->xf, b, h, c->compute)) return rc;
-        if (int rc = kvpr::launch_token_gemm_gated(c->xf, w->w1, c->ffn1, prod, b, f, h, c->compute, c->tok_ws, c->tok_ws_bytes)) return rc;
+        if (int rc = kvpr::launch_token_gemm_gated(c->xf, w->w1, c->ffn1, prod, b, f, h, c->compute, c->tok_ws, c->tok_ws_bytes, &norm)) return rc;
         return kvpr::launch_token_gemm_flags(prod, w->w2, nullptr, nullptr, hid_out, b, h, f, 0, h, 0, c->compute, c->tok_ws, c->tok_ws_bytes, c->resid);
     } else {
-        if (int rc = kvpr::launch_layernorm(c->resid, w->ln2_g, w->ln2_b, c->xf, b, h, c->compute)) return rc;
-        if (int rc = kvpr::launch_token_gemm_flags(c->xf, w->w1, w->b1, nullptr, c->ffn1, b, f, h, 0, f, 1, c->compute, c->tok_ws, c->tok_ws_bytes)) return rc;
+        if (int rc = kvpr::launch_token_gemm_flags(c->xf, w->w1, w->b1, nullptr, c->ffn1, b, f, h, 0, f, 1, c->compute, c->tok_ws, c->tok_ws_bytes,
+                                                   nullptr, kvpr::CopyJob(), &norm))
+            return rc;
         return kvpr::launch_token_gemm_flags(c->ffn1, w->w2, w->b2, nullptr, hid_out, b, h, f, 0, h, 0, c->compute, c->tok_ws, c->tok_ws_bytes, c->resid);
     }
 }
@@ -986,9 +990,10 @@ extern "C" int kvpr_decode_step(kvpr_ctx* c, int seq, const kvpr_layer_weights* 
         // pre-norm -> attention block -> residual -> norm -> FFN -> residual
         // the store-back of layer i reads this row until the attention of layer i + 1 has started
         half* xn = c->xn[i & 1];
-        if (int rc = pre_attention_norm(c, w, hid_in, xn)) return rc;
+        BlockNorm norm;
+        if (int rc = norm.begin(c, w, hid_in, xn)) return rc;
         if (int rc = enqueue_layer(c, i, seq, ls[i], w, xn, c->resid, i % c->nbuf, per_layer ? &c->tev[i] : nullptr, false, nullptr,
-                                   hid_in, true))
+                                   hid_in, true, norm.along))
             return rc;
         if (int rc = ffn_block(c, w, hid_out)) return rc;
         hid_in = hid_out;
@@ -1124,9 +1129,10 @@ extern "C" int kvpr_decode_step_columns(kvpr_ctx* c, int seq, const void* x_in_d
             // the norm's parameters arrive with [Wk;Wv]: neither the norm nor the recomputation that follows it
             // waits for Wq, Wo and the FFN matrices, which may still be on the link (Sec. 3.3 fine-grained MHA pipeline)
             KVPR_HIP(hipStreamWaitEvent(c->compute, c->weight_pipeline ? c->ev_wkv[wb] : c->ev_wall[wb], 0));
-            if (int rc = pre_attention_norm(c, &w, hid_in, c->xn[0])) return rc;
+            BlockNorm norm;
+            if (int rc = norm.begin(c, &w, hid_in, c->xn[0])) return rc;
             if (int rc = enqueue_layer(c, slot, seq, ls[slot], &w, c->xn[0], c->resid, slot % c->nbuf,
-                                       per_slot ? &c->tev[slot] : nullptr, false, &wf, hid_in))
+                                       per_slot ? &c->tev[slot] : nullptr, false, &wf, hid_in, false, norm.along))
                 return rc;
             if (int rc = ffn_block(c, &w, hid_out)) return rc;
             if (c->hid_offload) {

@@ -5,6 +5,7 @@
 namespace kvpr {
 
 bool takes_few_tokens(int M, int N, int K);   // launch_few_tokens is the kernel for this product
+bool few_tokens_norm(int M, int N, int K);    // ... and takes a norm in front of it along
 
 // y[M, N] = x[M, K] . W[N, K]^T + bias, K a multiple of 128: the first out_f32_cols features as float32 to y32
 // [M, out_f32_cols], the others as float16 to y16 (row stride ld16), with a residual laid out as y16 added if there is one
@@ -15,9 +16,20 @@ struct FewTokens {
     const _Float16* res;
     int64_t ld16;
     int M, N, K, out_f32_cols, relu;
+    // norm: x goes through LayerNorm (1) or RMSNorm (2) first, gains and offsets of K halfs; the normalised rows also go to xn if
+    // it is not null
+    int norm = 0;
+    const _Float16 *norm_g = nullptr, *norm_b = nullptr;
+    _Float16* xn = nullptr;
+    // rotary form: (cos, sin) of the rows' position, head_dim / 2 pairs
+    const float2* rope = nullptr;
+    int head_dim = 0;
 };
 
-// gated: W is [gate; up] of N / 2 features each (a multiple of 4), y16 [M, N / 2] = silu(x gate^T) * (x up^T); nothing else applies
-int launch_few_tokens(const FewTokens& a, bool gated, hipStream_t st, const CopyJob& beside = CopyJob());
+// Plain.  Gated: W is [gate; up] of N / 2 features each (a multiple of 4), y16 [M, N / 2] = silu(x gate^T) * (x up^T), no bias,
+// residual or ReLU.  Rotary: W is [q; k; v] of N / 3 features each, in heads of head_dim; q and k are rotated, q goes to y32.
+enum class FewForm { plain, gated, rotary };
+
+int launch_few_tokens(const FewTokens& a, FewForm form, hipStream_t st, const CopyJob& beside = CopyJob());
 
 }  // namespace kvpr

@@ -51,12 +51,17 @@ __device__ __forceinline__ float fold16(float a, float b) {
 }
 
 // MQ: tokens in fours.  P: pieces of K that a wave holds at a time (every wave has P or P - 1 of them in every segment).
-// A unit is 4 output features, or with PAIR 2 x 4: the gate and the up rows of 4 features of a gated FFN.
-template <int MQ, int P, bool PAIR, int WAVES>
+// A unit is 4 output features, or 2 x 4: the gate and the up rows of 4 features of a gated FFN, or 4 features of a head and
+// their rotary partners.
+// NORM: the rows of x are normalised in registers, where all of them are (one segment), while the first rows of W are on
+// their way.  A norm of its own was a launch of 4.5 us with a round trip through memory in front of each of a layer's two
+// wide products, the rotation one of 5 us behind the first (one token through 4 layers of hidden 4096, batch 1: 692 -> 658 us; 3
+// rotary layers, batch 3: 504 -> 482).
+template <int MQ, int P, FewForm FORM, int WAVES, bool NORM>
 __global__ __launch_bounds__(WAVES * 64) void few_tokens(const FewTokens a, int units, int segments, int grid, const CopyJob beside) {
     // rows four at a time: enough of them that a wave has at least four loads in flight behind the ones it works on
     constexpr int R = P == 1 ? 4 : P == 2 ? 2 : 1;
-    constexpr int PER_UNIT = PAIR ? 2 : 1;
+    constexpr int PER_UNIT = FORM == FewForm::plain ? 1 : 2;
     if ((int)blockIdx.x >= grid) {                            // copies that go along
         run_copy_job(beside, blockIdx.x - grid);
         return;
@@ -68,8 +73,14 @@ __global__ __launch_bounds__(WAVES * 64) void few_tokens(const FewTokens a, int 
     const int steps = (groups + R - 1) / R;
     auto row_of = [&](int g) {                                // first W row of this workgroup's group g
         const int unit = blockIdx.x + g / PER_UNIT * grid;
-        return unit * 4 + (PAIR && (g & 1) ? a.N / 2 : 0);
+        if constexpr (FORM == FewForm::gated) return unit * 4 + (g & 1) * (a.N / 2);
+        if constexpr (FORM == FewForm::rotary) {
+            const int per_head = a.head_dim / 8;
+            return unit / per_head * a.head_dim + unit % per_head * 4 + (g & 1) * (a.head_dim / 2);
+        }
+        return unit * 4;
     };
+    __shared__ float stats[2][WAVES][MQ * 4];                 // sums over a wave's columns, then of squared deviations
     const int pieces = a.K / PIECE, run0 = pieces * wave / WAVES, run = pieces * (wave + 1) / WAVES - run0;
 
     for (int s = 0; s < segments; ++s) {
@@ -78,6 +89,11 @@ __global__ __launch_bounds__(WAVES * 64) void few_tokens(const FewTokens a, int 
         auto walk = [&](auto count) {
             constexpr int CNT = decltype(count)::value;
             if constexpr (CNT == 0) {                         // fewer pieces than waves: K < 1024
+                if constexpr (NORM) {
+                    if (lane < MQ * 4) stats[0][wave][lane] = stats[1][wave][lane] = 0.f;
+                    if (a.norm == 1) __syncthreads();
+                    __syncthreads();
+                }
                 for (int i = lane; i < groups * MQ * 16; i += 64) red[i * WAVES + wave] = 0.f;
             } else {
                 half8 xf[MQ][CNT];
@@ -86,6 +102,14 @@ __global__ __launch_bounds__(WAVES * 64) void few_tokens(const FewTokens a, int 
 #pragma unroll
                     for (int u = 0; u < CNT; ++u)
                         xf[q][u] = *reinterpret_cast<const half8*>(a.x + (int64_t)min(q * 4 + r4, a.M - 1) * a.K + k0 + u * PIECE);
+                half8 gv[NORM ? CNT : 1], bv[NORM ? CNT : 1];
+                if constexpr (NORM) {
+#pragma unroll
+                    for (int u = 0; u < CNT; ++u) {
+                        gv[u] = *reinterpret_cast<const half8*>(a.norm_g + k0 + u * PIECE);
+                        bv[u] = a.norm == 1 ? *reinterpret_cast<const half8*>(a.norm_b + k0 + u * PIECE) : half8{};
+                    }
+                }
                 struct Rows { half8 w[R][CNT]; };
                 auto load = [&](Rows& f, int st) {            // beyond the last group or row: the last one again, not stored
 #pragma unroll
@@ -124,9 +148,85 @@ __global__ __launch_bounds__(WAVES * 64) void few_tokens(const FewTokens a, int 
                         }
                     }
                 };
+                // two groups of rows are on their way at any time; with a norm both from the start, since it takes as long as the
+                // first two take to be read (with one the product of 12288 x 4096 took 20 us behind it, with two 18.5)
                 Rows f0, f1;
                 load(f0, 0);
+                if constexpr (NORM) load(f1, 1);
+                if constexpr (NORM) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    // f(token quad, element) summed over a token's row
+                    auto row_sum = [&](int pass, float (&out)[MQ], auto&& f) {
+#pragma unroll
+                        for (int q = 0; q < MQ; ++q) {
+                            float v = 0.f;
+#pragma unroll
+                            for (int u = 0; u < CNT; ++u)
+#pragma unroll
+                                for (int e = 0; e < 8; ++e) v += f(q, (float)xf[q][u][e]);
+                            v += rotate_row<0x124>(v);
+                            v += rotate_row<0x128>(v);
+                            v += __shfl_xor(v, 16);
+                            v += __shfl_xor(v, 32);
+                            if (lane < 4) stats[pass][wave][q * 4 + lane] = v;
+                        }
+                        __syncthreads();
+#pragma unroll
+                        for (int q = 0; q < MQ; ++q) {
+                            out[q] = 0.f;
+#pragma unroll
+                            for (int w = 0; w < WAVES; ++w) out[q] += stats[pass][w][q * 4 + r4];
+                        }
+                    };
+                    float mean[MQ], var[MQ];
+#pragma unroll
+                    for (int q = 0; q < MQ; ++q) mean[q] = 0.f;
+                    if (a.norm == 1) {
+                        row_sum(0, mean, [](int, float v) { return v; });
+#pragma unroll
+                        for (int q = 0; q < MQ; ++q) mean[q] /= a.K;
+                    }
+                    row_sum(1, var, [&](int q, float v) { return (v - mean[q]) * (v - mean[q]); });
+#pragma unroll
+                    for (int q = 0; q < MQ; ++q) {
+                        const float rstd = rsqrtf(var[q] / a.K + 1e-5f);
+#pragma unroll
+                        for (int u = 0; u < CNT; ++u) {
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) {
+                                const float t = ((float)xf[q][u][e] - mean[q]) * rstd * (float)gv[u][e];
+                                xf[q][u][e] = (_Float16)(a.norm == 1 ? t + (float)bv[u][e] : t);
+                            }
+                            if (a.xn && blockIdx.x == 0 && q * 4 + r4 < a.M)
+                                *reinterpret_cast<half8*>(a.xn + (int64_t)(q * 4 + r4) * a.K + k0 + u * PIECE) = xf[q][u];
+                        }
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
                 int st = 0;
+                if constexpr (NORM) {
+                    for (; st + 3 < steps; st += 2) {
+                        multiply(f0, st);
+                        __builtin_amdgcn_sched_barrier(0);
+                        load(f0, st + 2);
+                        __builtin_amdgcn_sched_barrier(0);
+                        multiply(f1, st + 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                        load(f1, st + 3);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    multiply(f0, st);
+                    if (st + 2 < steps) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        load(f0, st + 2);
+                        __builtin_amdgcn_sched_barrier(0);
+                        multiply(f1, st + 1);
+                        multiply(f0, st + 2);
+                    } else if (st + 1 < steps) {
+                        multiply(f1, st + 1);
+                    }
+                    return;
+                }
                 for (; st + 2 < steps; st += 2) {
                     load(f1, st + 1);
                     __builtin_amdgcn_sched_barrier(0);
@@ -164,10 +264,30 @@ __global__ __launch_bounds__(WAVES * 64) void few_tokens(const FewTokens a, int 
     };
     for (int t = threadIdx.x; t < groups / PER_UNIT * MQ * 16; t += WAVES * 64) {
         const int m = (t >> 4) % MQ * 4 + (t & 3), unit = (t >> 4) / MQ, i = t & 15;
-        const int n = (blockIdx.x + unit * grid) * 4 + (i >> 2);
+        const int n = row_of(unit * PER_UNIT) + (i >> 2);
         if (m >= a.M) continue;
         const int at = (unit * PER_UNIT * MQ + (t >> 4) % MQ) * 16 + i;
-        if constexpr (PAIR) {
+        if constexpr (FORM == FewForm::rotary) {
+            const int h = a.N / 3, n2 = n + a.head_dim / 2;
+            float v1 = sum(at), v2 = sum(at + MQ * 16);
+            if (a.bias) {
+                v1 += (float)a.bias[n];
+                v2 += (float)a.bias[n2];
+            }
+            if (n < 2 * h) {
+                const float2 cs = a.rope[n % a.head_dim];
+                const float r1 = v1 * cs.x - v2 * cs.y, r2 = v2 * cs.x + v1 * cs.y;
+                v1 = r1;
+                v2 = r2;
+            }
+            if (n < h) {
+                a.y32[(int64_t)m * h + n] = v1;
+                a.y32[(int64_t)m * h + n2] = v2;
+            } else {
+                a.y16[(int64_t)m * a.ld16 + n - h] = (_Float16)v1;
+                a.y16[(int64_t)m * a.ld16 + n2 - h] = (_Float16)v2;
+            }
+        } else if constexpr (FORM == FewForm::gated) {
             // both rounded to float16, as a product stored in between would have them
             const float gate = (float)(_Float16)sum(at), up = (float)(_Float16)sum(at + MQ * 16);
             a.y16[(int64_t)m * a.ld16 + n] = (_Float16)silu_mul(gate, up);
@@ -189,24 +309,26 @@ __global__ __launch_bounds__(WAVES * 64) void few_tokens(const FewTokens a, int 
     }
 }
 
-template <int MQ, int P, bool PAIR, int WAVES>
+template <int MQ, int P, FewForm FORM, int WAVES>
 int launch(const FewTokens& a, int segments, hipStream_t st, const CopyJob& beside) {
-    const int units = PAIR ? a.N / 8 : (a.N + 3) / 4;
-    constexpr int per_unit = (PAIR ? 2 : 1) * MQ * 16 * WAVES * (int)sizeof(float), room = 64 * 1024;
+    const int units = FORM == FewForm::plain ? (a.N + 3) / 4 : a.N / 8;
+    constexpr int per_unit = (FORM == FewForm::plain ? 1 : 2) * MQ * 16 * WAVES * (int)sizeof(float), room = 64 * 1024;
     // one workgroup per compute unit, more where the sums of one would take more than 64 KiB of LDS
     const int cus = compute_units(), rounds = ((units + cus - 1) / cus * per_unit + room - 1) / room;
     const int grid = std::min(units, cus * rounds), lds = (units + grid - 1) / grid * per_unit;
-    hipLaunchKernelGGL((few_tokens<MQ, P, PAIR, WAVES>), dim3((unsigned)(grid + beside.blocks)), dim3(WAVES * 64), lds, st, a, units, segments,
-                       grid, beside);
+    auto kern = few_tokens<MQ, P, FORM, WAVES, false>;
+    if constexpr (WAVES == 8)
+        if (a.norm) kern = few_tokens<MQ, P, FORM, WAVES, true>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(grid + beside.blocks)), dim3(WAVES * 64), lds, st, a, units, segments, grid, beside);
     KVPR_HIP(hipGetLastError());
     return KVPR_OK;
 }
 
-template <int MQ, bool PAIR, int WAVES, int P>
+template <int MQ, FewForm FORM, int WAVES, int P>
 int launch_pieces(const FewTokens& a, int p, int segments, hipStream_t st, const CopyJob& beside) {
     if constexpr (P > 1)
-        if (p < P) return launch_pieces<MQ, PAIR, WAVES, P - 1>(a, p, segments, st, beside);
-    return launch<MQ, P, PAIR, WAVES>(a, segments, st, beside);
+        if (p < P) return launch_pieces<MQ, FORM, WAVES, P - 1>(a, p, segments, st, beside);
+    return launch<MQ, P, FORM, WAVES>(a, segments, st, beside);
 }
 
 // Waves and pieces.  A wave has 128 registers for its part of x and for two groups of rows: 8 pieces with up to 4 tokens,
@@ -215,13 +337,13 @@ int launch_pieces(const FewTokens& a, int p, int segments, hipStream_t st, const
 // 19.3 us, K = 20480: 37.1 against 38.0).  Where K is a multiple of 16384 the runs of 8 waves are multiples of 4 KiB apart and
 // crowd the same channels: 4 waves, of 7 pieces at a time (4096 x 16384, M = 1 / 3 / 8: 24.7 / 25.7 / 29.3 -> 23.3 / 23.3 / 27.1
 // us; elsewhere they are up to 3 % slower).
-template <int MQ, bool PAIR>
+template <int MQ, FewForm FORM>
 int launch_split(const FewTokens& a, hipStream_t st, const CopyJob& beside) {
     auto go = [&](auto waves, auto held, int most) {
         constexpr int W = decltype(waves)::value, P = decltype(held)::value;
         const int longest = (a.K / PIECE + W - 1) / W;
         const int segments = longest <= P ? 1 : (longest + most - 1) / most;
-        return launch_pieces<MQ, PAIR, W, P>(a, (longest + segments - 1) / segments, segments, st, beside);
+        return launch_pieces<MQ, FORM, W, P>(a, (longest + segments - 1) / segments, segments, st, beside);
     };
     if (a.K % 16384 == 0) return go(std::integral_constant<int, 4>{}, std::integral_constant<int, 7>{}, 7);
     if constexpr (MQ == 1) return go(std::integral_constant<int, 8>{}, std::integral_constant<int, 8>{}, 8);
@@ -240,9 +362,19 @@ bool takes_few_tokens(int M, int N, int K) {
     return M <= 6 || K <= 7168 || N > 16 * compute_units();
 }
 
-int launch_few_tokens(const FewTokens& a, bool gated, hipStream_t st, const CopyJob& beside) {
-    if (a.M <= 4) return gated ? launch_split<1, true>(a, st, beside) : launch_split<1, false>(a, st, beside);
-    return gated ? launch_split<2, true>(a, st, beside) : launch_split<2, false>(a, st, beside);
+// x has to be in registers whole: one segment (see launch_split)
+bool few_tokens_norm(int M, int N, int K) { return takes_few_tokens(M, N, K) && K <= (M <= 4 ? 8192 : 7168); }
+
+int launch_few_tokens(const FewTokens& a, FewForm form, hipStream_t st, const CopyJob& beside) {
+    auto go = [&](auto f) {
+        constexpr FewForm F = decltype(f)::value;
+        return a.M <= 4 ? launch_split<1, F>(a, st, beside) : launch_split<2, F>(a, st, beside);
+    };
+    switch (form) {
+        case FewForm::gated: return go(std::integral_constant<FewForm, FewForm::gated>{});
+        case FewForm::rotary: return go(std::integral_constant<FewForm, FewForm::rotary>{});
+        default: return go(std::integral_constant<FewForm, FewForm::plain>{});
+    }
 }
 
 }  // namespace kvpr

@@ -458,18 +458,44 @@ int launch_mt(const void* x, const void* w, const void* bias, void* y32, void* y
     return launch_t<MT, 1>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, res, st);
 }
 
+// the norm goes into the kernel for few rows
+void take_along(FewTokens& a, const TokenNorm& n) {
+    a.norm = n.b ? 1 : 2;
+    a.x = (const _Float16*)n.x;
+    a.norm_g = (const _Float16*)n.g;
+    a.norm_b = (const _Float16*)n.b;
+    a.xn = n.keep ? (_Float16*)n.xn : nullptr;
+}
+
 }  // namespace
+
+int launch_norm(const TokenNorm& n, int rows, int h, hipStream_t st) {
+    return n.b ? launch_layernorm(n.x, n.g, n.b, n.xn, rows, h, st) : launch_rmsnorm(n.x, n.g, n.xn, rows, h, st);
+}
+
+// (16-byte loads: a caller's rows and gains may start anywhere)
+bool norm_goes_along(const TokenNorm& n, int M, int N, int K) {
+    return few_tokens_norm(M, N, K) && !token_gemm_forced() && (((uintptr_t)n.x | (uintptr_t)n.g | (uintptr_t)n.b) & 15) == 0;
+}
 
 // flags bit 0: ReLU.  residual (optional): float16, laid out as y16, added to the float16 outputs.  ws (optional, device):
 // workspace that lets a narrow output split K over several workgroups; its first 4096 bytes must be zero before the first
 // launch that uses it and are zero again when a launch ends; launches that share a workspace must not overlap.
 int launch_token_gemm_flags(const void* x, const void* w, const void* bias, void* y32, void* y16, int M, int N, int K,
                             int out_f32_cols, int64_t ld16, int flags, hipStream_t st, void* ws, size_t ws_bytes,
-                            const void* residual, const CopyJob& beside) {
+                            const void* residual, const CopyJob& beside, const TokenNorm* norm) {
     const int relu = flags & 1;
-    if (takes_few_tokens(M, N, K) && !token_gemm_forced())
-        return launch_few_tokens({(const _Float16*)x, (const _Float16*)w, (const _Float16*)bias, (float*)y32, (_Float16*)y16,
-                                  (const _Float16*)residual, ld16, M, N, K, out_f32_cols, relu}, false, st, beside);
+    if (norm && !norm_goes_along(*norm, M, N, K)) {
+        if (int rc = launch_norm(*norm, M, K, st)) return rc;
+        x = norm->xn;
+        norm = nullptr;
+    }
+    if (takes_few_tokens(M, N, K) && !token_gemm_forced()) {
+        FewTokens a{(const _Float16*)x, (const _Float16*)w, (const _Float16*)bias, (float*)y32, (_Float16*)y16,
+                    (const _Float16*)residual, ld16, M, N, K, out_f32_cols, relu};
+        if (norm) take_along(a, *norm);
+        return launch_few_tokens(a, FewForm::plain, st, beside);
+    }
     if (int rc = launch_copy(beside, kCopyThreads, st)) return rc;
     if (ws_bytes <= TOKEN_WS_TICKET_BYTES) ws = nullptr;
     if (M <= 16) return launch_mt<1>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ws, ws_bytes, residual, st);
@@ -478,14 +504,48 @@ int launch_token_gemm_flags(const void* x, const void* w, const void* bias, void
     return launch_mt<4>(x, w, bias, y32, y16, M, N, K, out_f32_cols, ld16, relu, ws, ws_bytes, residual, st);
 }
 
-// y[M, f] = silu(x Wg^T) * (x Wu^T), w = [Wg; Wu] of [2f, K], for f a multiple of 64.  One launch where the wide kernel takes
-// the product of 2f features in blocks of 128 anyway (the same 144 workgroups): the separate product of both halves was a
-// launch of 4.8 us and a round trip of 3 M f halfs (token through 3 rotary layers of hidden 4096, batch 3: 570 -> 557 us).
+// The decode token's q, k and v of a rotary model: w = [Wq; Wk; Wv] of [3h, h]; q and k are rotated by position `pos`, q goes to
+// q32 [M, h], k and v to kv16 [M, 2h] (a row of the cache).  One launch where the kernel for few rows takes the product; else q and k
+// go through qk32 [M, 2h].
+int launch_token_qkv_rope(const void* x, const void* w, const void* bias, void* qk32, void* q32, void* kv16, int M, int h, int head_dim,
+                          const void* table, int pos, hipStream_t st, void* ws, size_t ws_bytes, const CopyJob& beside,
+                          const TokenNorm* norm) {
+    if (norm && !norm_goes_along(*norm, M, 3 * h, h)) {
+        if (int rc = launch_norm(*norm, M, h, st)) return rc;
+        x = norm->xn;
+        norm = nullptr;
+    }
+    if (takes_few_tokens(M, 3 * h, h) && !token_gemm_forced()) {
+        FewTokens a{(const _Float16*)x, (const _Float16*)w, (const _Float16*)bias, (float*)q32, (_Float16*)kv16, nullptr, 2 * (int64_t)h,
+                    M, 3 * h, h, h, 0};
+        a.rope = (const float2*)table + (size_t)pos * (head_dim / 2);
+        a.head_dim = head_dim;
+        if (norm) take_along(a, *norm);
+        return launch_few_tokens(a, FewForm::rotary, st, beside);
+    }
+    // q and k stay float32 until they are rotated; v goes straight into the cache row
+    if (int rc = launch_token_gemm_flags(x, w, bias, qk32, (_Float16*)kv16 + h, M, 3 * h, h, 2 * h, 2 * (int64_t)h, 0, st, ws, ws_bytes,
+                                         nullptr, beside, norm))
+        return rc;
+    return launch_rope_token(qk32, table, pos, M, h, head_dim, q32, kv16, 2 * (int64_t)h, st);
+}
+
+// y[M, f] = silu(x Wg^T) * (x Wu^T), w = [Wg; Wu] of [2f, K], for f a multiple of 64.  One launch for few rows, and where the wide
+// kernel takes the product of 2f features in blocks of 128 anyway (the same 144 workgroups): the separate product of both halves
+// was a launch of 4.8 us and a round trip of 3 M f halfs (token through 3 rotary layers of hidden 4096, batch 3: 570 -> 557 us).
 // Below that, and while a kernel choice is forced, the halves go through `mid` [M, 2f].
 int launch_token_gemm_gated(const void* x, const void* w, void* mid, void* y, int M, int f, int K, hipStream_t st, void* ws,
-                            size_t ws_bytes) {
-    if (takes_few_tokens(M, 2 * f, K) && !token_gemm_forced())
-        return launch_few_tokens({(const _Float16*)x, (const _Float16*)w, nullptr, nullptr, (_Float16*)y, nullptr, f, M, 2 * f, K, 0, 0}, true, st);
+                            size_t ws_bytes, const TokenNorm* norm) {
+    if (norm && !norm_goes_along(*norm, M, 2 * f, K)) {
+        if (int rc = launch_norm(*norm, M, K, st)) return rc;
+        x = norm->xn;
+        norm = nullptr;
+    }
+    if (takes_few_tokens(M, 2 * f, K) && !token_gemm_forced()) {
+        FewTokens a{(const _Float16*)x, (const _Float16*)w, nullptr, nullptr, (_Float16*)y, nullptr, f, M, 2 * f, K, 0, 0};
+        if (norm) take_along(a, *norm);
+        return launch_few_tokens(a, FewForm::gated, st);
+    }
     if (f % 64 || K % WIDE_KB || f / 64 < 144 || token_gemm_forced()) {
         if (int rc = launch_token_gemm_flags(x, w, nullptr, nullptr, mid, M, 2 * f, K, 0, 2 * (int64_t)f, 0, st, ws, ws_bytes)) return rc;
         return launch_silu_mul(mid, y, M, f, st);

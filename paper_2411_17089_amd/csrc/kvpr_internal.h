@@ -31,11 +31,24 @@ int launch_attention(const void* q, const void* kv, void* z, void* ws, int S, in
 size_t attention_workspace_bytes(int batch, int hidden, int n_heads, int S);
 int launch_attention_mixed(const void* q, const void* kv16, const void* kvq, void* z, void* ws, int S, int split, int batch,
                            int hidden, int n_heads, int phase, hipStream_t st, const CopyJob& beside = CopyJob());
+// A norm in front of a token GEMM, which then reads xn = norm(x) instead of its x: LayerNorm with offsets b, RMSNorm without.
+// keep: the normalised rows are needed in xn afterwards.
+struct TokenNorm {
+    const void *x, *g, *b;
+    void* xn;
+    bool keep;
+};
+bool norm_goes_along(const TokenNorm& n, int M, int N, int K);     // in the product's own launch; else in one in front of it
+int launch_norm(const TokenNorm& n, int rows, int h, hipStream_t st);
 int launch_token_gemm_flags(const void* x, const void* w, const void* bias, void* y32, void* y16, int M, int N,
                             int K, int out_f32_cols, int64_t ld16, int flags /*bit0: ReLU*/, hipStream_t st,
-                            void* ws = nullptr, size_t ws_bytes = 0, const void* residual = nullptr, const CopyJob& beside = CopyJob());
+                            void* ws = nullptr, size_t ws_bytes = 0, const void* residual = nullptr, const CopyJob& beside = CopyJob(),
+                            const TokenNorm* norm = nullptr);
+int launch_token_qkv_rope(const void* x, const void* w, const void* bias, void* qk32, void* q32, void* kv16, int M, int h, int head_dim,
+                          const void* table, int pos, hipStream_t st, void* ws, size_t ws_bytes, const CopyJob& beside = CopyJob(),
+                          const TokenNorm* norm = nullptr);
 int launch_token_gemm_gated(const void* x, const void* w, void* mid, void* y, int M, int f, int K, hipStream_t st, void* ws,
-                            size_t ws_bytes);
+                            size_t ws_bytes, const TokenNorm* norm = nullptr);
 size_t token_gemm_workspace_bytes(int M, int N);
 int launch_fill_u16(void* p, size_t n_halfs, uint16_t pattern, hipStream_t st);
 int launch_fill_random(void* p, size_t n_halfs, float scale, uint32_t seed, hipStream_t st);

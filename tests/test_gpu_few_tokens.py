@@ -1,12 +1,15 @@
-"""Token GEMM for at most 8 rows: K in fewer pieces than waves, in even and uneven runs, in several segments and in runs of
+"""Token GEMM for at most 8 rows, with the norm in front and the rotation behind: K in fewer pieces than waves, in even and uneven runs, in several segments and in runs of
 4 KiB; outputs that are no multiple of 4, fewer than 4, and more than one workgroup's sums can hold."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 import kvpr_inputs
 from oracle import kvpr_llama_oracle as lo
-from kvpr_testlib import dev, rel_err
+from oracle import kvpr_oracle as ko
+from kvpr_testlib import dev, rel_err, upload_layer
 from test_gpu_llama import _lib_arrays, _llama_params
 
 pytestmark = pytest.mark.gpu
@@ -61,3 +64,44 @@ def test_gated_decoder_layer(k, b, ffn):
         assert rel_err(out.cpu().numpy(), want) <= 5e-3
     finally:
         k.kvpr_destroy(ctx)
+
+
+# hidden 256: waves without columns; 1152: runs of 1 and 2 pieces; 2176: 2 and 3.  9 rows: the norm is a launch of its own
+@pytest.mark.parametrize("h,H", [(256, 4), (1152, 9), (2176, 17)])
+@pytest.mark.parametrize("b", [1, 4, 5, 8, 9])
+@pytest.mark.parametrize("arch", ["opt", "llama"])
+def test_norm_and_rotation_in_the_projection(k, arch, h, H, b):
+    print(f"norm along arch={arch} h={h} b={b}", flush=True)
+    s, ffn, llama = 7, 384, arch == "llama"
+    if llama:
+        P = _llama_params(70 + b, b, h, H, ffn)
+        layer = dict(P, X=kvpr_inputs._draw(np.random.default_rng(b), (s, b, h), 1.0))
+        stored, d = lo.stored_kv(layer, "fp16"), {n: dev(a) for n, a in _lib_arrays(P).items()}
+    else:
+        layer = dict(kvpr_inputs.make_layer(70 + b, b, s, h, H), **kvpr_inputs.make_ffn(70 + b, h, ffn))
+        up = upload_layer(layer)
+        stored, d = ko.stored_kv(layer, "fp16"), {n: up[n] for n in ("wqkv", "bqkv", "wo", "bo", "ln1_g", "ln1_b", "w1", "b1", "w2", "b2", "ln2_g", "ln2_b")}
+    x = kvpr_inputs._draw(np.random.default_rng(h), (b, h), 1.0)
+    want = (lo if llama else ko).decoder_stack_decode([layer], x, [3], [stored])[0]
+    shifted = torch.empty((b * h + 1,), dtype=torch.float16, device="cuda")      # rows that start off a 16-byte boundary
+    shifted[1:] = dev(x).view(-1)
+    for x_in in (dev(x), shifted[1:].view(b, h)):
+        ctx = k.kvpr_create(1, h, H, h // H, ffn, b, s + 2, arch=k.KVPR_ARCH_LLAMA if llama else k.KVPR_ARCH_OPT)
+        try:
+            k.kvpr_store_write(ctx, 0, 0, s, np.ascontiguousarray(layer["X"]), stored.astype(np.float16))
+            outs = []
+            for timing in (False, True):
+                out = torch.empty((b, h), dtype=torch.float16, device="cuda")
+                k.kvpr_decode_step(ctx, s, [k.make_weights(**d)], x_in, out, [3], timing=timing)
+                torch.cuda.synchronize()
+                outs.append(out.cpu().numpy())
+            assert np.array_equal(outs[0], outs[1])
+            assert rel_err(outs[0], want) <= 5e-3                                # the bound of the stack tests
+            # the row that goes to the store: norm and rotation, one rounding each (3e-3, 5e-3 as in the stack tests)
+            xp, kvp = k.kvpr_store_ptrs(ctx, 0)
+            view = lambda p, n: np.ctypeslib.as_array(ctypes.cast(p, ctypes.POINTER(ctypes.c_uint16)), ((s + 1) * n,)).view(np.float16).reshape(s + 1, n)   # noqa: E731
+            trace = (lo if llama else ko).decoder_stack_decode([layer], x, [3], [stored])[1][0]
+            assert rel_err(view(xp, b * h)[s], np.asarray(trace["xn"]).reshape(-1)) <= 3e-3
+            assert rel_err(view(kvp, b * 2 * h)[s], np.asarray(trace["kv_new"]).reshape(-1)) <= 5e-3
+        finally:
+            k.kvpr_destroy(ctx)
