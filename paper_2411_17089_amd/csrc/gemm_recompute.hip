@@ -101,14 +101,18 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bias_f16(
 
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
 
-    const int pid = blockIdx.x;
-    // behind the tiles: copies that go along.  (An instantiation of its own: the branch in all of them costs the large product
-    // 1.6 %, 3690 -> 3750 us at M = 24576, N = 14336, K = 7168.)
-    if constexpr (BESIDE)
-        if (pid >= tiles_per_xcd * 8) {
-            run_copy_job(beside, pid - tiles_per_xcd * 8);
+    int pid = blockIdx.x;
+    // In front of the tiles: copies that go along, in a multiple of 8 workgroups, which leaves the tiles on their XCDs.  (An
+    // instantiation of its own: the branch in all of them costs the large product 1.6 %, 3690 -> 3750 us at M = 24576, N = 14336,
+    // K = 7168.)
+    if constexpr (BESIDE) {
+        const int front = (beside.blocks + 7) / 8 * 8;
+        if (pid < front) {
+            if (pid < beside.blocks) run_copy_job(beside, pid);
             return;
         }
+        pid -= front;
+    }
     int tile_m, tile_n;
     if (xcd_split_n) {
         const int xcd = pid & 7, i = pid >> 3;
@@ -396,7 +400,7 @@ int launch_tile(const void* a, const void* w, const void* bias, void* c, int64_t
     const int xcd_split_n = band_mapping(N, K) ? 1 : 0;
     const int max_width = (tiles_n + 7) / 8;
     const int tiles_per_xcd = xcd_split_n ? max_width * tiles_m : (int)((total + 7) / 8);
-    const unsigned grid = (unsigned)(tiles_per_xcd * 8 + beside.blocks);
+    const unsigned grid = (unsigned)(tiles_per_xcd * 8 + (beside.blocks + 7) / 8 * 8);
     static_assert(WM * WN * 64 == kCopyThreads, "copies are cut for workgroups of this size");
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WM * WN * 64), lds_bytes, st, (const _Float16*)a, (const _Float16*)w,
                        (const _Float16*)bias, (_Float16*)c, M, N, K, ldc, tiles_m, tiles_n, tiles_per_xcd, xcd_split_n, rope, beside);

@@ -63,6 +63,16 @@ extern "C" int kvpr_store_ptrs(kvpr_ctx* c, int layer, void** x_host, void** kv_
     return KVPR_OK;
 }
 
+constexpr double kPrefillFirst = 1.5 * (1 << 20);     // bytes of activations of the first run, at least
+constexpr int kPrefillRuns = 24;
+// Above this many bytes of rows the helper stays one copy, one product, one copy.  The memory of a context that was destroyed
+// before is given back in the background for some 20 ms, and copies by the DMA engines meanwhile run at 30 instead of 57 GB/s (with
+// or without this helper; not if the old contexts are kept or 0.1 s pass).  Small contexts are done with that at once: in 24
+// contexts one after the other one of the first three decodes was slow in 0 - 2 either way up to 128 MiB of rows.  With 256 MiB it was
+// in 7 with runs and in 1 without, because the slow helper covers that time: what the runs gain there (30.4 -> 20.5 ms for 1024
+// positions, batch 32, hidden 7168) a program that makes one large context after the other would lose in the decodes that follow.
+constexpr size_t kPrefillInRuns = size_t(96) << 20;
+
 extern "C" int kvpr_store_prefill_kv(kvpr_ctx* c, int layer, int seq, const kvpr_layer_weights* w) {
     if (!c) return fail(KVPR_E_INVAL, "ctx is null");
     if (layer < 0 || layer >= c->slots()) return fail(KVPR_E_RANGE, "layer %d outside [0, %d)", layer, c->slots());
@@ -70,30 +80,55 @@ extern "C" int kvpr_store_prefill_kv(kvpr_ctx* c, int layer, int seq, const kvpr
     if (int rc = check_weights(c, w, false)) return rc;
     if (c->x_rows[layer] < seq) return fail(KVPR_E_STATE, "layer %d: only %d activation rows written", layer, c->x_rows[layer]);
     if (seq == 0) return KVPR_OK;
-    const int h = c->d.hidden;
-    const size_t xsb = c->x_store_bytes(), ksb = c->kv_store_bytes();
+    const int h = c->d.hidden, b = c->d.batch;
+    const size_t xr = c->x_row_halfs(), kr = c->kv_row_halfs(), xsb = c->x_store_bytes(), ksb = c->kv_store_bytes();
     KVPR_HIP(hipDeviceSynchronize());
-    // One copy in, one product, one copy out, all on the compute stream.  Cut into runs of positions on several streams the
-    // three overlap (512 positions, batch 8, hidden 4096: 2.00 -> 1.54 ms; 1024, batch 32, hidden 7168: 30.5 -> 19.2).  But in
-    // a quarter to a half of fresh contexts the host-to-device copies of the one to three decodes that followed then ran at
-    // 30 instead of 57 GB/s, with no kernel beside them (layer of that size 14.1 - 19.5 ms instead of 10.7), and the helper
-    // itself took up to twice as long (300 positions, batch 2, hidden 4096: 0.33 -> 0.57).  With activations coming in on the
-    // store stream and rows going out on this one the decodes were spared, but the helper still ran at one of two speeds,
-    // by context (768 positions, batch 4, hidden 4096 as 4 runs: 1.3 or 2.7 ms, as one: 1.5).
-    // the activations as the store returns them (dequantised if it keeps them packed)
-    KVPR_HIP(hipMemcpyAsync(c->qx ? (void*)c->dxq[0] : (void*)c->dx[0], c->hx[layer], (size_t)seq * xsb, hipMemcpyHostToDevice, c->compute));
-    if (c->qx)
-        if (int rc = kvpr::launch_dequant_int4(c->dxq[0], c->dx[0], (int64_t)seq * c->d.batch, h, c->compute)) return rc;
+    char *x_stage = c->qx ? c->dxq[0] : (char*)c->dx[0], *kv_stage = c->qkv ? c->dkvq[0] : (char*)c->dkv[0];
     const half* wkv = (const half*)w->wqkv + (size_t)h * h;
     const half* bkv = w->bqkv ? (const half*)w->bqkv + h : nullptr;
-    if (int rc = c->llama ? kvpr::launch_gemm_rope(c->dx[0], wkv, bkv, c->dkv[0], (int64_t)seq * c->d.batch, 2 * h, h, 2 * (int64_t)h,
-                                                   c->rope_tab, h, c->d.head_dim, c->d.batch, 0, c->compute)
-                          : kvpr::launch_gemm(c->dx[0], wkv, bkv, c->dkv[0], (int64_t)seq * c->d.batch, 2 * h, h, 2 * (int64_t)h, c->compute))
-        return rc;
-    if (c->qkv)
-        if (int rc = kvpr::launch_quant_int4(c->dkv[0], c->dkvq[0], (int64_t)seq * c->d.batch, 2 * h, c->compute)) return rc;
-    KVPR_HIP(hipMemcpyAsync(c->hkv[layer], c->qkv ? (const void*)c->dkvq[0] : (const void*)c->dkv[0], (size_t)seq * ksb,
-                            hipMemcpyDeviceToHost, c->compute));
+    // positions [p0, p1): the activations as the store returns them (dequantised if it keeps them packed), their rows as it takes them
+    auto rows_of = [&](int p0, int p1, const kvpr::CopyJob& beside) -> int {
+        const int64_t rows = (int64_t)(p1 - p0) * b;
+        half *x = c->dx[0] + p0 * xr, *kv = c->dkv[0] + p0 * kr;
+        if (c->qx)
+            if (int rc = kvpr::launch_dequant_int4(x_stage + p0 * xsb, x, rows, h, c->compute)) return rc;
+        if (int rc = c->llama ? kvpr::launch_gemm_rope(x, wkv, bkv, kv, rows, 2 * h, h, 2 * (int64_t)h, c->rope_tab, h, c->d.head_dim, b, p0,
+                                                       c->compute, beside)
+                              : kvpr::launch_gemm(x, wkv, bkv, kv, rows, 2 * h, h, 2 * (int64_t)h, c->compute, beside))
+            return rc;
+        return c->qkv ? kvpr::launch_quant_int4(kv, kv_stage + p0 * ksb, rows, 2 * h, c->compute) : KVPR_OK;
+    };
+    if ((size_t)seq * ksb > kPrefillInRuns) {
+        KVPR_HIP(hipMemcpyAsync(x_stage, c->hx[layer], (size_t)seq * xsb, hipMemcpyHostToDevice, c->compute));
+        if (int rc = rows_of(0, seq, kvpr::CopyJob())) return rc;
+        KVPR_HIP(hipMemcpyAsync(c->hkv[layer], kv_stage, (size_t)seq * ksb, hipMemcpyDeviceToHost, c->compute));
+    } else {
+        // Runs of positions, in order: beside the product of one run the activations of the next come in and the rows of the one
+        // before go out, by workgroups of the same launch.  The link carries both directions at once and the product hides
+        // under them.  Every launch costs the link about 20 us of start and end, and nothing goes out before the first two runs
+        // are in: the first is small and each is 1.4 times as long as the one before, for which the activations of one run
+        // take as long to come in as the rows two runs before it to go out.  512 positions, batch 8, hidden 4096: 2.00 ms one
+        // after the other, 1.80 in 16 equal runs, 1.58 in these.
+        int runs = 1;
+        while (runs < kPrefillRuns && (double)seq * xsb * (std::sqrt(2.0) - 1.0) >= kPrefillFirst * (std::pow(2.0, 0.5 * (runs + 1)) - 1.0)) ++runs;
+        auto bound = [&](int r) {
+            return r >= runs ? seq : (int)(seq * (std::pow(2.0, 0.5 * r) - 1.0) / (std::pow(2.0, 0.5 * runs) - 1.0));
+        };
+        // the activations of run `in` and the rows of run `out` (none outside [0, runs))
+        auto copies = [&](int in, int out) {
+            const size_t i0 = bound(in), i1 = bound(in + 1), o0 = out < 0 ? 0 : bound(out), o1 = out < 0 ? 0 : bound(out + 1);
+            return kvpr::copy_both_ways(c->hx[layer] + i0 * xsb, x_stage + i0 * xsb, (i1 - i0) * xsb,
+                                        kv_stage + o0 * ksb, c->hkv[layer] + o0 * ksb, (o1 - o0) * ksb);
+        };
+        if (int rc = kvpr::launch_copy(copies(0, -1), kvpr::kCopyThreads, c->compute)) return rc;
+        for (int r = 0; r < runs; ++r)
+            if (int rc = rows_of(bound(r), bound(r + 1), copies(r + 1, r - 1))) return rc;
+        const size_t last = bound(runs - 1);
+        if (int rc = kvpr::launch_copy(kvpr::copy_job(kvpr::kCopyThreads, kv_stage + last * ksb, c->hkv[layer] + last * ksb, (seq - last) * ksb,
+                                                      nullptr, nullptr, 0, 16),
+                                       kvpr::kCopyThreads, c->compute))
+            return rc;
+    }
     KVPR_HIP(hipStreamSynchronize(c->compute));
     c->kv_rows[layer] = std::max(c->kv_rows[layer], seq);
     return KVPR_OK;
