@@ -60,16 +60,18 @@ __device__ __forceinline__ void copy_along(const CopyJob& job, int z) {
     if (block < job.blocks) run_copy_job(job, block);
 }
 
-template <int D, int UNROLL, int ATT_WAVES>
+// BESIDE: an instantiation of its own, since looking for copies costs a launch of 6 - 8 us 0.1 - 0.2
+template <int D, int UNROLL, int ATT_WAVES, bool BESIDE>
 __global__ __launch_bounds__(ATT_WAVES * 64) void attention_partial(
     const float* __restrict__ q, const _Float16* __restrict__ kv, float* __restrict__ ws_acc,
     float* __restrict__ ws_ml, _Float16* __restrict__ z, int S, int batch, int h, int chunk, int splits,
     float scale_log2, const CopyJob beside) {
     const int cg = blockIdx.x, n = blockIdx.y, sp = blockIdx.z;
-    if (sp >= splits) {                           // behind the splits: copies that go along
-        copy_along(beside, sp - splits);
-        return;
-    }
+    if constexpr (BESIDE)
+        if (sp >= splits) {                       // behind the splits: copies that go along
+            copy_along(beside, sp - splits);
+            return;
+        }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col = cg * COLS_PER_GROUP + lane * 8;
     const bool active = col < h;
@@ -265,16 +267,17 @@ __device__ __forceinline__ bool merge_waves(float (*sm)[10][64], int wave, int l
 
 // Positions pos0 .. pos0 + n_pos - 1, then extra_pos if it is >= 0, rows of kv16 [*, batch, 2h] float16.  Writes partial
 // slot split_base + blockIdx.z, or (fuse_slot >= 0) merges the partial in that slot and writes z.
-template <int D, int UNROLL, int ATT_WAVES>
+template <int D, int UNROLL, int ATT_WAVES, bool BESIDE>
 __global__ __launch_bounds__(ATT_WAVES * 64) void attention_partial_ranged(
     const float* __restrict__ q, const _Float16* __restrict__ kv16,
     float* __restrict__ ws_acc, float* __restrict__ ws_ml, int pos0, int n_pos, int extra_pos, int batch, int h,
     int chunk, int splits, int split_base, float scale_log2, int fuse_slot, _Float16* __restrict__ z, const CopyJob beside) {
     const int cg = blockIdx.x, n = blockIdx.y, sp = blockIdx.z;
-    if (sp >= splits) {
-        copy_along(beside, sp - splits);
-        return;
-    }
+    if constexpr (BESIDE)
+        if (sp >= splits) {
+            copy_along(beside, sp - splits);
+            return;
+        }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col = cg * COLS_PER_GROUP + lane * 8;
     const bool active = col < h;
@@ -603,7 +606,7 @@ int launch_attention_plan(SplitPlan sp, const void* q, const void* kv, void* z, 
     const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)d));
     dim3 grid(groups, batch, sp.splits + layers_for(beside, groups, batch));
 #define KVPR_LAUNCH_PART(D_, U_, W_)                                                                                \
-    hipLaunchKernelGGL((attention_partial<D_, U_, W_>), grid, dim3(64 * W_), 0, st, (const float*)q, (const _Float16*)kv, \
+    hipLaunchKernelGGL((beside.blocks ? attention_partial<D_, U_, W_, true> : attention_partial<D_, U_, W_, false>), grid, dim3(64 * W_), 0, st, (const float*)q, (const _Float16*)kv, \
                        ws_acc, ws_ml, (_Float16*)z, S, batch, hidden, sp.chunk, sp.splits, scale_log2, beside)
     if (d == 128) {
         switch (cfg) {
@@ -660,14 +663,10 @@ int launch_ranged(const void* q, const void* kv16, float* ws_acc, float* ws_ml, 
     const int groups = (hidden + COLS_PER_GROUP - 1) / COLS_PER_GROUP;
     const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)d));
     dim3 grid(groups, batch, sp.splits + layers_for(beside, groups, batch));
-    if (d == 128)
-        hipLaunchKernelGGL((attention_partial_ranged<128, 8, 4>), grid, dim3(256), 0, st, (const float*)q,
-                           (const _Float16*)kv16, ws_acc, ws_ml, pos0, n_pos, extra_pos, batch, hidden,
-                           sp.chunk, sp.splits, split_base, scale_log2, fuse_slot, (_Float16*)z, beside);
-    else
-        hipLaunchKernelGGL((attention_partial_ranged<64, 8, 4>), grid, dim3(256), 0, st, (const float*)q,
-                           (const _Float16*)kv16, ws_acc, ws_ml, pos0, n_pos, extra_pos, batch, hidden,
-                           sp.chunk, sp.splits, split_base, scale_log2, fuse_slot, (_Float16*)z, beside);
+    auto kern = d == 128 ? (beside.blocks ? attention_partial_ranged<128, 8, 4, true> : attention_partial_ranged<128, 8, 4, false>)
+                         : (beside.blocks ? attention_partial_ranged<64, 8, 4, true> : attention_partial_ranged<64, 8, 4, false>);
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, (const float*)q, (const _Float16*)kv16, ws_acc, ws_ml, pos0, n_pos, extra_pos, batch, hidden,
+                       sp.chunk, sp.splits, split_base, scale_log2, fuse_slot, (_Float16*)z, beside);
     KVPR_HIP(hipGetLastError());
     return KVPR_OK;
 }

@@ -57,15 +57,21 @@ __device__ __forceinline__ float fold16(float a, float b) {
 // their way.  A norm of its own was a launch of 4.5 us with a round trip through memory in front of each of a layer's two
 // wide products, the rotation one of 5 us behind the first (one token through 4 layers of hidden 4096, batch 1: 692 -> 658 us; 3
 // rotary layers, batch 3: 504 -> 482).
-template <int MQ, int P, FewForm FORM, int WAVES, bool NORM>
+// What comes with the product: nothing, the norm, or copies by extra workgroups (each an instantiation of its own: looking for
+// copies costs a launch of 7 us 0.2).
+enum class FewExtra { none, norm, copies };
+
+template <int MQ, int P, FewForm FORM, int WAVES, FewExtra EXTRA>
 __global__ __launch_bounds__(WAVES * 64) void few_tokens(const FewTokens a, int units, int segments, int grid, const CopyJob beside) {
     // rows four at a time: enough of them that a wave has at least four loads in flight behind the ones it works on
     constexpr int R = P == 1 ? 4 : P == 2 ? 2 : 1;
     constexpr int PER_UNIT = FORM == FewForm::plain ? 1 : 2;
-    if ((int)blockIdx.x >= grid) {                            // copies that go along
-        run_copy_job(beside, blockIdx.x - grid);
-        return;
-    }
+    constexpr bool NORM = EXTRA == FewExtra::norm;
+    if constexpr (EXTRA == FewExtra::copies)
+        if ((int)blockIdx.x >= grid) {
+            run_copy_job(beside, blockIdx.x - grid);
+            return;
+        }
     extern __shared__ float red[];                            // [group of 4 rows][quad of tokens][row][token][wave]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r4 = lane & 3, chunk = lane >> 2;
@@ -316,9 +322,12 @@ int launch(const FewTokens& a, int segments, hipStream_t st, const CopyJob& besi
     // one workgroup per compute unit, more where the sums of one would take more than 64 KiB of LDS
     const int cus = compute_units(), rounds = ((units + cus - 1) / cus * per_unit + room - 1) / room;
     const int grid = std::min(units, cus * rounds), lds = (units + grid - 1) / grid * per_unit;
-    auto kern = few_tokens<MQ, P, FORM, WAVES, false>;
-    if constexpr (WAVES == 8)
-        if (a.norm) kern = few_tokens<MQ, P, FORM, WAVES, true>;
+    auto kern = few_tokens<MQ, P, FORM, WAVES, FewExtra::none>;
+    if constexpr (WAVES == 8) {
+        if (a.norm) kern = few_tokens<MQ, P, FORM, WAVES, FewExtra::norm>;
+        if constexpr (FORM != FewForm::gated)
+            if (beside.blocks) kern = few_tokens<MQ, P, FORM, WAVES, FewExtra::copies>;
+    }
     hipLaunchKernelGGL(kern, dim3((unsigned)(grid + beside.blocks)), dim3(WAVES * 64), lds, st, a, units, segments, grid, beside);
     KVPR_HIP(hipGetLastError());
     return KVPR_OK;
@@ -365,7 +374,13 @@ bool takes_few_tokens(int M, int N, int K) {
 // x has to be in registers whole: one segment (see launch_split)
 bool few_tokens_norm(int M, int N, int K) { return takes_few_tokens(M, N, K) && K <= (M <= 4 ? 8192 : 7168); }
 
-int launch_few_tokens(const FewTokens& a, FewForm form, hipStream_t st, const CopyJob& beside) {
+int launch_few_tokens(const FewTokens& a, FewForm form, hipStream_t st, const CopyJob& job) {
+    // the copies are a launch of their own where no instantiation takes them: with a norm, in the gated form, with 4 waves
+    CopyJob beside = job;
+    if (a.norm || form == FewForm::gated || a.K % 16384 == 0) {
+        if (int rc = launch_copy(job, kCopyThreads, st)) return rc;
+        beside = CopyJob();
+    }
     auto go = [&](auto f) {
         constexpr FewForm F = decltype(f)::value;
         return a.M <= 4 ? launch_split<1, F>(a, st, beside) : launch_split<2, F>(a, st, beside);
