@@ -106,7 +106,7 @@ constexpr size_t kSmallCopy = size_t(1) << 20, kSmallCacheCopy = 2 * kSmallCopy;
 // so: up to 1 MiB always, up to 16 MiB while less overlap is lost than the copies' start-up costs behind that projection.  Over
 // hidden 768 - 7168, batch 1 - 10, 0.3 - 16 MiB and four splits (487 calls): 0.80 / 0.84 of the time on average, 1.05 at most.
 constexpr size_t kInOrderCopy = 16 * kSmallCopy;
-constexpr double kStartUp = 32e-6, kHidden = 0.45, kLinkRate = 55e9, kFewRate = 6.5e12, kWeightRate = 4.6e12;
+constexpr double kStartUp = 32e-6, kHidden = 0.45, kLinkRate = 57e9, kFewRate = 6.5e12, kWeightRate = 4.6e12;
 
 bool runs_in_order(const kvpr_ctx* c, int l, size_t x_bytes, size_t kv_bytes, bool beside_recompute) {
     if (!c->inline_store() || x_bytes + kv_bytes > kInOrderCopy) return false;
@@ -135,6 +135,30 @@ bool runs_ahead(const kvpr_ctx* c, int l) {
     if (c->d.n_layers < 2 || streamed < 128000000 || c->flops_per_pos() * l < 2000000000) return false;
     const int64_t rows = (int64_t)l * c->d.batch / std::min(c->chunks, std::max(1, l / 8));
     return kvpr::gemm_workgroups(rows, 2 * c->d.hidden) * 4 <= 3 * kvpr::compute_units();
+}
+
+// Single-layer call that is not timed, with copies by the DMA engine: parts that the activations come in by, so that the
+// recomputation of one runs while the next is on the link.  In one part it starts when all of them have landed, and where it and the
+// attention over its rows take longer than the rest of the cache, that is what the call waits for.  A part costs the link 16 us.
+// Of 1 to 8 parts those that leave least behind the last activations, the product by its estimate; after milliseconds of idle a
+// long one runs 15 % longer than that (clocks), one of a millisecond 3 %.  Hidden 7168, batch 32, 1024 positions, split 0.75 /
+// 0.85 / 1: 10.62 -> 10.49, 12.1 -> 9.7, 14.2 -> 9.3 ms; hidden 4096, packed store, 0.65 / 0.75 / 0.85: 2.13 -> 1.90, 2.39 -> 1.78,
+// 2.74 -> 1.88; where the cache takes longer, one part as before.
+// (kvpr_set_chunks asks for parts in every call, and the planner then knows of them; the clock keep-alive is meant for one.)
+int copy_parts(const kvpr_ctx* c, int l, size_t x_bytes, size_t kv_bytes) {
+    if (l == 0 || c->chunks > 1 || c->keep_warm > 0.0) return c->chunks;
+    const int64_t b = c->d.batch, h = c->d.hidden;
+    const double x = (double)x_bytes / kLinkRate, cache = (double)kv_bytes / kLinkRate, attention = 4.0 * h * b * l / 6.3e12;
+    int best = 1;
+    double least = 0.0;
+    for (int n = 1; n <= 8 && l / n >= 8; ++n) {
+        double part = kvpr::gemm_estimate_s((l + n - 1) / n * b, (int)(2 * h), (int)h);
+        part *= n * part > 3e-3 ? 1.15 : 1.03;
+        const double left = std::max(part, n * part - x * (n - 1) / n) + attention;
+        const double t = 16e-6 * (n - 1) + std::max(cache, left);
+        if (n == 1 || t < least) { least = t; best = n; }
+    }
+    return best;
 }
 
 int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weights* w, const half* x_new, half* out, int buf,
@@ -211,8 +235,10 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::c0], c->copy));
     // chunk boundaries: equal parts of [0, l) rounded down to multiples of 8 positions (whole GEMM tile rows
     // at batch 32); a single chunk is the paper's schedule
-    int nchunk = (l > 0) ? (small ? 1 : std::min(c->chunks, std::max(1, l / 8))) : 0;
+    const int parts = fence_copy_to_start && !ev && !wf ? copy_parts(c, l, x_bytes, kv_bytes) : c->chunks;
+    int nchunk = (l > 0) ? (small ? 1 : std::min(parts, std::max(1, l / 8))) : 0;
     int bound[kvpr_ctx::kMaxChunks + 1];
+    c->last_parts = nchunk;
     for (int j = 0; j <= nchunk; ++j) bound[j] = (j == nchunk) ? l : (int)((int64_t)l * j / nchunk) / 8 * 8;
     const void* rest_from = c->hkv[layer] + (size_t)l * ksb;
     void* rest_to = kv_stage + (size_t)l * ksb;
@@ -771,6 +797,8 @@ int create_impl(const kvpr_model_desc* d, int n_gpu_batches, void* compute_strea
 
 extern "C" int kvpr_debug_streams_replaced(void) { return g_streams_replaced; }
 extern "C" int64_t kvpr_debug_layers_ahead(kvpr_ctx* c) { return c->layers_ahead; }   // since the context was created
+
+extern "C" int kvpr_debug_copy_parts(kvpr_ctx* c) { return c->last_parts; }           // of the last layer that was enqueued
 
 extern "C" int kvpr_destroy(kvpr_ctx* c) {
     if (!c) return fail(KVPR_E_INVAL, "ctx is null");
