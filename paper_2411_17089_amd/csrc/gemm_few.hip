@@ -318,8 +318,8 @@ __global__ __launch_bounds__(WAVES * 64) void few_tokens(const FewTokens a, int 
 template <int MQ, int P, FewForm FORM, int WAVES>
 int launch(const FewTokens& a, int segments, hipStream_t st, const CopyJob& beside) {
     const int units = FORM == FewForm::plain ? (a.N + 3) / 4 : a.N / 8;
-    constexpr int per_unit = (FORM == FewForm::plain ? 1 : 2) * MQ * 16 * WAVES * (int)sizeof(float), room = 64 * 1024;
-    // one workgroup per compute unit, more where the sums of one would take more than 64 KiB of LDS
+    constexpr int per_unit = (FORM == FewForm::plain ? 1 : 2) * MQ * 16 * WAVES * (int)sizeof(float), room = 63 * 1024;   // the norm's sums lie beside
+    // one workgroup per compute unit, more where the sums of one would take more than 63 KiB of LDS
     const int cus = compute_units(), rounds = ((units + cus - 1) / cus * per_unit + room - 1) / room;
     const int grid = std::min(units, cus * rounds), lds = (units + grid - 1) / grid * per_unit;
     auto kern = few_tokens<MQ, P, FORM, WAVES, FewExtra::none>;

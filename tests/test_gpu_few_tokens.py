@@ -23,7 +23,7 @@ def k():
 
 @pytest.mark.parametrize("M", [1, 4, 5, 8])
 @pytest.mark.parametrize("N,K,f32", [(3, 128, 0), (520, 768, 8), (1301, 1152, 1024), (1026, 2048, 0), (64, 7168, 64), (260, 7296, 0),
-                                     (132, 8320, 4), (132, 11008, 0), (40, 16384, 8), (24, 32768, 0), (140000, 256, 0)])
+                                     (132, 8320, 4), (132, 11008, 0), (40, 16384, 8), (24, 32768, 0), (65536, 1024, 0), (140000, 256, 0)])
 def test_product(k, M, N, K, f32):
     print(f"few tokens M={M} N={N} K={K} f32={f32}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(M * 1000 + N)
@@ -45,7 +45,7 @@ def test_product(k, M, N, K, f32):
     assert bool(torch.isnan(y16[:, N - f32:]).all()), "columns beyond the last feature must not be written"
 
 
-@pytest.mark.parametrize("b,ffn", [(3, 128), (4, 384), (5, 1152), (8, 11008)])
+@pytest.mark.parametrize("b,ffn", [(3, 128), (4, 384), (5, 1152), (8, 11008), (8, 32768)])
 def test_gated_decoder_layer(k, b, ffn):
     s, h, H = 12, 256, 2
     P = _llama_params(300 + b, b, h, H, ffn)
