@@ -233,6 +233,8 @@ int kvpr_cost(const kvpr_profile_t* prof, int cost_model, int split, int batch, 
 /* Extension (not in the paper): the activation copy X[0:l] is cut into `chunks` equal parts
  * (1..32; 1 = the paper's schedule) and the recomputation of part j starts as soon as part j has
  * landed, while the later parts and then the cache are still on the link.  Results are unchanged.
+ * (With chunks = 1 and the clock keep-alive off, an untimed kvpr_layer_decode may use parts too, where it would
+ * otherwise wait for the recomputation; timed calls and the planner keep one.)
  * kvpr_cost_chunked / kvpr_plan_split_chunked are Eq. 10 / Eq. 11 for that schedule: with
  * t_act, t_kv, t_rc as in Eq. 10, part j's GEMM starts at max(j*t_act/chunks, end of part j-1)
  * and takes t_rc/chunks; t = max(end of the last GEMM, t_act + t_kv).  chunks = 1 gives Eq. 10. */

@@ -19,7 +19,7 @@ def k():
 
 @pytest.mark.parametrize("rotary", [False, True])
 @pytest.mark.parametrize("packed", [False, True])
-@pytest.mark.parametrize("b,s", [(3, 41), (64, 150), (61, 601), (64, 24), (64, 66), (1, 3000), (64, 1)])    # 1 to 6 runs
+@pytest.mark.parametrize("b,s", [(3, 41), (64, 150), (61, 601)])
 def test_rows_equal_one_product(k, b, s, packed, rotary):
     h, H = 512, 4
     rng = np.random.default_rng(s)
