@@ -315,30 +315,11 @@ __global__ __launch_bounds__(WAVES * 64) void few_tokens(const FewTokens a, int 
     }
 }
 
-template <int MQ, int P, FewForm FORM, int WAVES>
-int launch(const FewTokens& a, int segments, hipStream_t st, const CopyJob& beside) {
-    const int units = FORM == FewForm::plain ? (a.N + 3) / 4 : a.N / 8;
-    constexpr int per_unit = (FORM == FewForm::plain ? 1 : 2) * MQ * 16 * WAVES * (int)sizeof(float), room = 63 * 1024;   // the norm's sums lie beside
-    // one workgroup per compute unit, more where the sums of one would take more than 63 KiB of LDS
-    const int cus = compute_units(), rounds = ((units + cus - 1) / cus * per_unit + room - 1) / room;
-    const int grid = std::min(units, cus * rounds), lds = (units + grid - 1) / grid * per_unit;
-    auto kern = few_tokens<MQ, P, FORM, WAVES, FewExtra::none>;
-    if constexpr (WAVES == 8) {
-        if (a.norm) kern = few_tokens<MQ, P, FORM, WAVES, FewExtra::norm>;
-        if constexpr (FORM != FewForm::gated)
-            if (beside.blocks) kern = few_tokens<MQ, P, FORM, WAVES, FewExtra::copies>;
-    }
-    hipLaunchKernelGGL(kern, dim3((unsigned)(grid + beside.blocks)), dim3(WAVES * 64), lds, st, a, units, segments, grid, beside);
-    KVPR_HIP(hipGetLastError());
-    return KVPR_OK;
-}
-
-template <int MQ, FewForm FORM, int WAVES, int P>
-int launch_pieces(const FewTokens& a, int p, int segments, hipStream_t st, const CopyJob& beside) {
-    if constexpr (P > 1)
-        if (p < P) return launch_pieces<MQ, FORM, WAVES, P - 1>(a, p, segments, st, beside);
-    return launch<MQ, P, FORM, WAVES>(a, segments, st, beside);
-}
+// How a product is cut: waves and the pieces of K that each holds at a time, column segments, workgroups, bytes of LDS for the sums
+// of one of them.
+struct FewPlan {
+    int waves, pieces, segments, grid, lds;
+};
 
 // Waves and pieces.  A wave has 128 registers for its part of x and for two groups of rows: 8 pieces with up to 4 tokens,
 // 7 with up to 8.  One segment where that is enough (K = 7168, M = 8: 18.5 us against 18.9 in two), else with more than 4
@@ -346,17 +327,50 @@ int launch_pieces(const FewTokens& a, int p, int segments, hipStream_t st, const
 // 19.3 us, K = 20480: 37.1 against 38.0).  Where K is a multiple of 16384 the runs of 8 waves are multiples of 4 KiB apart and
 // crowd the same channels: 4 waves, of 7 pieces at a time (4096 x 16384, M = 1 / 3 / 8: 24.7 / 25.7 / 29.3 -> 23.3 / 23.3 / 27.1
 // us; elsewhere they are up to 3 % slower).
+// One workgroup per compute unit, each with whole units; more where the sums of one would take more than 63 KiB of LDS (64 KiB is
+// what a launch gets, and the norm's sums lie beside).
+FewPlan few_plan(int M, int N, int K, FewForm form, int cus) {
+    const bool quad = M <= 4;
+    FewPlan p;
+    p.waves = K % 16384 == 0 ? 4 : 8;
+    const int longest = (K / PIECE + p.waves - 1) / p.waves;
+    const int held = p.waves == 8 && quad ? 8 : 7, most = p.waves == 4 ? 7 : quad ? 8 : 4;
+    p.segments = longest <= held ? 1 : (longest + most - 1) / most;
+    p.pieces = (longest + p.segments - 1) / p.segments;
+    const int units = form == FewForm::plain ? (N + 3) / 4 : N / 8;
+    const int per_unit = (form == FewForm::plain ? 1 : 2) * (quad ? 1 : 2) * 16 * p.waves * (int)sizeof(float);
+    const int fit = 63 * 1024 / per_unit, rounds = ((units + cus - 1) / cus + fit - 1) / fit;
+    p.grid = std::min(units, cus * rounds);
+    p.lds = (units + p.grid - 1) / p.grid * per_unit;
+    return p;
+}
+
+template <int MQ, int P, FewForm FORM, int WAVES>
+int launch(const FewTokens& a, const FewPlan& p, hipStream_t st, const CopyJob& beside) {
+    const int units = FORM == FewForm::plain ? (a.N + 3) / 4 : a.N / 8;
+    auto kern = few_tokens<MQ, P, FORM, WAVES, FewExtra::none>;
+    if constexpr (WAVES == 8) {
+        if (a.norm) kern = few_tokens<MQ, P, FORM, WAVES, FewExtra::norm>;
+        if constexpr (FORM != FewForm::gated)
+            if (beside.blocks) kern = few_tokens<MQ, P, FORM, WAVES, FewExtra::copies>;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)(p.grid + beside.blocks)), dim3(WAVES * 64), p.lds, st, a, units, p.segments, p.grid, beside);
+    KVPR_HIP(hipGetLastError());
+    return KVPR_OK;
+}
+
+template <int MQ, FewForm FORM, int WAVES, int P>
+int launch_pieces(const FewTokens& a, const FewPlan& p, hipStream_t st, const CopyJob& beside) {
+    if constexpr (P > 1)
+        if (p.pieces < P) return launch_pieces<MQ, FORM, WAVES, P - 1>(a, p, st, beside);
+    return launch<MQ, P, FORM, WAVES>(a, p, st, beside);
+}
+
 template <int MQ, FewForm FORM>
-int launch_split(const FewTokens& a, hipStream_t st, const CopyJob& beside) {
-    auto go = [&](auto waves, auto held, int most) {
-        constexpr int W = decltype(waves)::value, P = decltype(held)::value;
-        const int longest = (a.K / PIECE + W - 1) / W;
-        const int segments = longest <= P ? 1 : (longest + most - 1) / most;
-        return launch_pieces<MQ, FORM, W, P>(a, (longest + segments - 1) / segments, segments, st, beside);
-    };
-    if (a.K % 16384 == 0) return go(std::integral_constant<int, 4>{}, std::integral_constant<int, 7>{}, 7);
-    if constexpr (MQ == 1) return go(std::integral_constant<int, 8>{}, std::integral_constant<int, 8>{}, 8);
-    else return go(std::integral_constant<int, 8>{}, std::integral_constant<int, 7>{}, 4);
+int launch_form(const FewTokens& a, hipStream_t st, const CopyJob& beside) {
+    const FewPlan p = few_plan(a.M, a.N, a.K, FORM, compute_units());
+    if (p.waves == 4) return launch_pieces<MQ, FORM, 4, 7>(a, p, st, beside);
+    return launch_pieces<MQ, FORM, 8, MQ == 1 ? 8 : 7>(a, p, st, beside);
 }
 
 }  // namespace
@@ -371,7 +385,7 @@ bool takes_few_tokens(int M, int N, int K) {
     return M <= 6 || K <= 7168 || N > 16 * compute_units();
 }
 
-// x has to be in registers whole: one segment (see launch_split)
+// x has to be in registers whole: one segment (see few_plan)
 bool few_tokens_norm(int M, int N, int K) { return takes_few_tokens(M, N, K) && K <= (M <= 4 ? 8192 : 7168); }
 
 int launch_few_tokens(const FewTokens& a, FewForm form, hipStream_t st, const CopyJob& job) {
@@ -383,7 +397,7 @@ int launch_few_tokens(const FewTokens& a, FewForm form, hipStream_t st, const Co
     }
     auto go = [&](auto f) {
         constexpr FewForm F = decltype(f)::value;
-        return a.M <= 4 ? launch_split<1, F>(a, st, beside) : launch_split<2, F>(a, st, beside);
+        return a.M <= 4 ? launch_form<1, F>(a, st, beside) : launch_form<2, F>(a, st, beside);
     };
     switch (form) {
         case FewForm::gated: return go(std::integral_constant<FewForm, FewForm::gated>{});
@@ -393,3 +407,15 @@ int launch_few_tokens(const FewTokens& a, FewForm form, hipStream_t st, const Co
 }
 
 }  // namespace kvpr
+
+// for tests: the cut of a product on a device of `cus` compute units; form 0 plain, 1 gated, 2 rotary
+extern "C" int kvpr_debug_few_plan(int M, int N, int K, int form, int cus, int32_t* waves, int32_t* pieces, int32_t* segments, int32_t* grid,
+                                   int32_t* lds) {
+    const kvpr::FewPlan p = kvpr::few_plan(M, N, K, (kvpr::FewForm)form, cus);
+    *waves = p.waves;
+    *pieces = p.pieces;
+    *segments = p.segments;
+    *grid = p.grid;
+    *lds = p.lds;
+    return KVPR_OK;
+}
