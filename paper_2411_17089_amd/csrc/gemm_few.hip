@@ -359,18 +359,18 @@ int launch(const FewTokens& a, const FewPlan& p, hipStream_t st, const CopyJob& 
     return KVPR_OK;
 }
 
-template <int MQ, FewForm FORM, int WAVES, int P>
+template <int MQ, FewForm FORM, int P>
 int launch_pieces(const FewTokens& a, const FewPlan& p, hipStream_t st, const CopyJob& beside) {
     if constexpr (P > 1)
-        if (p.pieces < P) return launch_pieces<MQ, FORM, WAVES, P - 1>(a, p, st, beside);
-    return launch<MQ, P, FORM, WAVES>(a, p, st, beside);
+        if (p.pieces < P) return launch_pieces<MQ, FORM, P - 1>(a, p, st, beside);
+    return launch<MQ, P, FORM, 8>(a, p, st, beside);
 }
 
 template <int MQ, FewForm FORM>
 int launch_form(const FewTokens& a, hipStream_t st, const CopyJob& beside) {
     const FewPlan p = few_plan(a.M, a.N, a.K, FORM, compute_units());
-    if (p.waves == 4) return launch_pieces<MQ, FORM, 4, 7>(a, p, st, beside);
-    return launch_pieces<MQ, FORM, 8, MQ == 1 ? 8 : 7>(a, p, st, beside);
+    if (p.waves == 4) return launch<MQ, 7, FORM, 4>(a, p, st, beside);     // 32 n pieces a wave, in ceil(32 n / 7) segments: always 7
+    return launch_pieces<MQ, FORM, MQ == 1 ? 8 : 7>(a, p, st, beside);
 }
 
 }  // namespace

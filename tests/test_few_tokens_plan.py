@@ -40,7 +40,7 @@ def test_pieces_cover_the_columns(plan, M):
     for K in range(128, 1 << 17, 128):
         waves, pieces, segments, _, _ = plan(M, 4096, K)
         assert waves == (4 if K % 16384 == 0 else 8)
-        assert 1 <= pieces <= (8 if M <= 4 and waves == 8 else 7)
+        assert 1 <= pieces <= (8 if M <= 4 else 7) if waves == 8 else pieces == 7      # the only kernel of 4 waves
         runs = [K // 128 * (w + 1) // waves - K // 128 * w // waves for w in range(waves)]
         for run in set(runs):                               # a wave walks a segment of `pieces` or one less
             parts = {run * (s + 1) // segments - run * s // segments for s in range(segments)}
