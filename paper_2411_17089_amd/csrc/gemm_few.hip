@@ -161,8 +161,19 @@ __global__ __launch_bounds__(WAVES * 64) void few_tokens(const FewTokens a, int 
                 if constexpr (NORM) load(f1, 1);
                 if constexpr (NORM) {
                     __builtin_amdgcn_sched_barrier(0);
+                    // Float copies of x kept from one pass over it to the next would be 8 registers a piece, 112 with 7 pieces of 8
+                    // tokens, and up to 67 of the 256 went to scratch (12 kernels, hidden 6144 and more).  Converted anew in
+                    // each pass nothing does: token through 2 layers of hidden 7168, M = 1 / 4 / 8: 582 / 647 / 810 -> 561 / 615
+                    // / 729 us (norm as a launch of its own 592 / 622 / 729); hidden 4096 and 5120 as before.
+                    auto forget = [&]() {
+#pragma unroll
+                        for (int q = 0; q < MQ; ++q)
+#pragma unroll
+                            for (int u = 0; u < CNT; ++u) asm volatile("" : "+v"(xf[q][u]));
+                    };
                     // f(token quad, element) summed over a token's row
                     auto row_sum = [&](int pass, float (&out)[MQ], auto&& f) {
+                        forget();
 #pragma unroll
                         for (int q = 0; q < MQ; ++q) {
                             float v = 0.f;
@@ -193,6 +204,7 @@ __global__ __launch_bounds__(WAVES * 64) void few_tokens(const FewTokens a, int 
                         for (int q = 0; q < MQ; ++q) mean[q] /= a.K;
                     }
                     row_sum(1, var, [&](int q, float v) { return (v - mean[q]) * (v - mean[q]); });
+                    forget();
 #pragma unroll
                     for (int q = 0; q < MQ; ++q) {
                         const float rstd = rsqrtf(var[q] / a.K + 1e-5f);
