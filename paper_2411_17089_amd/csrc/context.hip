@@ -115,7 +115,7 @@ bool runs_in_order(const kvpr_ctx* c, int l, size_t x_bytes, size_t kv_bytes, bo
     const int b = c->d.batch, h = c->d.hidden;
     double lost = 0.0;
     if (l > 0 && !beside_recompute) lost += std::min(kvpr::gemm_estimate_s((int64_t)l * b, 2 * h, h), (double)kv_bytes / kLinkRate);
-    if (!kvpr::takes_few_tokens(b, 3 * h, h)) lost += 4e-6 + 6.0 * h * h / kWeightRate;
+    if (!kvpr::few_tokens_along(b, 3 * h, h)) lost += 4e-6 + 6.0 * h * h / kWeightRate;
     return lost < kStartUp - kHidden * 6.0 * h * h / kFewRate;
 }
 
@@ -281,7 +281,7 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
                                                      c->rope_tab, seq, c->compute, c->tok_ws, c->tok_ws_bytes, with_projection, norm))
                 return rc;
         } else if (int rc = kvpr::launch_token_gemm_flags(x_new, w->wqkv, w->bqkv, c->q32, dkv + (size_t)seq * kr, b, 3 * h, h, h,
-                                                          2 * (int64_t)h, 0, c->compute, c->tok_ws, c->tok_ws_bytes, nullptr,
+                                                          2 * (int64_t)h, 2, c->compute, c->tok_ws, c->tok_ws_bytes, nullptr,
                                                           with_projection, norm)) {
             return rc;
         }

@@ -4,8 +4,9 @@
 
 namespace kvpr {
 
-bool takes_few_tokens(int M, int N, int K);   // launch_few_tokens is the kernel for this product
-bool few_tokens_norm(int M, int N, int K);    // ... and takes a norm in front of it along
+bool takes_few_tokens(int M, int N, int K);   // launch_few_tokens is the kernel for this product by itself
+bool few_tokens_along(int M, int N, int K);   // ... for this product with copies, the rotation or the gate along
+bool few_tokens_norm(int M, int N, int K);    // ... and with a norm in front
 
 // y[M, N] = x[M, K] . W[N, K]^T + bias, K a multiple of 128: the first out_f32_cols features as float32 to y32
 // [M, out_f32_cols], the others as float16 to y16 (row stride ld16), with a residual laid out as y16 added if there is one

@@ -391,14 +391,22 @@ int launch_form(const FewTokens& a, hipStream_t st, const CopyJob& beside) {
 // launch is all there is (2304 x 768, M = 8: 3.8 us there, 4.0 here), and 7 or 8 rows in several segments of few steps, whose
 // ends are not hidden (4096 x 11008, M = 8: 18.5 there, in slices of K, and 19.2 here; 4096 x 16384: 27.5 and 27.4; with 5 rows
 // 18.6 and 17.7; 5120 x 13824, five steps: 27.2 and 26.2).
-bool takes_few_tokens(int M, int N, int K) {
+bool few_tokens_along(int M, int N, int K) {
     if (M <= 4) return true;
     if (M > 8 || K < 1024) return false;
     return M <= 6 || K <= 7168 || N > 16 * compute_units();
 }
 
+// A product with nothing along: of less than 1024 columns, some waves have one piece of K or none, and the exchange of their sums is
+// longer than the read.  There / here, us, M = 1: 768 x 768 3.1 / 3.6, 2304 x 768 3.3 / 3.9, 6144 x 768 4.5 / 4.7, 9216 x 768 6.1 /
+// 5.8, 32768 x 768 12.1 / 11.1; 2304 x 256 2.7 / 3.4, 32768 x 256 6.4 / 7.4; 9216 x 640 5.7 / 5.4, 9216 x 512 5.0 / 5.1; of 1024
+// columns 2304 x 1024 5.6 / 4.1.  (A launch of its own for what goes along is 4 us.)
+bool takes_few_tokens(int M, int N, int K) {
+    return few_tokens_along(M, N, K) && (K >= 1024 || (K >= 640 && N > 32 * compute_units()));
+}
+
 // x has to be in registers whole: one segment (see few_plan)
-bool few_tokens_norm(int M, int N, int K) { return takes_few_tokens(M, N, K) && K <= (M <= 4 ? 8192 : 7168); }
+bool few_tokens_norm(int M, int N, int K) { return few_tokens_along(M, N, K) && K <= (M <= 4 ? 8192 : 7168); }
 
 int launch_few_tokens(const FewTokens& a, FewForm form, hipStream_t st, const CopyJob& job) {
     // the copies are a launch of their own where no instantiation takes them: with a norm, in the gated form, with 4 waves
@@ -419,6 +427,9 @@ int launch_few_tokens(const FewTokens& a, FewForm form, hipStream_t st, const Co
 }
 
 }  // namespace kvpr
+
+// for tests: whether the kernel takes a product with something along / alone
+extern "C" int kvpr_debug_few_tokens(int M, int N, int K, int alone) { return alone ? kvpr::takes_few_tokens(M, N, K) : kvpr::few_tokens_along(M, N, K); }
 
 // for tests: the cut of a product on a device of `cus` compute units; form 0 plain, 1 gated, 2 rotary
 extern "C" int kvpr_debug_few_plan(int M, int N, int K, int form, int cus, int32_t* waves, int32_t* pieces, int32_t* segments, int32_t* grid,

@@ -478,8 +478,8 @@ bool norm_goes_along(const TokenNorm& n, int M, int N, int K) {
     return few_tokens_norm(M, N, K) && !token_gemm_forced() && (((uintptr_t)n.x | (uintptr_t)n.g | (uintptr_t)n.b) & 15) == 0;
 }
 
-// flags bit 0: ReLU.  residual (optional): float16, laid out as y16, added to the float16 outputs.  ws (optional, device):
-// workspace that lets a narrow output split K over several workgroups; its first 4096 bytes must be zero before the first
+// flags bit 0: ReLU; bit 1: calls of this product may take something along, and the others shall give the same bits.
+// residual (optional): float16, laid out as y16, added to the float16 outputs.  ws (optional, device): workspace that lets a narrow output split K over several workgroups; its first 4096 bytes must be zero before the first
 // launch that uses it and are zero again when a launch ends; launches that share a workspace must not overlap.
 int launch_token_gemm_flags(const void* x, const void* w, const void* bias, void* y32, void* y16, int M, int N, int K,
                             int out_f32_cols, int64_t ld16, int flags, hipStream_t st, void* ws, size_t ws_bytes,
@@ -490,7 +490,8 @@ int launch_token_gemm_flags(const void* x, const void* w, const void* bias, void
         x = norm->xn;
         norm = nullptr;
     }
-    if (takes_few_tokens(M, N, K) && !token_gemm_forced()) {
+    const bool along = norm || beside.blocks || (flags & 2);
+    if ((along ? few_tokens_along(M, N, K) : takes_few_tokens(M, N, K)) && !token_gemm_forced()) {
         FewTokens a{(const _Float16*)x, (const _Float16*)w, (const _Float16*)bias, (float*)y32, (_Float16*)y16,
                     (const _Float16*)residual, ld16, M, N, K, out_f32_cols, relu};
         if (norm) take_along(a, *norm);
@@ -515,7 +516,7 @@ int launch_token_qkv_rope(const void* x, const void* w, const void* bias, void* 
         x = norm->xn;
         norm = nullptr;
     }
-    if (takes_few_tokens(M, 3 * h, h) && !token_gemm_forced()) {
+    if (few_tokens_along(M, 3 * h, h) && !token_gemm_forced()) {
         FewTokens a{(const _Float16*)x, (const _Float16*)w, (const _Float16*)bias, (float*)q32, (_Float16*)kv16, nullptr, 2 * (int64_t)h,
                     M, 3 * h, h, h, 0};
         a.rope = (const float2*)table + (size_t)pos * (head_dim / 2);
@@ -541,7 +542,7 @@ int launch_token_gemm_gated(const void* x, const void* w, void* mid, void* y, in
         x = norm->xn;
         norm = nullptr;
     }
-    if (takes_few_tokens(M, 2 * f, K) && !token_gemm_forced()) {
+    if (few_tokens_along(M, 2 * f, K) && !token_gemm_forced()) {
         FewTokens a{(const _Float16*)x, (const _Float16*)w, nullptr, nullptr, (_Float16*)y, nullptr, f, M, 2 * f, K, 0, 0};
         if (norm) take_along(a, *norm);
         return launch_few_tokens(a, FewForm::gated, st);

@@ -45,3 +45,13 @@ def test_pieces_cover_the_columns(plan, M):
         for run in set(runs):                               # a wave walks a segment of `pieces` or one less
             parts = {run * (s + 1) // segments - run * s // segments for s in range(segments)}
             assert parts <= {pieces, pieces - 1}, (K, run, parts)
+
+
+@pytest.mark.parametrize("M,N,K,along,alone", [
+    (1, 2304, 768, 1, 0), (4, 768, 768, 1, 0), (4, 8192, 768, 1, 0), (4, 8256, 768, 1, 1), (1, 50272, 640, 1, 1), (1, 50272, 512, 1, 0),
+    (1, 768, 1024, 1, 1), (4, 128, 128, 1, 0), (5, 2304, 768, 0, 0), (5, 50272, 896, 0, 0), (5, 2304, 1024, 1, 1),
+    (6, 4096, 11008, 1, 1), (7, 4096, 11008, 0, 0), (8, 4104, 11008, 1, 1), (8, 4096, 7168, 1, 1), (9, 12288, 4096, 0, 0)])
+def test_rule(plan, M, N, K, along, alone):
+    """With something along it saves a launch; alone it has to be the faster kernel."""
+    import paper_2411_17089_amd as k
+    assert (k.lib.kvpr_debug_few_tokens(M, N, K, 0), k.lib.kvpr_debug_few_tokens(M, N, K, 1)) == (along, alone)

@@ -45,6 +45,13 @@ def test_product(k, M, N, K, f32):
     assert bool(torch.isnan(y16[:, N - f32:]).all()), "columns beyond the last feature must not be written"
 
 
+@pytest.mark.parametrize("N,K", [(8192, 768), (8256, 768), (8300, 640), (8256, 512), (2304, 896)])
+def test_product_of_few_columns(k, N, K):
+    """Both sides of the rule for a product of less than 1024 columns."""
+    for M in (1, 4):
+        test_product(k, M, N, K, 8)
+
+
 @pytest.mark.parametrize("b,ffn", [(3, 128), (4, 384), (5, 1152), (8, 11008), (8, 32768)])
 def test_gated_decoder_layer(k, b, ffn):
     s, h, H = 12, 256, 2
