@@ -283,8 +283,18 @@ int launch_copy(const CopyJob& job, int threads, hipStream_t st) {
     return KVPR_OK;
 }
 
+// At most 64 workgroups of 256 lanes, 256 KiB on the way: more of them only crowd the link (single-layer calls in a row / waited
+// for, cache alone, 512 / 256 / 64 workgroups: hidden 4096, batch 10, 1.6 MiB 85 / 80 / 77 and 108 / 103 / 95 us; hidden 768, batch 8,
+// 1.4 MiB 76 / 72 / 68 and 86 / 82 / 80).
+constexpr int kCopyBytesThreads = 256, kCopyBytesBlocks = 64;
+
 int launch_copy_bytes(const void* src, void* dst, size_t bytes, hipStream_t st, const void* src2, void* dst2, size_t bytes2) {
-    return launch_copy(copy_job(256, src, dst, bytes, src2, dst2, bytes2, 512), 256, st);
+    return launch_copy(copy_job(kCopyBytesThreads, src, dst, bytes, src2, dst2, bytes2, kCopyBytesBlocks), kCopyBytesThreads, st);
 }
 
 }  // namespace kvpr
+
+// for tests: workgroups of launch_copy_bytes
+extern "C" int kvpr_debug_copy_workgroups(size_t bytes, size_t bytes2) {
+    return kvpr::copy_job(kvpr::kCopyBytesThreads, nullptr, nullptr, bytes, nullptr, nullptr, bytes2, kvpr::kCopyBytesBlocks).blocks;
+}
