@@ -93,6 +93,7 @@ struct kvpr_ctx {
     // MFMA loop before it waits for the activations (0 = off)
     double keep_warm = 0.0;
     double wall_clock_hz = 0.0;
+    int prefill_runs = 0;                // runs of the last prefill helper (read by tests)
     int last_parts = 0;                  // parts that the last layer's activations came in by (read by tests)
     int64_t layers_ahead = 0;            // recomputations that ran beside the previous layer (read by tests)
     int cost_model = KVPR_COST_EQ10, granularity = 1;

@@ -68,10 +68,26 @@ constexpr int kPrefillRuns = 24;
 // Above this many bytes of rows the helper stays one copy, one product, one copy.  The memory of a context that was destroyed
 // before is given back in the background for some 20 ms, and copies by the DMA engines meanwhile run at 30 instead of 57 GB/s (with
 // or without this helper; not if the old contexts are kept or 0.1 s pass).  Small contexts are done with that at once: in 24
-// contexts one after the other one of the first three decodes was slow in 0 - 2 either way up to 128 MiB of rows.  With 256 MiB it was
-// in 7 with runs and in 1 without, because the slow helper covers that time: what the runs gain there (30.4 -> 20.5 ms for 1024
-// positions, batch 32, hidden 7168) a program that makes one large context after the other would lose in the decodes that follow.
+// contexts one after the other one of the first three decodes was slow in 0 - 2 either way up to 128 MiB of rows; the line is drawn
+// below that.  With 256 MiB it was in 7 with runs and in 1 without, because the slow helper covers that time: what the runs gain there
+// (30.4 -> 20.5 ms for 1024 positions, batch 32, hidden 7168) a program that makes one large context after the other would lose in the
+// decodes that follow.
 constexpr size_t kPrefillInRuns = size_t(96) << 20;
+
+// Positions go in runs whose copies are workgroups of the products' launches (0: one DMA copy in, one product, one DMA copy out).  A
+// kernel's copies save the engines' start, some 14 us, but rows go out at 45 - 50 instead of 57 GB/s, so runs have to gain that back:
+// by what lies beside them, the product and the other direction.  One run has nothing beside its copies: better up to 3 MiB of rows.
+// A narrow product hides little: with float16 rows, one after the other / in runs, hidden 256 9 MiB 289 / 320 us, 35 MiB 1022 / 1027;
+// hidden 768 9 MiB 296 / 322, 14 MiB 444 / 468, 25 MiB 750 / 753, 32 MiB 955 / 931; hidden 1024 15 MiB 463 / 474, 45 MiB 1309 / 1176;
+// hidden 2048 7 MiB 249 / 246, 14 MiB 442 / 401.  Packed rows are few, and their codec is beside nothing in either form: 0.8 - 1.01 of the time.
+static int prefill_runs(int seq, int hidden, size_t x_row_bytes, size_t kv_row_bytes, bool packed_rows) {
+    const size_t x = seq * x_row_bytes, kv = seq * kv_row_bytes, least = size_t(3) << 20, mib = size_t(1) << 20;
+    if (kv > kPrefillInRuns) return 0;
+    int runs = 1;
+    while (runs < kPrefillRuns && (double)x * (std::sqrt(2.0) - 1.0) >= kPrefillFirst * (std::pow(2.0, 0.5 * (runs + 1)) - 1.0)) ++runs;
+    if (kv > least && (runs == 1 || (!packed_rows && kv + hidden * (mib / 60) < 40 * mib))) return 0;
+    return runs;
+}
 
 extern "C" int kvpr_store_prefill_kv(kvpr_ctx* c, int layer, int seq, const kvpr_layer_weights* w) {
     if (!c) return fail(KVPR_E_INVAL, "ctx is null");
@@ -98,7 +114,8 @@ extern "C" int kvpr_store_prefill_kv(kvpr_ctx* c, int layer, int seq, const kvpr
             return rc;
         return c->qkv ? kvpr::launch_quant_int4(kv, kv_stage + p0 * ksb, rows, 2 * h, c->compute) : KVPR_OK;
     };
-    if ((size_t)seq * ksb > kPrefillInRuns) {
+    const int runs = c->prefill_runs = prefill_runs(seq, h, xsb, ksb, c->qkv);
+    if (runs == 0) {
         KVPR_HIP(hipMemcpyAsync(x_stage, c->hx[layer], (size_t)seq * xsb, hipMemcpyHostToDevice, c->compute));
         if (int rc = rows_of(0, seq, kvpr::CopyJob())) return rc;
         KVPR_HIP(hipMemcpyAsync(c->hkv[layer], kv_stage, (size_t)seq * ksb, hipMemcpyDeviceToHost, c->compute));
@@ -109,8 +126,6 @@ extern "C" int kvpr_store_prefill_kv(kvpr_ctx* c, int layer, int seq, const kvpr
         // are in: the first is small and each is 1.4 times as long as the one before, for which the activations of one run
         // take as long to come in as the rows two runs before it to go out.  512 positions, batch 8, hidden 4096: 2.00 ms one
         // after the other, 1.80 in 16 equal runs, 1.58 in these.
-        int runs = 1;
-        while (runs < kPrefillRuns && (double)seq * xsb * (std::sqrt(2.0) - 1.0) >= kPrefillFirst * (std::pow(2.0, 0.5 * (runs + 1)) - 1.0)) ++runs;
         auto bound = [&](int r) {
             return r >= runs ? seq : (int)(seq * (std::pow(2.0, 0.5 * r) - 1.0) / (std::pow(2.0, 0.5 * runs) - 1.0));
         };
@@ -133,3 +148,9 @@ extern "C" int kvpr_store_prefill_kv(kvpr_ctx* c, int layer, int seq, const kvpr
     c->kv_rows[layer] = std::max(c->kv_rows[layer], seq);
     return KVPR_OK;
 }
+
+// for tests: the rule, and what the last call of a context took
+extern "C" int kvpr_debug_prefill_rule(int seq, int hidden, size_t x_row_bytes, size_t kv_row_bytes, int packed_rows) {
+    return prefill_runs(seq, hidden, x_row_bytes, kv_row_bytes, packed_rows != 0);
+}
+extern "C" int kvpr_debug_prefill_runs(kvpr_ctx* c) { return c->prefill_runs; }
