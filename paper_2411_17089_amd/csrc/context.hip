@@ -209,6 +209,7 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
         if (c->qx) if (int rc = kvpr::launch_fill_u16(x_stage, (size_t)seq * xsb / 2, 0xFFFF, c->compute)) return rc;
         if (c->qkv) if (int rc = kvpr::launch_fill_u16(kv_stage, (size_t)seq * ksb / 2, 0xFFFF, c->compute)) return rc;
     }
+    const bool w_again = fence_copy_to_start && l > 0;       // the recomputation follows right behind the projection and reads [Wk; Wv]
     const size_t x_bytes = (size_t)l * xsb, kv_bytes = (size_t)(seq - l) * ksb;
     const bool small_copy = fence_copy_to_start && x_bytes + kv_bytes <= (l == 0 && !c->qkv ? kSmallCacheCopy : kSmallCopy);
     // the copy of the cache beside the recomputation, if that leaves it compute units (a GEMM workgroup takes a whole one)
@@ -278,10 +279,10 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
         if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::p0], c->compute));
         if (c->llama) {
             if (int rc = kvpr::launch_token_qkv_rope(x_new, w->wqkv, w->bqkv, c->qk32, c->q32, dkv + (size_t)seq * kr, b, h, c->d.head_dim,
-                                                     c->rope_tab, seq, c->compute, c->tok_ws, c->tok_ws_bytes, with_projection, norm))
+                                                     c->rope_tab, seq, c->compute, c->tok_ws, c->tok_ws_bytes, with_projection, norm, w_again))
                 return rc;
         } else if (int rc = kvpr::launch_token_gemm_flags(x_new, w->wqkv, w->bqkv, c->q32, dkv + (size_t)seq * kr, b, 3 * h, h, h,
-                                                          2 * (int64_t)h, 2, c->compute, c->tok_ws, c->tok_ws_bytes, nullptr,
+                                                          2 * (int64_t)h, 2 | (w_again ? 4 : 0), c->compute, c->tok_ws, c->tok_ws_bytes, nullptr,
                                                           with_projection, norm)) {
             return rc;
         }

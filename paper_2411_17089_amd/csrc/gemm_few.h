@@ -25,6 +25,8 @@ struct FewTokens {
     // rotary form: (cos, sin) of the rows' position, head_dim / 2 pairs
     const float2* rope = nullptr;
     int head_dim = 0;
+    // the kernels behind read (most of) W again
+    bool w_again = false;
 };
 
 // Plain.  Gated: W is [gate; up] of N / 2 features each (a multiple of 4), y16 [M, N / 2] = silu(x gate^T) * (x up^T), no bias,

@@ -61,7 +61,13 @@ __device__ __forceinline__ float fold16(float a, float b) {
 // copies costs a launch of 7 us 0.2).
 enum class FewExtra { none, norm, copies };
 
-template <int MQ, int P, FewForm FORM, int WAVES, FewExtra EXTRA>
+// AGAIN: ordinary loads of W instead of non-temporal ones, for weights that the next kernels read again.  From memory the
+// non-temporal ones are the faster (12288 x 4096, M = 1: 17.7 us against 18.6, 7168 x 28672: 64 against 71), but they leave nothing
+// behind in the Infinity Cache.  In a single-layer call the recomputation reads [Wk; Wv] right after the projection has, and with few
+// rows that read is what it takes.  6 layers called in turn, 24 positions, split 10, non-temporal / ordinary (kernels for up to 64
+// rows): hidden 4096, batch 1 60.0 / 56.7 us (78.7), hidden 5120, batch 4 97.4 / 87.8 (104.2), hidden 7168, batch 6 166 / 155 (159);
+// no recomputation: hidden 5120, batch 1 47.6 / 49.5, hidden 7168, batch 1 78 / 82.
+template <int MQ, int P, FewForm FORM, int WAVES, FewExtra EXTRA, bool AGAIN = false>
 __global__ __launch_bounds__(WAVES * 64) void few_tokens(const FewTokens a, int units, int segments, int grid, const CopyJob beside) {
     // rows four at a time: enough of them that a wave has at least four loads in flight behind the ones it works on
     constexpr int R = P == 1 ? 4 : P == 2 ? 2 : 1;
@@ -122,7 +128,10 @@ __global__ __launch_bounds__(WAVES * 64) void few_tokens(const FewTokens a, int 
                     for (int r = 0; r < R; ++r) {
                         const _Float16* p = a.W + (int64_t)min(row_of(min(st * R + r, groups - 1)) + r4, a.N - 1) * a.K + k0;
 #pragma unroll
-                        for (int u = 0; u < CNT; ++u) f.w[r][u] = __builtin_nontemporal_load(reinterpret_cast<const half8*>(p + u * PIECE));
+                        for (int u = 0; u < CNT; ++u) {
+                            const half8* from = reinterpret_cast<const half8*>(p + u * PIECE);
+                            f.w[r][u] = AGAIN ? *from : __builtin_nontemporal_load(from);
+                        }
                     }
                 };
                 auto multiply = [&](const Rows& f, int st) {
@@ -363,8 +372,11 @@ int launch(const FewTokens& a, const FewPlan& p, hipStream_t st, const CopyJob& 
     auto kern = few_tokens<MQ, P, FORM, WAVES, FewExtra::none>;
     if constexpr (WAVES == 8) {
         if (a.norm) kern = few_tokens<MQ, P, FORM, WAVES, FewExtra::norm>;
-        if constexpr (FORM != FewForm::gated)
+        if constexpr (FORM != FewForm::gated) {
             if (beside.blocks) kern = few_tokens<MQ, P, FORM, WAVES, FewExtra::copies>;
+            if (a.w_again && !a.norm)
+                kern = beside.blocks ? few_tokens<MQ, P, FORM, WAVES, FewExtra::copies, true> : few_tokens<MQ, P, FORM, WAVES, FewExtra::none, true>;
+        }
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)(p.grid + beside.blocks)), dim3(WAVES * 64), p.lds, st, a, units, p.segments, p.grid, beside);
     KVPR_HIP(hipGetLastError());

@@ -478,7 +478,8 @@ bool norm_goes_along(const TokenNorm& n, int M, int N, int K) {
     return few_tokens_norm(M, N, K) && !token_gemm_forced() && (((uintptr_t)n.x | (uintptr_t)n.g | (uintptr_t)n.b) & 15) == 0;
 }
 
-// flags bit 0: ReLU; bit 1: calls of this product may take something along, and the others shall give the same bits.
+// flags bit 0: ReLU; bit 1: calls of this product may take something along, and the others shall give the same bits;
+// bit 2: the kernels behind read W again.
 // residual (optional): float16, laid out as y16, added to the float16 outputs.  ws (optional, device): workspace that lets a narrow output split K over several workgroups; its first 4096 bytes must be zero before the first
 // launch that uses it and are zero again when a launch ends; launches that share a workspace must not overlap.
 int launch_token_gemm_flags(const void* x, const void* w, const void* bias, void* y32, void* y16, int M, int N, int K,
@@ -494,6 +495,7 @@ int launch_token_gemm_flags(const void* x, const void* w, const void* bias, void
     if ((along ? few_tokens_along(M, N, K) : takes_few_tokens(M, N, K)) && !token_gemm_forced()) {
         FewTokens a{(const _Float16*)x, (const _Float16*)w, (const _Float16*)bias, (float*)y32, (_Float16*)y16,
                     (const _Float16*)residual, ld16, M, N, K, out_f32_cols, relu};
+        a.w_again = flags & 4;
         if (norm) take_along(a, *norm);
         return launch_few_tokens(a, FewForm::plain, st, beside);
     }
@@ -510,7 +512,7 @@ int launch_token_gemm_flags(const void* x, const void* w, const void* bias, void
 // go through qk32 [M, 2h].
 int launch_token_qkv_rope(const void* x, const void* w, const void* bias, void* qk32, void* q32, void* kv16, int M, int h, int head_dim,
                           const void* table, int pos, hipStream_t st, void* ws, size_t ws_bytes, const CopyJob& beside,
-                          const TokenNorm* norm) {
+                          const TokenNorm* norm, bool w_again) {
     if (norm && !norm_goes_along(*norm, M, 3 * h, h)) {
         if (int rc = launch_norm(*norm, M, h, st)) return rc;
         x = norm->xn;
@@ -521,6 +523,7 @@ int launch_token_qkv_rope(const void* x, const void* w, const void* bias, void* 
                     M, 3 * h, h, h, 0};
         a.rope = (const float2*)table + (size_t)pos * (head_dim / 2);
         a.head_dim = head_dim;
+        a.w_again = w_again;
         if (norm) take_along(a, *norm);
         return launch_few_tokens(a, FewForm::rotary, st, beside);
     }

@@ -41,12 +41,12 @@ struct TokenNorm {
 bool norm_goes_along(const TokenNorm& n, int M, int N, int K);     // in the product's own launch; else in one in front of it
 int launch_norm(const TokenNorm& n, int rows, int h, hipStream_t st);
 int launch_token_gemm_flags(const void* x, const void* w, const void* bias, void* y32, void* y16, int M, int N,
-                            int K, int out_f32_cols, int64_t ld16, int flags /*bit 0: ReLU, bit 1: as with something along*/, hipStream_t st,
+                            int K, int out_f32_cols, int64_t ld16, int flags /*bit 0: ReLU, 1: as with something along, 2: W is read again*/, hipStream_t st,
                             void* ws = nullptr, size_t ws_bytes = 0, const void* residual = nullptr, const CopyJob& beside = CopyJob(),
                             const TokenNorm* norm = nullptr);
 int launch_token_qkv_rope(const void* x, const void* w, const void* bias, void* qk32, void* q32, void* kv16, int M, int h, int head_dim,
                           const void* table, int pos, hipStream_t st, void* ws, size_t ws_bytes, const CopyJob& beside = CopyJob(),
-                          const TokenNorm* norm = nullptr);
+                          const TokenNorm* norm = nullptr, bool w_again = false);
 int launch_token_gemm_gated(const void* x, const void* w, void* mid, void* y, int M, int f, int K, hipStream_t st, void* ws,
                             size_t ws_bytes, const TokenNorm* norm = nullptr);
 size_t token_gemm_workspace_bytes(int M, int N);
