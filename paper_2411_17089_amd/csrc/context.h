@@ -94,6 +94,9 @@ struct kvpr_ctx {
     double keep_warm = 0.0;
     double wall_clock_hz = 0.0;
     int prefill_runs = 0;                // runs of the last prefill helper (read by tests)
+    // how the last layer was enqueued (read by tests)
+    enum Mode { kInOrder = 1, kCacheBesideRecompute = 2, kRowsBesideAttention = 4 };
+    int last_mode = 0;
     int last_parts = 0;                  // parts that the last layer's activations came in by (read by tests)
     int64_t layers_ahead = 0;            // recomputations that ran beside the previous layer (read by tests)
     int cost_model = KVPR_COST_EQ10, granularity = 1;
@@ -104,9 +107,9 @@ struct kvpr_ctx {
     // bytes of one position (all sequences of the batch) as the host store holds it and as it crosses the link
     size_t x_store_bytes() const { return qx ? d.batch * kvpr::int4_row_bytes(d.hidden) : x_row_halfs() * sizeof(half); }
     size_t kv_store_bytes() const { return qkv ? d.batch * kvpr::int4_row_bytes(2 * d.hidden) : kv_row_halfs() * sizeof(half); }
-    // The new token's rows go back to the host on the compute stream, right behind the projections, while they are few: the
-    // copy kernel takes 4 - 8 us there, a hand-over to the store stream costs 15 us of the host's time for each of its two
-    // waits and about 6 us on the compute stream for each of its two markers.  From 256 KiB on the copy is the longer one.
+    // The new token's rows go back to the host on the compute stream while they are few, behind the projections or beside the
+    // attention: by themselves they take 4 - 8 us there, a hand-over to the store stream costs 15 us of the host's time for each of
+    // its two waits and about 6 us on the compute stream for each of its two markers.  From 256 KiB on the copy is the longer one.
     bool inline_store() const { return x_store_bytes() + kv_store_bytes() <= 256 * 1024; }
     int64_t flops_per_pos() const { return 4 * (int64_t)d.batch * d.hidden * d.hidden; }   // Eq. 8
     int plan_chunks() const { return (chunks > 1 && cost_model == KVPR_COST_EQ10) ? chunks : 1; }

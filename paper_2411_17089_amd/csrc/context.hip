@@ -218,6 +218,7 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
     const bool in_order = fence_copy_to_start && !ev && !wf && runs_in_order(c, l, x_bytes, kv_bytes, beside_recompute);
     const bool small = small_copy || in_order;
     const bool at_once = small && !ev;                   // timed: a launch each, with the event in between
+    c->last_mode = in_order ? kvpr_ctx::kInOrder | (beside_recompute ? kvpr_ctx::kCacheBesideRecompute : 0) : 0;
     // In order on the compute stream: behind everything that touched these buffers and rows, which that stream has waited for
     // (copies in front of an attention, store-backs at the end of their layer or step).
     if (!in_order && (fence_copy_to_start || (c->debug & KVPR_DEBUG_POISON))) {
@@ -296,16 +297,19 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
         const void* kv_from = kv_stage + (size_t)seq * ksb;
         char *x_to = c->hx[layer] + (size_t)seq * xsb, *kv_to = c->hkv[layer] + (size_t)seq * ksb;
         if (c->inline_store()) {
-            // in order with everything else that touches these rows, beside the attention or (timed) by itself: the device
-            // buffer is released, and with it the slot's host rows to the copies of the next token, by ev_free behind the
-            // attention
-            if (!ev) {
+            // In order with everything else that touches these rows: the device buffer is released, and with it the slot's host
+            // rows to the copies of the next token, by ev_free behind the attention.  Beside the attention, a launch less, where
+            // the stream has work all along: in the layer pipeline (1 - 4 % of a token at batch 1 - 8) and in calls in order.  Where
+            // the stream waits for copies behind this it is a launch of its own that nothing waits for: beside a short attention
+            // 200 KiB of rows cost 1 - 3 % of the call (hidden 4096, batch 10, split 51 of 51: 174 us, beside 176; waited for 180, 183).
+            if (!ev && (in_order || !fence_copy_to_start)) {
+                c->last_mode |= kvpr_ctx::kRowsBesideAttention;
                 with_attention = kvpr::copy_job(256, kv_from, kv_to, ksb, x_from, x_to, xsb);
                 return debug_sync(c);
             }
-            KVPR_HIP(hipEventRecord(ev->at[LayerEvents::s0], c->compute));
+            if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::s0], c->compute));
             if (int rc = kvpr::launch_copy_bytes(kv_from, kv_to, ksb, c->compute, x_from, x_to, xsb)) return rc;
-            KVPR_HIP(hipEventRecord(ev->at[LayerEvents::s1], c->compute));
+            if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::s1], c->compute));
             return debug_sync(c);
         }
         KVPR_HIP(hipEventRecord(c->ev_proj, c->compute));
@@ -800,6 +804,7 @@ extern "C" int kvpr_debug_streams_replaced(void) { return g_streams_replaced; }
 extern "C" int64_t kvpr_debug_layers_ahead(kvpr_ctx* c) { return c->layers_ahead; }   // since the context was created
 
 extern "C" int kvpr_debug_copy_parts(kvpr_ctx* c) { return c->last_parts; }           // of the last layer that was enqueued
+extern "C" int kvpr_debug_layer_mode(kvpr_ctx* c) { return c->last_mode; }            // likewise: kvpr_ctx::Mode
 
 extern "C" int kvpr_destroy(kvpr_ctx* c) {
     if (!c) return fail(KVPR_E_INVAL, "ctx is null");
