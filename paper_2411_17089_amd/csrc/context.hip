@@ -92,6 +92,38 @@ struct WeightFence {
 // the kernel stays the better one for longer (batch 8, 32 positions, hidden 2048, 2 MiB: 97 -> 84 us).
 constexpr size_t kSmallCopy = size_t(1) << 20, kSmallCacheCopy = 2 * kSmallCopy;
 
+// (measured, like the rates below, and fixed: a call with a split of its own may have no profile)
+constexpr double kLinkRate = 57e9;
+
+// Single-layer call that is not timed, with copies by the DMA engine: parts that the activations come in by, so that the
+// recomputation of one runs while the next is on the link.  In one part it starts when all of them have landed, and where it and the
+// attention over its rows take longer than the rest of the cache, that is what the call waits for.  A part costs the link 16 us.
+// Of 1 to 8 parts those that leave least behind the last activations, the product by its estimate; after milliseconds of idle a
+// long one runs 15 % longer than that (clocks), one of a millisecond 3 %.  Hidden 7168, batch 32, 1024 positions, split 0.75 /
+// 0.85 / 1: 10.62 -> 10.49, 12.1 -> 9.7, 14.2 -> 9.3 ms; hidden 4096, packed store, 0.65 / 0.75 / 0.85: 2.13 -> 1.90, 2.39 -> 1.78,
+// 2.74 -> 1.88; where the cache takes longer, one part as before.
+// (kvpr_set_chunks asks for parts in every call, and the planner then knows of them; the clock keep-alive is meant for one.)
+struct CopyParts {
+    int n;
+    double gain;     // seconds that they save of one part
+};
+CopyParts copy_parts(const kvpr_ctx* c, int l, size_t x_bytes, size_t kv_bytes) {
+    if (l == 0 || c->chunks > 1 || c->keep_warm > 0.0) return {c->chunks, 0.0};
+    const int64_t b = c->d.batch, h = c->d.hidden;
+    const double x = (double)x_bytes / kLinkRate, cache = (double)kv_bytes / kLinkRate, attention = 4.0 * h * b * l / 6.3e12;
+    CopyParts best{1, 0.0};
+    double one = 0.0;
+    for (int n = 1; n <= 8 && l / n >= 8; ++n) {
+        double part = kvpr::gemm_estimate_s((l + n - 1) / n * b, (int)(2 * h), (int)h);
+        part *= n * part > 3e-3 ? 1.15 : 1.03;
+        const double left = std::max(part, n * part - x * (n - 1) / n) + attention;
+        const double t = 16e-6 * (n - 1) + std::max(cache, left);
+        if (n == 1) one = t;
+        if (one - t > best.gain) best = {n, one - t};
+    }
+    return best;
+}
+
 // Single-layer call with few new rows (inline_store): everything on the compute stream.  The copies are workgroups of the
 // launches beside which they belong, activations of the token projection, cache of the recomputation, new rows of the attention;
 // four launches and one event are left of seven launches and ten operations on events (hidden 768, batch 2, 96 positions: 57
@@ -103,10 +135,15 @@ constexpr size_t kSmallCopy = size_t(1) << 20, kSmallCacheCopy = 2 * kSmallCopy;
 //   16 MiB (60 us) 1.07 / 1.11; batch 10 (no kernel for few rows), split 0.4: 1.02 / 1.08
 //   hidden 7168, batch 1, split 0.4: 1 MiB (cache 14 us) 0.96 / 0.87, 4 MiB (recomputation 43 us) 1.13 / 1.12
 //   hidden 7168, batch 3, split 0.75: 2 MiB (cache 15 us) 1.06 / 1.02 (DMA copies start up behind the projection's 47 us)
-// so: up to 1 MiB always, up to 16 MiB while less overlap is lost than the copies' start-up costs behind that projection.  Over
-// hidden 768 - 7168, batch 1 - 10, 0.3 - 16 MiB and four splits (487 calls): 0.80 / 0.84 of the time on average, 1.05 at most.
+// With copies by DMA the activations may come in by parts, and what those gain is lost too: hidden 7168, split 1, batch 3, 9 MiB 0.96 /
+// 1.0 in order, 0.90 / 0.90 in 2 parts; batch 5, split 0.9, 7 MiB 1.01 / 1.05, 0.94 / 0.95.  And where the projection hides the copies'
+// start-up whole, the engines' 57 GB/s beat the kernel's 54 in the end: hidden 7168, cache alone, batch 6, 7 - 10 MiB 0.98 - 1.0 /
+// 1.02 - 1.05, by DMA 0.99 / 1.0.
+// So: up to 1 MiB always, up to 16 MiB while less overlap is lost than the copies' start-up costs behind that projection.  Over
+// hidden 256 - 8192, batch 1 - 64, three stores, both architectures, 0.25 - 20 MiB and eight splits (460 calls): 0.83 / 0.84 of the
+// time on average, 1.03 at most.
 constexpr size_t kInOrderCopy = 16 * kSmallCopy;
-constexpr double kStartUp = 32e-6, kHidden = 0.45, kLinkRate = 57e9, kFewRate = 6.5e12, kWeightRate = 4.6e12;
+constexpr double kStartUp = 32e-6, kHidden = 0.45, kFewRate = 6.5e12, kWeightRate = 4.6e12;
 
 bool runs_in_order(const kvpr_ctx* c, int l, size_t x_bytes, size_t kv_bytes, bool beside_recompute) {
     if (!c->inline_store() || x_bytes + kv_bytes > kInOrderCopy) return false;
@@ -116,7 +153,10 @@ bool runs_in_order(const kvpr_ctx* c, int l, size_t x_bytes, size_t kv_bytes, bo
     double lost = 0.0;
     if (l > 0 && !beside_recompute) lost += std::min(kvpr::gemm_estimate_s((int64_t)l * b, 2 * h, h), (double)kv_bytes / kLinkRate);
     if (!kvpr::few_tokens_along(b, 3 * h, h)) lost += 4e-6 + 6.0 * h * h / kWeightRate;
-    return lost < kStartUp - kHidden * 6.0 * h * h / kFewRate;
+    lost += copy_parts(c, l, x_bytes, kv_bytes).gain;
+    const double projection = 6.0 * h * h / kFewRate;
+    if (l == 0 && projection > 45e-6 && kv_bytes > 6 * kSmallCopy) return false;
+    return lost < kStartUp - kHidden * projection;
 }
 
 // Layer pipeline with resident weights: the recomputation needs nothing of this step's hidden states, so it may run on the
@@ -135,30 +175,6 @@ bool runs_ahead(const kvpr_ctx* c, int l) {
     if (c->d.n_layers < 2 || streamed < 128000000 || c->flops_per_pos() * l < 2000000000) return false;
     const int64_t rows = (int64_t)l * c->d.batch / std::min(c->chunks, std::max(1, l / 8));
     return kvpr::gemm_workgroups(rows, 2 * c->d.hidden) * 4 <= 3 * kvpr::compute_units();
-}
-
-// Single-layer call that is not timed, with copies by the DMA engine: parts that the activations come in by, so that the
-// recomputation of one runs while the next is on the link.  In one part it starts when all of them have landed, and where it and the
-// attention over its rows take longer than the rest of the cache, that is what the call waits for.  A part costs the link 16 us.
-// Of 1 to 8 parts those that leave least behind the last activations, the product by its estimate; after milliseconds of idle a
-// long one runs 15 % longer than that (clocks), one of a millisecond 3 %.  Hidden 7168, batch 32, 1024 positions, split 0.75 /
-// 0.85 / 1: 10.62 -> 10.49, 12.1 -> 9.7, 14.2 -> 9.3 ms; hidden 4096, packed store, 0.65 / 0.75 / 0.85: 2.13 -> 1.90, 2.39 -> 1.78,
-// 2.74 -> 1.88; where the cache takes longer, one part as before.
-// (kvpr_set_chunks asks for parts in every call, and the planner then knows of them; the clock keep-alive is meant for one.)
-int copy_parts(const kvpr_ctx* c, int l, size_t x_bytes, size_t kv_bytes) {
-    if (l == 0 || c->chunks > 1 || c->keep_warm > 0.0) return c->chunks;
-    const int64_t b = c->d.batch, h = c->d.hidden;
-    const double x = (double)x_bytes / kLinkRate, cache = (double)kv_bytes / kLinkRate, attention = 4.0 * h * b * l / 6.3e12;
-    int best = 1;
-    double least = 0.0;
-    for (int n = 1; n <= 8 && l / n >= 8; ++n) {
-        double part = kvpr::gemm_estimate_s((l + n - 1) / n * b, (int)(2 * h), (int)h);
-        part *= n * part > 3e-3 ? 1.15 : 1.03;
-        const double left = std::max(part, n * part - x * (n - 1) / n) + attention;
-        const double t = 16e-6 * (n - 1) + std::max(cache, left);
-        if (n == 1 || t < least) { least = t; best = n; }
-    }
-    return best;
 }
 
 int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weights* w, const half* x_new, half* out, int buf,
@@ -237,7 +253,7 @@ int enqueue_layer(kvpr_ctx* c, int layer, int seq, int l, const kvpr_layer_weigh
     if (ev) KVPR_HIP(hipEventRecord(ev->at[LayerEvents::c0], c->copy));
     // chunk boundaries: equal parts of [0, l) rounded down to multiples of 8 positions (whole GEMM tile rows
     // at batch 32); a single chunk is the paper's schedule
-    const int parts = fence_copy_to_start && !ev && !wf ? copy_parts(c, l, x_bytes, kv_bytes) : c->chunks;
+    const int parts = fence_copy_to_start && !ev && !wf ? copy_parts(c, l, x_bytes, kv_bytes).n : c->chunks;
     int nchunk = (l > 0) ? (small ? 1 : std::min(parts, std::max(1, l / 8))) : 0;
     int bound[kvpr_ctx::kMaxChunks + 1];
     c->last_parts = nchunk;

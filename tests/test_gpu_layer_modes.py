@@ -37,7 +37,9 @@ BESIDE_PROJECTION = IN_ORDER | ROWS_BESIDE_ATTENTION
 @pytest.mark.parametrize("b,h,H,s,l,mode", [
     (2, 768, 12, 96, 40, ALL), (2, 768, 12, 96, 0, BESIDE_PROJECTION), (56, 768, 12, 20, 10, ALL), (64, 768, 12, 20, 10, 0),
     (4, 1024, 8, 60, 60, ALL), (8, 1024, 8, 300, 50, ALL), (8, 1024, 8, 700, 100, 0), (3, 768, 12, 4000, 1000, 0), (1, 768, 12, 6000, 4000, BESIDE_PROJECTION),
-    (8, 2048, 16, 40, 20, ALL), (4, 4096, 32, 100, 50, BESIDE_PROJECTION), (8, 4096, 32, 300, 100, 0)])
+    (8, 2048, 16, 40, 20, ALL), (4, 4096, 32, 100, 50, BESIDE_PROJECTION), (8, 4096, 32, 300, 100, 0),
+    (3, 7168, 56, 40, 40, ALL), (3, 7168, 56, 217, 217, 0),                   # parts gain more
+    (6, 7168, 56, 20, 0, BESIDE_PROJECTION), (6, 7168, 56, 50, 0, 0)])        # cache alone behind a long projection
 def test_single_layer_call(k, b, h, H, s, l, mode):
     print(f"mode b={b} h={h} s={s} l={l}", flush=True)
     ctx, w, x, out = _context(k, b, h, H, s)
