@@ -53,6 +53,18 @@ def test_single_layer_call(k, b, h, H, s, l, mode):
         k.kvpr_destroy(ctx)
 
 
+def test_unpacking_in_front_of_the_recomputation(k):
+    """Packed activations of 13014 rows: unpacking and product take longer than a call in order saves, beside a cache that hides them."""
+    b, h, H, s, l = 9, 768, 12, 1808, 1446
+    ctx, w, x, out = _context(k, b, h, H, s, flags=k.KVPR_STORE_INT4)
+    try:
+        k.kvpr_layer_decode(ctx, 0, s, l, k.make_weights(**w), x, out)
+        torch.cuda.synchronize()
+        assert k.lib.kvpr_debug_layer_mode(ctx) == 0
+    finally:
+        k.kvpr_destroy(ctx)
+
+
 @pytest.mark.parametrize("b,mode", [(4, ROWS_BESIDE_ATTENTION), (64, 0)])
 def test_layer_of_a_step(k, b, mode):
     h, H, s = 1024, 8, 40
