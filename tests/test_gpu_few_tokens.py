@@ -1,5 +1,6 @@
 """Token GEMM for at most 8 rows, with the norm in front and the rotation behind: K in fewer pieces than waves, in even and uneven runs, in several segments and in runs of
-4 KiB; outputs that are no multiple of 4, fewer than 4, and more than one workgroup's sums can hold."""
+4 KiB; outputs that are no multiple of 4, fewer than 4, and more than one workgroup's sums can hold.  (Of less than 1024 columns the
+kernels for up to 64 rows take the products with 5 to 8 rows, and the narrow ones with fewer.)"""
 import ctypes
 
 import numpy as np
@@ -112,3 +113,74 @@ def test_norm_and_rotation_in_the_projection(k, arch, h, H, b):
             assert rel_err(view(kvp, b * 2 * h)[s], np.asarray(trace["kv_new"]).reshape(-1)) <= 5e-3
         finally:
             k.kvpr_destroy(ctx)
+
+
+def _ffn_only(k, arch, b, h, width, ffn, seed):
+    """One decoder layer whose attention block adds nothing (Wo = 0): result, stored rows of the new token, and what float64 gives for
+    them with the roundings to float16 where the library rounds."""
+    s, llama = 5, arch == "llama"
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    rand = lambda *shape, scale, mean=0.0: (torch.randn(shape, generator=g, device="cuda") * scale + mean).half()   # noqa: E731
+    w = {"wqkv": rand(3 * h, h, scale=0.02), "wo": torch.zeros((h, h), dtype=torch.float16, device="cuda"), "ln1_g": rand(h, scale=0.05, mean=1.0),
+         "ln2_g": rand(h, scale=0.05, mean=1.0), "w1": rand((2 if llama else 1) * ffn, h, scale=0.02), "w2": rand(h, ffn, scale=0.02)}
+    if not llama:
+        w.update(bqkv=rand(3 * h, scale=0.1), ln1_b=rand(h, scale=0.02), ln2_b=rand(h, scale=0.02), b1=rand(ffn, scale=0.1), b2=rand(h, scale=0.1))
+    x, rows = rand(b, h, scale=1.0), rand(s, b, h, scale=1.0).cpu().numpy()
+    ctx = k.kvpr_create(1, h, h // width, width, ffn, b, s + 2, arch=k.KVPR_ARCH_LLAMA if llama else k.KVPR_ARCH_OPT)
+    try:
+        k.kvpr_store_write(ctx, 0, 0, s, rows, None)
+        k.kvpr_store_prefill_kv(ctx, 0, s, k.make_weights(**w))
+        out = torch.full((b, h), float("nan"), dtype=torch.float16, device="cuda")
+        k.kvpr_decode_step(ctx, s, [k.make_weights(**w)], x, out, [3])
+        torch.cuda.synchronize()
+        xp, kvp = k.kvpr_store_ptrs(ctx, 0)
+        row = lambda p, n: torch.from_numpy(np.frombuffer((ctypes.c_ubyte * (b * n * 2)).from_address(p + s * b * n * 2), np.float16).copy().reshape(b, n)).cuda()   # noqa: E731
+        xn, kv_new = row(xp, h), row(kvp, 2 * h)
+    finally:
+        k.kvpr_destroy(ctx)
+    d = {n: t.double() for n, t in w.items()}
+    half = lambda t: t.half().double()   # noqa: E731
+
+    def norm(i):
+        t = x.double()
+        t = t if llama else t - t.mean(1, keepdim=True)
+        t = t * torch.rsqrt((t * t).mean(1, keepdim=True) + 1e-5) * d[f"ln{i}_g"]
+        return t if llama else t + d[f"ln{i}_b"]
+    a = half(norm(2)) @ d["w1"].T
+    if llama:
+        gate, up = half(a[:, :ffn]), half(a[:, ffn:])
+        a = half(gate / (1.0 + torch.exp(-gate)) * up)
+    else:
+        a = half(torch.relu(a + d["b1"]))
+    want = x.double() + half(a @ d["w2"].T + (0.0 if llama else d["b2"]))
+    wv, bv = d["wqkv"][2 * h:], torch.zeros(h, device="cuda").double() if llama else d["bqkv"][2 * h:]
+    v = xn.double() @ wv.T + bv
+    sums = h * 2.0 ** -24 * (xn.double().abs() @ wv.abs().T + bv.abs())         # float32 sums of h products in any order
+    return out.double(), want, xn.double(), norm(1), kv_new[:, h:].double(), v, sums
+
+
+def _check_ffn_only(out, want, xn, xn_want, v, v_want, sums):
+    # one rounding to float16; mean and variance of up to 8192 values of order 1 in float32, and four operations of 2^-24 on values
+    # up to 6 (2e-5 is eight times that)
+    assert bool(((xn - xn_want).abs() <= (2.0 ** -11 + 1e-5) * xn_want.abs() + 2e-5).all())
+    # a product with the row that was stored, one rounding
+    assert bool(((v - v_want).abs() <= sums + 2.0 ** -11 * v_want.abs() + 2.0 ** -24).all())
+    # a value next to a rounding boundary may fall either way: 2^-11 of a normalised value or an activation, summed over the features
+    assert rel_err(out.cpu().numpy(), want.cpu().numpy()) <= 5e-3                # the bound of the stack tests
+
+
+@pytest.mark.parametrize("h", [4096, 5120, 6144, 7168, 8192])                    # 4 to 8 pieces of K a wave
+@pytest.mark.parametrize("b", [1, 4, 5, 8])
+@pytest.mark.parametrize("arch", ["opt", "llama"])
+def test_norm_along_with_wide_rows(k, arch, h, b):
+    print(f"norm along, wide rows: {arch} h={h} b={b}", flush=True)
+    _check_ffn_only(*_ffn_only(k, arch, b, h, 128, 256, h + b))
+
+
+# hidden 1024 and more: with 5 to 8 rows too the gated product is the kernel's.  63616 features are 63 units of rows for each of 256
+# compute units: two workgroups of 32 would need more LDS than a launch gets
+@pytest.mark.parametrize("h,ffn", [(1024, 128), (1152, 1152), (1024, 63616), (5120, 13824)])
+@pytest.mark.parametrize("b", [4, 5, 8])
+def test_gated_product(k, b, h, ffn):
+    print(f"gated product h={h} ffn={ffn} b={b}", flush=True)
+    _check_ffn_only(*_ffn_only(k, "llama", b, h, 128, ffn, ffn + b))

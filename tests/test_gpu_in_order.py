@@ -18,8 +18,9 @@ def k():
     return k
 
 
-# (batch, hidden, heads): 8 and 9 rows are the two sides of the token GEMMs; hidden 384, batch 3 has packed rows of 8-byte pieces
-@pytest.mark.parametrize("b,h,H", [(2, 256, 2), (8, 512, 4), (9, 512, 4), (3, 384, 3)])
+# (batch, hidden, heads): 8 and 9 rows at hidden 1024 are the two sides of the token GEMMs, at hidden 512 both take the one for up to
+# 64 rows; hidden 384, batch 3 has packed rows of 8-byte pieces.  (test_gpu_layer_modes.py asserts which calls are in order.)
+@pytest.mark.parametrize("b,h,H", [(2, 256, 2), (8, 512, 4), (9, 512, 4), (3, 384, 3), (8, 1024, 8), (5, 1024, 8), (9, 1024, 8)])
 @pytest.mark.parametrize("packed", [False, True])
 @pytest.mark.parametrize("s,l", [(70, 0), (70, 30), (70, 70), (1400, 300), (3000, 1500)])
 def test_rows_written_and_read_in_either_order(k, b, h, H, packed, s, l):

@@ -1,5 +1,6 @@
-"""The prefill helper in runs whose copies go along with the products: one to seven runs, the last position count that goes in runs
-and the first that goes in one piece, against one product over all positions."""
+"""The prefill helper in runs whose copies go along with the products and in one piece: one to seven runs, the last position count that
+goes in runs and the first above them, against one product over all positions.  (test_gpu_prefill_rows.py asserts the number of
+runs.)"""
 import pytest
 
 import test_gpu_prefill_runs as whole
