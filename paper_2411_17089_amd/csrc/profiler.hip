@@ -149,10 +149,10 @@ extern "C" int kvpr_profile(kvpr_ctx* c, int batch, int seq, kvpr_profile_t* out
                 return kvpr::launch_attention(c->q32, dkv, c->z16, c->attn_ws, S, c->d.batch, h, c->d.n_heads, c->compute); }, &t);
         if (!rc) p.attn_bytes_per_s = (double)S * c->d.batch * 2 * h * sizeof(half) / t;
         // the rest of a layer's GPU work besides the recomputation: projections, attention, FFN (random weights), with the
-        // epilogues that a decoder layer launches
+        // residuals, activations and gate that a decoder layer has in its products; without its norms and its rotation
         if (!rc) rc = time_median(c->compute, 5, [&]() -> int {
                 const int b = c->d.batch, f = c->d.ffn_dim;
-                if (int r = kvpr::launch_token_gemm_flags(c->z16, wtmp, nullptr, c->q32, dkv, b, 3 * h, h, h, 2 * (int64_t)h, 0, c->compute, c->tok_ws, c->tok_ws_bytes)) return r;
+                if (int r = kvpr::launch_token_gemm_flags(c->z16, wtmp, nullptr, c->q32, dkv, b, 3 * h, h, h, 2 * (int64_t)h, 2, c->compute, c->tok_ws, c->tok_ws_bytes)) return r;
                 if (int r = kvpr::launch_attention(c->q32, dkv, c->z16, c->attn_ws, S, b, h, c->d.n_heads, c->compute)) return r;
                 if (int r = kvpr::launch_token_gemm_flags(c->z16, wtmp, nullptr, nullptr, dkv, b, h, h, 0, h, 0, c->compute, c->tok_ws, c->tok_ws_bytes, c->resid)) return r;
                 if (f > 0) {
