@@ -140,7 +140,9 @@ typedef struct {
 } kvpr_layer_weights;
 
 /* Per-layer timing, milliseconds from HIP events (same categories as the paper's
- * runtime breakdown figure: load-activation, load-cache, compute, store). */
+ * runtime breakdown figure: load-activation, load-cache, compute, store).  A timed call always runs on three streams, copies
+ * by the DMA engines in one part (small ones by a kernel): an untimed kvpr_layer_decode with little to copy runs in order on
+ * the compute stream instead, and with much to copy may bring the activations in by parts, and is then the faster one. */
 typedef struct {
     float ms_act_copy;   /* H2D of X[0:l]                                              */
     float ms_kv_copy;    /* H2D of KV[l:s]                                             */
@@ -234,7 +236,7 @@ int kvpr_cost(const kvpr_profile_t* prof, int cost_model, int split, int batch, 
  * (1..32; 1 = the paper's schedule) and the recomputation of part j starts as soon as part j has
  * landed, while the later parts and then the cache are still on the link.  Results are unchanged.
  * (With chunks = 1 and the clock keep-alive off, an untimed kvpr_layer_decode may use parts too, where it would
- * otherwise wait for the recomputation; timed calls and the planner keep one.)
+ * otherwise wait for the recomputation; timed calls, calls while kvpr_set_adaptive measures and the planner keep one.)
  * kvpr_cost_chunked / kvpr_plan_split_chunked are Eq. 10 / Eq. 11 for that schedule: with
  * t_act, t_kv, t_rc as in Eq. 10, part j's GEMM starts at max(j*t_act/chunks, end of part j-1)
  * and takes t_rc/chunks; t = max(end of the last GEMM, t_act + t_kv).  chunks = 1 gives Eq. 10. */
@@ -263,7 +265,9 @@ int kvpr_plan_split_linear(const kvpr_profile_t* prof, int cost_model, int chunk
  * events around its copies and its recompute GEMM (no waiting); the next planned split (split = -1) first
  * folds the samples of all finished layers into the context's profile with kvpr_adapt_update.  alpha = 0
  * (the default) turns it off.  With a chunked activation copy only the link rate is adapted; where kvpr_decode_step runs
- * recomputations beside the previous layer, the first layer's stays in line and gives the GEMM rate.
+ * recomputations beside the previous layer, the first layer's stays in line and gives the GEMM rate.  A layer that is measured
+ * takes the schedule of a timed call (kvpr_layer_timing), so a context that adapts in every call gives up what untimed
+ * single-layer calls gain over it; alpha may be set back to 0 once the rates have settled.
  * kvpr_get_profile: the context's current profile, after folding in finished samples. */
 int kvpr_adapt_update(kvpr_profile_t* prof, double alpha, int64_t link_bytes, double link_seconds,
                       int64_t gemm_flops, double gemm_seconds);

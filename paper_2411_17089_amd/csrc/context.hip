@@ -140,8 +140,8 @@ CopyParts copy_parts(const kvpr_ctx* c, int l, size_t x_bytes, size_t kv_bytes) 
 // start-up whole, the engines' 57 GB/s beat the kernel's 54 in the end: hidden 7168, cache alone, batch 6, 7 - 10 MiB 0.98 - 1.0 /
 // 1.02 - 1.05, by DMA 0.99 / 1.0.
 // So: up to 1 MiB always, up to 16 MiB while less overlap is lost than the copies' start-up costs behind that projection.  Over
-// hidden 256 - 8192, batch 1 - 64, three stores, both architectures, 0.25 - 20 MiB and eight splits (460 calls): 0.83 / 0.84 of the
-// time on average, 1.03 at most.
+// hidden 256 - 8192, batch 1 - 64, three stores, both architectures, 0.25 - 20 MiB and eight splits (460 calls): 0.84 / 0.84 of the
+// time on average; 6 are above 1.02, 1.03 / 1.06 at most (hidden 7168, batch 6, cache alone of 3 - 4 MiB).
 constexpr size_t kInOrderCopy = 16 * kSmallCopy;
 constexpr double kStartUp = 32e-6, kHidden = 0.45, kFewRate = 6.5e12, kWeightRate = 4.6e12;
 
