@@ -67,11 +67,11 @@ constexpr double kPrefillFirst = 1.5 * (1 << 20);     // bytes of activations of
 constexpr int kPrefillRuns = 24;
 // Above this many bytes of rows the helper stays one copy, one product, one copy.  The memory of a context that was destroyed
 // before is given back in the background for some 20 ms, and copies by the DMA engines meanwhile run at 30 instead of 57 GB/s (with
-// or without this helper; not if the old contexts are kept or 0.1 s pass).  Small contexts are done with that at once: in 24
-// contexts one after the other one of the first three decodes was slow in 0 - 2 either way up to 128 MiB of rows; the line is drawn
-// below that.  With 256 MiB it was in 7 with runs and in 1 without, because the slow helper covers that time: what the runs gain there
-// (30.4 -> 20.5 ms for 1024 positions, batch 32, hidden 7168) a program that makes one large context after the other would lose in the
-// decodes that follow.
+// or without this helper; not if the old contexts are kept or 0.1 s pass).  Small contexts are done with that at once; the slow helper
+// covers that time for the large ones, and a fast one does not.  Contexts one after the other of which one of the first three decodes
+// was slow, in runs / in one piece: 37, 64 and 94 MiB of rows 0 / 1 of 144, 105 MiB 1 / 0 of 60, 125 and 127 MiB 14 and 4 / 0 of 60, 175
+// MiB 11 / 5 of 60.  What the runs gain beyond (30.4 -> 20.5 ms for 1024 positions, batch 32, hidden 7168) a program that makes one
+// large context after the other would lose in the decodes that follow.
 constexpr size_t kPrefillInRuns = size_t(96) << 20;
 
 // Positions go in runs whose copies are workgroups of the products' launches (0: one DMA copy in, one product, one DMA copy out).  A
